@@ -28,6 +28,7 @@
 
 #define GLMR_SUB 64   // bins per subtile (mask word)
 #define GLMR_TT 256   // bins per time tile of the likelihood kernel
+#define GLMR_GW 1024  // bins per window of the spike lists
 
 // Element (i, t) of a chunk's weights W (neuron i < Np, chunk-local bin t < L):
 //   layout 0  row-major [Np][L];
@@ -94,6 +95,8 @@ hipError_t launch_ingest_scatter(const IngestBufs& b, hipStream_t st);
 hipError_t launch_ingest_sort(const IngestBufs& b, hipStream_t st);
 hipError_t launch_ingest_masks(const IngestBufs& b, uint64_t* masks, int planes, int64_t Np,
                                hipStream_t st);
+// exclusive scan of cnt[0 .. n) into off[0 .. n], off[n] the total; tmp of ingest_scan_tmp_len(n)
+hipError_t launch_scan_i32(const int32_t* cnt, int64_t n, int64_t* tmp, int32_t* off, hipStream_t st);
 hipError_t launch_digest_u64(const uint64_t* p, int64_t n_outer, int64_t inner, int64_t ld, int64_t cols,
                              unsigned long long* out, hipStream_t st);
 
@@ -147,18 +150,32 @@ struct CarryArgs {
 };
 hipError_t launch_carries(const CarryArgs& c, hipStream_t st);
 
+// Spike lists of a raster, from its masks (recur.hip).
+struct ListArgs {
+  const uint64_t* masks;   // [planes][NS][Np]
+  int planes;
+  int64_t NS, Np;
+  int32_t* wcnt;           // [windows] groups of four entries
+  int32_t* woff;           // [windows + 1] their exclusive scan
+  int32_t* end2;           // [windows][Np] end of a neuron's groups (end2[-1] = 0)
+  uint16_t* ent2;          // [groups + 1][4] window-major entries
+};
+hipError_t launch_list_count(const ListArgs& a, hipStream_t st);
+hipError_t launch_list_windows(const ListArgs& a, hipStream_t st);
+int64_t gather_blocks(int64_t cols, int64_t Np);
+
 struct SpikeTermArgs {
   const uint64_t* masks;
   int planes;
-  const int32_t* seg_off;
-  const uint16_t* seg_ent;
+  const int32_t* end2;     // window-major lists of the recorded raster
+  const uint16_t* ent2;
   const double* C64;
   const double* CY64;      // nullable: then dsigY not computed
   const Tables* tab;
   double ctau;
-  int64_t NS, Np, NIB;
+  int64_t NS, Np;
   int splits;              // time splits
-  double* part;            // [splits][Np][Np] (and a second block for Y)
+  double* part;            // [splits][Np][Np]
   double* dsig;            // [Np][Np]
   double* dsigY;           // [Np][Np] or null
   EvSlots ev;              // event grid: left limits at the events

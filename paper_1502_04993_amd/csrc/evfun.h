@@ -111,10 +111,11 @@ struct Slot {
   double delta, eh, c1, c2, c3, c4, c5, c6, e1, xi;
 };
 
-GLMR_HD inline Slot slot_consts(double delta) {
+// the part that the short-interval branch uses, eh = e^{-delta / 2}
+GLMR_HD inline Slot slot_short(double delta, double eh) {
   Slot q;
   q.delta = delta;
-  q.eh = exp(-0.5 * delta);
+  q.eh = eh;
   const double d2 = delta * delta;
   q.c1 = d2 * (1.0 / 24.0);
   q.c2 = d2 * d2 * (1.0 / 1920.0);
@@ -122,6 +123,12 @@ GLMR_HD inline Slot slot_consts(double delta) {
   q.c4 = d2 * d2 * d2 * d2 * (1.0 / 92897280.0);
   q.c5 = q.c4 * d2 * (1.0 / 440.0);   // delta^10 / (4^5 11!)
   q.c6 = q.c5 * d2 * (1.0 / 624.0);   // delta^12 / (4^6 13!)
+  q.e1 = q.xi = 0.0;
+  return q;
+}
+
+GLMR_HD inline Slot slot_consts(double delta) {
+  Slot q = slot_short(delta, exp(-0.5 * delta));
   q.e1 = -expm1(-delta);  // 1 - xi, exact for short intervals
   q.xi = exp(-delta);
   return q;
@@ -129,14 +136,14 @@ GLMR_HD inline Slot slot_consts(double delta) {
 
 GLMR_HD inline void interval_long(double D, const Slot& q, double* F, double* H);
 
-// F and H of one interval of length q.delta (in units of tau) that starts with
-// potential offset D; delta = 0 gives 0 for both.
-GLMR_HD inline void interval(double D, const Slot& q, double* F, double* H) {
+// The short-interval branch (and the empty interval) from slot_short's
+// constants; returns whether it applies.
+GLMR_HD inline bool interval_short(double D, const Slot& q, double* F, double* H) {
   const double delta = q.delta;
   if (!(delta > 0.0)) {
     *F = 0.0;
     *H = 0.0;
-    return;
+    return true;
   }
   const double u = D * q.eh;
   if (delta * fmax(1.0, fabs(u)) <= 0.25) {
@@ -165,9 +172,15 @@ GLMR_HD inline void interval(double D, const Slot& q, double* F, double* H) {
     const double g = delta * exp(u);
     *F = g * (1.0 + (q.c1 * T2 + (q.c2 * T4 + (q.c3 * T6 + (q.c4 * T8 + (q.c5 * T10 + q.c6 * T12))))));
     *H = g * q.eh * (1.0 + (q.c1 * Q2 + (q.c2 * Q4 + (q.c3 * Q6 + (q.c4 * Q8 + (q.c5 * Q10 + q.c6 * Q12))))));
-    return;
+    return true;
   }
-  interval_long(D, q, F, H);
+  return false;
+}
+
+// F and H of one interval of length q.delta (in units of tau) that starts with
+// potential offset D; delta = 0 gives 0 for both.
+GLMR_HD inline void interval(double D, const Slot& q, double* F, double* H) {
+  if (!interval_short(D, q, F, H)) interval_long(D, q, F, H);
 }
 
 // Intervals past the short-interval branch (rare between the events of a

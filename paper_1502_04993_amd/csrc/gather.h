@@ -1,0 +1,111 @@
+// Sums over a raster's spikes of one of a window's quantities (gfx950): a tile
+// of 1024 bins x 16 columns (FP64, 128 KB of LDS) holds the quantity, and every
+// neuron adds up the tile's rows at its own spikes in registers, from the
+// window-major spike lists (spikes.hip).
+#pragma once
+
+#include "common.h"
+
+namespace glmr_gather {
+
+constexpr int GW = GLMR_GW;          // bins per window
+constexpr int GI = 16;               // tile columns, lanes of a group
+constexpr int GNT = 1024;            // threads of the gather workgroups
+constexpr int GG = GNT / GI;         // their groups of 16 lanes
+constexpr int TILE = (GW + 1) * GI;  // doubles; the last row is zero
+constexpr int CAP = 3070;            // groups of four entries staged in LDS
+constexpr size_t GATHER_LDS = (size_t)(TILE + CAP + 2) * 8;
+static_assert(GATHER_LDS <= 160 * 1024, "tile and entries fit in a CU's LDS");
+
+// value of v in lane K of the 16-lane group
+template <int K>
+__device__ __forceinline__ int group_bcast(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, 0x150 + K, 0xf, 0xf, false);  // row_newbcast
+}
+
+// A window's share of the lists for the JB neurons of a group (from idx in
+// end2): where they begin, and in lane k the end of neuron k's.
+struct Ends {
+  int begin, end;
+};
+template <int JB>
+__device__ __forceinline__ Ends load_ends(const int32_t* __restrict__ end2, int64_t idx, int il) {
+  return Ends{end2[idx - 1], end2[idx + (il < JB ? il : 0)]};
+}
+
+// acc[k] += the tile's rows at the entries of the group's neuron k: its 16
+// lanes hold 16 tile columns and take one neuron after another; the lists of
+// consecutive neurons follow each other, so the next four entries are always
+// being loaded.
+template <int K, int JB>
+__device__ __forceinline__ void walk(double (&acc)[JB], const double* col, const uint2* es, int& p, uint2& nx, int ends,
+                                     int lim) {
+  if constexpr (K < JB) {
+    const int e0 = group_bcast<K>(ends), end = e0 < lim ? e0 : lim;
+    while (p < end) {
+      const uint2 e = nx;
+      nx = es[++p];
+      const double v0 = col[e.x & 0xffffu], v1 = col[e.x >> 16], v2 = col[e.y & 0xffffu], v3 = col[e.y >> 16];
+      acc[K] += v0;
+      acc[K] += v1;
+      acc[K] += v2;
+      acc[K] += v3;
+    }
+    walk<K + 1, JB>(acc, col, es, p, nx, ends, lim);
+  }
+}
+
+// The window's entries of a workgroup's neurons, groups base .. base + n - 1,
+// pass through LDS in pieces of CAP (one piece up to 3 spikes a neuron and
+// second in 1 ms bins at 1024 neurons).  The first piece is copied with the
+// tile, before its barrier; every thread of the workgroup calls both.
+__device__ __forceinline__ void stage_entries(uint2* es, const uint2* __restrict__ ent, int base, int n) {
+  n = n < CAP ? n : CAP;
+  for (int q = threadIdx.x; q <= n; q += GNT) es[q] = ent[base + q];  // one past the end is loaded ahead
+}
+
+template <int JB>
+__device__ __forceinline__ void gather_lists(double (&acc)[JB], const double* tile, uint2* es,
+                                             const uint2* __restrict__ ent, int base, int n, Ends e, int il,
+                                             bool rows) {
+  const double* col = tile + il;
+  int p = e.begin - base;
+#pragma unroll 1
+  for (int q0 = 0; q0 < n; q0 += CAP) {
+    if (q0 > 0) {
+      __syncthreads();
+      stage_entries(es, ent, base + q0, n - q0);
+      __syncthreads();
+    }
+    if (rows && p >= q0 && p < q0 + CAP) {  // a group that is done stays where its lists ended
+      int pl = p - q0;
+      uint2 nx = es[pl];
+      walk<0, JB>(acc, col, es, pl, nx, e.end - base - q0, CAP);
+      p = pl + q0;
+    }
+  }
+}
+
+// neurons per group of 16 lanes: the smallest that covers them, at most 16
+// (16 FP64 sums a lane; more neurons take further blocks of 1024)
+inline int gather_jb(int64_t Np) {
+  int jb = 1;
+  while (jb < 16 && GG * jb < Np) jb *= 2;
+  return jb;
+}
+
+// workgroups of one time split over `cols` tile columns
+inline int64_t blocks_of(int64_t cols, int64_t Np) {
+  const int jb = gather_jb(Np);
+  return ((cols + GI - 1) / GI) * ((Np + GG * jb - 1) / (GG * jb));
+}
+
+template <typename K, typename A>
+hipError_t run_gather(K kern, const A& a, int64_t blocks, int splits, hipStream_t st) {
+  const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GATHER_LDS);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)splits), dim3(GNT), GATHER_LDS, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace glmr_gather

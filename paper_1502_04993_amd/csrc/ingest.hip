@@ -170,14 +170,16 @@ hipError_t launch_ingest_count(const IngestBufs& b, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_ingest_scan(const IngestBufs& b, hipStream_t st) {
-  const int64_t n = b.NS * b.NIB;
+hipError_t launch_scan_i32(const int32_t* cnt, int64_t n, int64_t* tmp, int32_t* off, hipStream_t st) {
   const int64_t nb = (n + SCAN_CH - 1) / SCAN_CH;
-  hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(SCAN_T), 0, st, b.cnt, n, b.scan_tmp);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SCAN_T), 0, st, b.scan_tmp, nb);
-  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(SCAN_T), 0, st, b.cnt, n, b.scan_tmp, nb,
-                     b.off);
+  hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(SCAN_T), 0, st, cnt, n, tmp);
+  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SCAN_T), 0, st, tmp, nb);
+  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(SCAN_T), 0, st, cnt, n, tmp, nb, off);
   return hipGetLastError();
+}
+
+hipError_t launch_ingest_scan(const IngestBufs& b, hipStream_t st) {
+  return launch_scan_i32(b.cnt, b.NS * b.NIB, b.scan_tmp, b.off, st);
 }
 
 hipError_t launch_ingest_scatter(const IngestBufs& b, hipStream_t st) {

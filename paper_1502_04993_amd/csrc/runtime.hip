@@ -79,6 +79,14 @@ struct glmr_ctx {
   bool all_spiking = false;
   uint64_t raster_digest = 0;  // digest of the recorded masks (and, on the event grid, the slot times)
 
+  // window-major spike lists of the recorded raster (spikes.hip)
+  struct WinList {
+    int32_t* end2 = nullptr;  // allocation; the lists' end2 starts 4 entries in
+    uint16_t* ent2 = nullptr;
+    bool ok = false;
+  };
+  WinList wl;
+
   // event grid (continuous time): slot start times and per-slot tables
   bool evm = false;
   double T0 = 0, T1 = 0, max_gap = 0;
@@ -498,12 +506,58 @@ glmr_status build_resident_trace(glmr_ctx* c, Arena* ar) {
   return GLMR_OK;
 }
 
+
+// The spike lists of the recorded raster; they depend on the spikes only.
+glmr_status ensure_lists(glmr_ctx* c, Arena* ar) {
+  if (c->wl.ok) return GLMR_OK;
+  if (ar)
+    return fail(c, GLMR_ESTATE, "the spike lists do not exist yet: call glmr_set_kernel once on this "
+                                "context before glmr_set_kernel_noalloc");
+  const int64_t nw = (c->NS * 64 + GLMR_GW - 1) / GLMR_GW;
+  ListArgs a{};
+  a.masks = delayed(c) ? c->masks0 : c->masks;
+  a.planes = c->planes;
+  a.NS = c->NS;
+  a.Np = c->Np;
+  int64_t* tmp = nullptr;
+  glmr_status st = GLMR_OK;
+  do {
+    if ((st = dalloc(c, a.wcnt, (size_t)nw)) != GLMR_OK) break;
+    if ((st = dalloc(c, a.woff, (size_t)nw + 1)) != GLMR_OK) break;
+    if ((st = dalloc(c, tmp, (size_t)ingest_scan_tmp_len(nw))) != GLMR_OK) break;
+    int32_t total = 0;
+    if (launch_list_count(a, c->st) != hipSuccess || launch_scan_i32(a.wcnt, nw, tmp, a.woff, c->st) != hipSuccess ||
+        hipMemcpyAsync(&total, a.woff + nw, sizeof total, hipMemcpyDeviceToHost, c->st) != hipSuccess ||
+        hipStreamSynchronize(c->st) != hipSuccess) {
+      st = fail(c, GLMR_EDEVICE, "spike lists: %s", hipGetErrorString(hipGetLastError()));
+      break;
+    }
+    if (!c->wl.end2 && (st = dalloc(c, c->wl.end2, (size_t)(nw * c->Np + 4))) != GLMR_OK) break;
+    if ((st = dalloc(c, c->wl.ent2, 4 * ((size_t)total + 1))) != GLMR_OK) break;
+    a.end2 = c->wl.end2 + 4;
+    a.ent2 = c->wl.ent2;
+    // the entry loads run one group ahead of the lists' end
+    if (launch_list_windows(a, c->st) != hipSuccess ||
+        launch_fill_i32((int32_t*)(a.ent2 + 4 * (size_t)total), 2, 0, c->st) != hipSuccess ||
+        hipStreamSynchronize(c->st) != hipSuccess) {
+      st = fail(c, GLMR_EDEVICE, "spike lists: %s", hipGetErrorString(hipGetLastError()));
+      break;
+    }
+    c->wl.ok = true;
+  } while (false);
+  dfree(c, a.wcnt);
+  dfree(c, a.woff);
+  dfree(c, tmp);
+  return st;
+}
+
 // The per-tau caches: carries, resident trace, spike term.  ar != nullptr:
 // the temporaries come from the static scratch and nothing is allocated (the
 // spike term then takes as many time splits as the scratch holds).
 glmr_status build_kernel_caches(glmr_ctx* c, bool want_y, Arena* ar = nullptr) {
   const double dt = c->dt, tau = c->tau;
   c->have_kernel = false;
+  TRY(ensure_lists(c, ar));
   if (c->evm) {
     want_y = false;
     TRY(build_ev_tables(c, ar));
@@ -570,28 +624,27 @@ glmr_status build_kernel_caches(glmr_ctx* c, bool want_y, Arena* ar = nullptr) {
   const int64_t nij = c->Np * c->Np;
   TRY(persist(c, ar, c->dsig, (size_t)nij));
   if (want_y) TRY(persist(c, ar, c->dsigY, (size_t)nij));
-  int64_t pairs = c->NIB * c->NIB;
-  int splits = (int)std::max<int64_t>(1, std::min<int64_t>((8192 + pairs - 1) / pairs, c->NS));
+  // four rounds of workgroups over the 256 CUs (one a CU: its tile takes 128 KB of LDS)
+  const int64_t windows = (c->NS * 64 + GLMR_GW - 1) / GLMR_GW, blocks = gather_blocks(c->Np, c->Np);
+  int splits = (int)std::max<int64_t>(1, std::min<int64_t>((1024 + blocks - 1) / blocks, windows));
   // bound the partial buffer to ~512 MB (with the static scratch, to what it has left)
   const size_t part_cap = ar ? (ar->cap > ar->used + 256 ? ar->cap - ar->used - 256 : 0) : (512ull << 20);
-  while (splits > 1 && (size_t)splits * nij * 8 * (want_y ? 2 : 1) > part_cap) splits /= 2;
+  while (splits > 1 && (size_t)splits * nij * 8 > part_cap) splits /= 2;
   double* part = nullptr;
   // the self-delay correction reuses it for 64 time splits of Np sums
-  const size_t part_n = std::max<size_t>((size_t)splits * nij * (want_y ? 2 : 1),
-                                         self_delayed(c) ? 64 * (size_t)c->Np : 0);
+  const size_t part_n = std::max<size_t>((size_t)splits * nij, self_delayed(c) ? 64 * (size_t)c->Np : 0);
   TRY(temp_alloc(c, ar, part, part_n));
   SpikeTermArgs sa{};
   sa.masks = c->masks;
   sa.planes = c->planes;
-  sa.seg_off = c->seg_off;
-  sa.seg_ent = c->seg_ent;
+  sa.end2 = c->wl.end2 + 4;  // the rows' spikes stay at their recorded bins
+  sa.ent2 = c->wl.ent2;
   sa.C64 = c->C64;
   sa.CY64 = want_y ? c->CY64 : nullptr;
   sa.tab = c->tab;
   sa.ctau = dt / (tau * tau);
   sa.NS = c->NS;
   sa.Np = c->Np;
-  sa.NIB = c->NIB;
   sa.splits = splits;
   sa.part = part;
   sa.dsig = c->dsig;
@@ -2083,6 +2136,7 @@ glmr_status ingest_pairs(glmr_ctx* c, const int64_t* bin, const int32_t* neuron,
   dfree(c, scan_tmp);
   c->nspk = n;
   c->have_spikes = true;
+  c->wl.ok = false;
   TRY(apply_delays(c));
   c->all_spiking = true;
   for (int i = 0; i < c->N; ++i)
