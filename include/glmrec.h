@@ -76,10 +76,14 @@ typedef enum {
 /* Arithmetic of the trace X, the weights J and the two contractions.
  * Cross-tile sums, the likelihood assembly and the ascent are FP64 in all modes. */
 typedef enum {
-  GLMR_FP64 = 0, /* trace, J, U, lambda in FP64; FP64 MFMA */
-  GLMR_FP32 = 1, /* trace and J in FP32 (the trace rounded stochastically from
-                    FP64); U accumulated on the FP64 MFMA, the gradient
-                    contraction on the FP32 MFMA; exp and lambda sums in FP64 */
+  GLMR_FP64 = 0, /* trace, J, U, lambda in FP64: the potentials by the trace's
+                    recurrence over the spikes of each bin, or on the FP64 MFMA
+                    (rasters of more than 0.12 N + 40 spikes a bin, a self-delay
+                    other than d, more than 8192 neurons) */
+  GLMR_FP32 = 1, /* J and the weights lambda in FP32; by the recurrence the rest
+                    in FP64, on the MFMA (as for FP64) with the trace in FP32
+                    too (rounded stochastically), both contractions on the FP64
+                    MFMA; exp and lambda sums in FP64 */
   GLMR_BF16 = 2, /* trace, J and lambda in BF16 (trace rounded stochastically),
                     MFMA with FP32 accumulation */
   GLMR_FP8 = 3,  /* trace, J and lambda in OCP e4m3 with power-of-two scales,

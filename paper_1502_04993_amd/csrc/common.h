@@ -52,6 +52,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 struct Tables {
   double pw[64];     // a^m
@@ -69,6 +70,7 @@ struct EvSlots {
   const double* left;      // [NS*64] e^{-(t_{k+1} - t_k0)/tau}
   const double* delta;     // [NS*64] (t_{k+1} - t_k)/tau
   const double* edec;      // [NS*64] e^{-(t_{k+1} - t_k)/tau}  (decay over slot k)
+  const double* eh;        // [NS*64] e^{-(t_{k+1} - t_k)/(2 tau)}
   const double* asub;      // [NS]    e^{-(t_{k0+64} - t_k0)/tau}
 };
 
@@ -126,7 +128,7 @@ struct EvTableArgs {
   const double* tslot;
   double tau;
   int64_t NS;
-  double *pw, *ainv, *left, *delta, *edec, *asub;
+  double *pw, *ainv, *left, *delta, *edec, *eh, *asub;
   float* gl;                    // [NS*64][16]: the FP32 evaluation's per-slot table (null: none)
   unsigned long long* maxspan;  // max over subtiles of the span / tau (double bits), zero on entry
 };
@@ -157,11 +159,15 @@ struct ListArgs {
   int64_t NS, Np;
   int32_t* wcnt;           // [windows] groups of four entries
   int32_t* woff;           // [windows + 1] their exclusive scan
+  int32_t* scnt;           // [NS] spikes of a subtile (null: not counted)
+  int32_t* off1;           // [NS + 1] their exclusive scan
+  uint32_t* ent1;          // [spikes + 24] time-major entries (the last 24 zero)
   int32_t* end2;           // [windows][Np] end of a neuron's groups (end2[-1] = 0)
   uint16_t* ent2;          // [groups + 1][4] window-major entries
 };
 hipError_t launch_list_count(const ListArgs& a, hipStream_t st);
 hipError_t launch_list_windows(const ListArgs& a, hipStream_t st);
+hipError_t launch_list_bins(const ListArgs& a, hipStream_t st);
 int64_t gather_blocks(int64_t cols, int64_t Np);
 
 struct SpikeTermArgs {
@@ -262,6 +268,51 @@ struct Gemm2Args {
   EvSlots ev;              // event grid
 };
 hipError_t launch_gemm2(int prec, int tile, const Gemm2Args& a, hipStream_t st);
+
+// The recurrence (FP64, FP32; recur.hip) --------------------------------------
+struct RecFDims {
+  int64_t N, Np, NS, B;
+  int64_t t0;              // first bin of this launch
+  int64_t seg, n_seg;      // bins per segment (16 .. 1024), segments of this launch
+  int64_t seg0;            // index of the first in the row partials
+  int64_t tw;              // bin of W's first row
+  int64_t kc, row0;        // subtiles per row of Dc, its first row's index
+  double a, ctau;
+};
+struct RecFArgs {
+  RecFDims g;
+  const uint32_t* ent1;
+  const int32_t* off1;
+  const void* Jt;          // [Np][Np] J transposed, double or float
+  double *Dc, *Vc;         // [rows][Np] V (and sum_j J y_j) at every kc-th subtile
+  int64_t rows;
+  int fused;               // the segments form theirs themselves (few neurons)
+  const double *C64, *CY64;
+  const double *edec, *delta, *eh;  // event grid (null on the regular grid)
+  void* W;                 // [L][Np] double or float, null: not kept
+  double* rowpart;         // [segments][Np]
+  double* rowpartV;        // dL/dtau (null: not computed)
+};
+hipError_t launch_rec_forward(int prec, const RecFArgs& a, hipStream_t st);
+struct RecGArgs {
+  const void* W;
+  int64_t N, Np, B;
+  int64_t t0, Lc;          // chunk
+  double a;
+  EvSlots ev;
+  const int32_t* end2;
+  const uint16_t* ent2;
+  int n_splits;
+  int64_t wps;             // windows per split
+  void* Gp;                // [n_splits][Np (j)][Np (i)] double
+  double* head;            // [n_splits][Np]
+  const double* C64;
+  double* G64;
+  int64_t NS64;            // slots of the tables (event grid)
+};
+hipError_t launch_rec_gather(int prec, const RecGArgs& a, int first, hipStream_t st);
+hipError_t launch_prepare_t(int prec, int N, int64_t Np, const double* J64, const double* mu, void* Jt, double* Jr,
+                            double* rowscale, hipStream_t st);
 
 // Resident trace (BF16): x built once per tau in two layouts -----------------
 struct ResXArgs {

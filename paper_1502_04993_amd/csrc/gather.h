@@ -1,7 +1,8 @@
 // Sums over a raster's spikes of one of a window's quantities (gfx950): a tile
 // of 1024 bins x 16 columns (FP64, 128 KB of LDS) holds the quantity, and every
 // neuron adds up the tile's rows at its own spikes in registers, from the
-// window-major spike lists (spikes.hip).
+// window-major spike lists (spikes.hip).  Used by the spike term (columns of
+// the trace) and by kernel G of the recurrence (rows of R, recur.hip).
 #pragma once
 
 #include "common.h"
@@ -14,8 +15,10 @@ constexpr int GNT = 1024;            // threads of the gather workgroups
 constexpr int GG = GNT / GI;         // their groups of 16 lanes
 constexpr int TILE = (GW + 1) * GI;  // doubles; the last row is zero
 constexpr int CAP = 3070;            // groups of four entries staged in LDS
-constexpr size_t GATHER_LDS = (size_t)(TILE + CAP + 2) * 8;
-static_assert(GATHER_LDS <= 160 * 1024, "tile and entries fit in a CU's LDS");
+constexpr int SCAN = 2 * 16 * GI;    // doubles of kernel G's scan
+constexpr int ENTRIES = TILE + SCAN; // where the staged entries start (in 8 bytes)
+constexpr size_t GATHER_LDS = (size_t)(ENTRIES + CAP + 2) * 8;
+static_assert(GATHER_LDS <= 160 * 1024, "tile, scan and entries fit in a CU's LDS");
 
 // value of v in lane K of the 16-lane group
 template <int K>
@@ -37,21 +40,38 @@ __device__ __forceinline__ Ends load_ends(const int32_t* __restrict__ end2, int6
 // lanes hold 16 tile columns and take one neuron after another; the lists of
 // consecutive neurons follow each other, so the next four entries are always
 // being loaded.
+// LDS byte address 8 u + base of the low or high half u of e, in one instruction
+__device__ __forceinline__ uint32_t addr_lo(uint32_t e, uint32_t base) {
+  uint32_t a;
+  asm("v_mad_u32_u16 %0, %1, 8, %2" : "=v"(a) : "v"(e), "v"(base));
+  return a;
+}
+__device__ __forceinline__ uint32_t addr_hi(uint32_t e, uint32_t base) {
+  uint32_t a;
+  asm("v_mad_u32_u16 %0, %1, 8, %2 op_sel:[1,0,0,0]" : "=v"(a) : "v"(e), "v"(base));
+  return a;
+}
+typedef __attribute__((address_space(3))) const double lds_double;
+typedef __attribute__((address_space(3))) const u32x2 lds_u32x2;
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+
+// col: byte address of the lane's column; p, lim: of entries
 template <int K, int JB>
-__device__ __forceinline__ void walk(double (&acc)[JB], const double* col, const uint2* es, int& p, uint2& nx, int ends,
-                                     int lim) {
+__device__ __forceinline__ void walk(double (&acc)[JB], uint32_t col, uint32_t& p, u32x2& nx, uint32_t ends,
+                                     uint32_t lim) {
   if constexpr (K < JB) {
-    const int e0 = group_bcast<K>(ends), end = e0 < lim ? e0 : lim;
+    const uint32_t e0 = (uint32_t)group_bcast<K>((int)ends), end = e0 < lim ? e0 : lim;
     while (p < end) {
-      const uint2 e = nx;
-      nx = es[++p];
-      const double v0 = col[e.x & 0xffffu], v1 = col[e.x >> 16], v2 = col[e.y & 0xffffu], v3 = col[e.y >> 16];
-      acc[K] += v0;
-      acc[K] += v1;
-      acc[K] += v2;
-      acc[K] += v3;
+      const u32x2 e = nx;
+      p += 8;
+      nx = *(lds_u32x2*)p;
+      const double v0 = *(lds_double*)addr_lo(e[0], col), v1 = *(lds_double*)addr_hi(e[0], col);
+      const double v2 = *(lds_double*)addr_lo(e[1], col), v3 = *(lds_double*)addr_hi(e[1], col);
+      acc[K] += (v0 + v1) + (v2 + v3);
     }
-    walk<K + 1, JB>(acc, col, es, p, nx, ends, lim);
+    walk<K + 1, JB>(acc, col, p, nx, ends, lim);
   }
 }
 
@@ -65,10 +85,10 @@ __device__ __forceinline__ void stage_entries(uint2* es, const uint2* __restrict
 }
 
 template <int JB>
-__device__ __forceinline__ void gather_lists(double (&acc)[JB], const double* tile, uint2* es,
-                                             const uint2* __restrict__ ent, int base, int n, Ends e, int il,
-                                             bool rows) {
-  const double* col = tile + il;
+__device__ __forceinline__ void gather_lists(double (&acc)[JB], double* lds, const uint2* __restrict__ ent, int base,
+                                             int n, Ends e, int il, bool rows) {
+  uint2* es = (uint2*)(lds + ENTRIES);
+  const uint32_t l0 = lds_addr(lds), col = l0 + 8 * il, e8 = l0 + 8 * ENTRIES;
   int p = e.begin - base;
 #pragma unroll 1
   for (int q0 = 0; q0 < n; q0 += CAP) {
@@ -78,10 +98,11 @@ __device__ __forceinline__ void gather_lists(double (&acc)[JB], const double* ti
       __syncthreads();
     }
     if (rows && p >= q0 && p < q0 + CAP) {  // a group that is done stays where its lists ended
-      int pl = p - q0;
-      uint2 nx = es[pl];
-      walk<0, JB>(acc, col, es, pl, nx, e.end - base - q0, CAP);
-      p = pl + q0;
+      const int e1 = e.end - base - q0;
+      uint32_t pl = e8 + 8 * (p - q0);
+      u32x2 nx = *(lds_u32x2*)pl;
+      walk<0, JB>(acc, col, pl, nx, e8 + 8 * (e1 < CAP ? e1 : CAP), e8 + 8 * CAP);
+      p = q0 + (int)(pl - e8) / 8;
     }
   }
 }

@@ -1,0 +1,486 @@
+// The likelihood by the trace's recurrence (FP64 and FP32 modes) on the
+// raster's spike lists (gfx950).
+//
+// The potentials obey the trace's own recurrence (Eq. (13)): with
+// V_i[t] = sum_j J_ij x_j[t] and d_t the decay over bin t (a on the regular
+// grid, e^{-delta_t} on the event grid),
+//   V_i[t+1] = d_t V_i[t] + sum_{spikes j of bin t} J_ij,
+// so a bin costs as many additions a row as it holds spikes (6.6 of 1000
+// neurons at 5 to 10 spikes per second and 1 ms) instead of the N products of
+// the dense contraction.  The integral of Eq. (12) has the same structure
+// backwards in time: G_ij = sum_t W_i[t] x_j[t] = sum_{spikes t of j} R_i[t] with
+//   R_i[t-1] = W_i[t] + d_t R_i[t]
+// (W_i = exp V_i, or the interval integral of Eq. (14)).  All sums are FP64,
+// in a fixed order.
+//
+//   k_rec_fwd     one wave per 64 rows i and time segment: the recurrence for
+//                 V from its value at the segment start, exp (or the interval
+//                 integrals), row sums, and W in [bin][row] order.
+//   k_rec_gather  one workgroup per 16 rows i and time split, windows of 1024
+//                 bins walked backwards: R in LDS, then every neuron j adds up
+//                 R at its spikes in a register.
+// Segments and splits start from the carries C (trace at every 64th bin):
+// V at a segment start is C J^T (k_carry_gemm; a 1/64 .. 1/1024 of the dense
+// work), and a split's W acts on all earlier spikes through
+// sum_t W_i[t] (decay since its start) times C_j at its start (k_rec_reduce).
+//
+// What bounds it (N = 1000, 1.2e6 bins, 7.7e6 spikes, one evaluation with the
+// gradient): k_rec_fwd 2.5 ms (FP32) and 4.9 ms (FP64: twice the bytes of J
+// from the L2), half of it vector and scalar issue (20 of the instructions a
+// bin are the exponential, 7 a spike); k_rec_gather 3.7 ms, LDS reads and the
+// phases that form a tile.  The dense kernels took 56 and 58 ms.
+#include <algorithm>
+
+#include "evfun.h"
+#include "fexp.h"
+#include "gather.h"
+
+namespace {
+
+using namespace glmr_gather;
+
+// Kernel G: rows i0 .. i0 + 15, windows of a split from the last to the
+// first.  A thread holds 16 bins of one row: their W are loaded while the
+// window before is gathered, a first backward pass gives the 16 bins' share
+// of R, the shares are combined across the workgroup (a suffix scan), and a
+// second pass with the carried-in value writes R to LDS.
+template <typename WT, bool EV, int JB>
+__global__ __launch_bounds__(GNT) void k_rec_gather(RecGArgs a) {
+  extern __shared__ __align__(16) double tile[];
+  double* wh = tile + TILE;       // [16 waves][GI] a wave's 64 bins: share of R before them
+  double* wp = wh + 16 * GI;      // and their decay
+  uint2* es = (uint2*)(tile + ENTRIES);
+  const uint2* __restrict__ ent = (const uint2*)a.ent2;
+  const int tid = threadIdx.x, il = tid & (GI - 1), tb = tid / GI, wave = tid >> 6, tl = tb & 3;
+  const int64_t nib = (a.N + GI - 1) / GI;
+  const int64_t i = (int64_t)(blockIdx.x % nib) * GI + il;
+  const int64_t jb0 = (int64_t)(blockIdx.x / nib) * (GG * JB);
+  const int64_t split = blockIdx.y;
+  const int64_t nw = (a.Lc + GW - 1) / GW;
+  const int64_t w0 = split * a.wps, w1 = w0 + a.wps < nw ? w0 + a.wps : nw;
+  const int64_t j0 = jb0 + (int64_t)tb * JB;
+  const bool rows = j0 < a.Np;
+  double acc[JB];
+#pragma unroll
+  for (int k = 0; k < JB; ++k) acc[k] = 0.0;
+  if (tid < GI) tile[GW * GI + tid] = 0.0;
+  const double ag = a.a;
+  // W of the window by raw buffer loads: the row offsets sit in scalar
+  // registers and bins past the recording read as zero
+  const int64_t valid = a.B - a.t0 < a.Lc ? a.B - a.t0 : a.Lc;
+  const int voff = (int)((tb * 16 * a.Np + i) * (int64_t)sizeof(WT)), pitch = (int)(a.Np * (int64_t)sizeof(WT));
+  WT wn[16];
+  auto fetch = [&](int64_t w) {
+    const int64_t n = valid - w * GW < GW ? valid - w * GW : GW;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((const WT*)a.W + w * GW * a.Np), (short)0, n > 0 ? (int)(n * pitch) : 0, 0x00020000);
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      if constexpr (sizeof(WT) == 8)
+        wn[m] = __builtin_bit_cast(WT, __builtin_amdgcn_raw_buffer_load_b64(r, voff, m * pitch, 0));
+      else
+        wn[m] = __builtin_bit_cast(WT, __builtin_amdgcn_raw_buffer_load_b32(r, voff, m * pitch, 0));
+    }
+  };
+  const int64_t jend = jb0 + GG * JB < a.Np ? jb0 + GG * JB : a.Np;
+  const int64_t wg = a.t0 / GW;  // the chunk's first window
+  Ends en{0, 0};
+  double cend = 0.0;  // R at the last bin of the window
+  if (w1 > w0) {
+    fetch(w1 - 1);
+    if (rows) en = load_ends<JB>(a.end2, (wg + w1 - 1) * a.Np + j0, il);
+  }
+  for (int64_t w = w1 - 1; w >= w0; --w) {
+    double h = 0.0, P = 1.0;
+    double dn[EV ? 16 : 1];
+    if (EV) {
+      const double* __restrict__ ed = a.ev.edec + a.t0 + w * GW + tb * 16;
+      const bool in = a.t0 + w * GW + tb * 16 < a.NS64;
+#pragma unroll
+      for (int m = 0; m < 16; ++m) dn[m] = in ? ed[m] : 1.0;
+    }
+    if (!EV) {
+      P = ag * ag;
+      P *= P;
+      P *= P;
+      P *= P;
+    }
+#pragma unroll
+    for (int m = 15; m >= 0; --m) {
+      h = (double)wn[m] + (EV ? dn[m] : ag) * h;
+      if (EV) P *= dn[m];
+    }
+    // inclusive suffix over the wave's four 16-bin blocks
+    double hs = h, Ps = P;
+    {
+      const double h1 = __shfl_down(hs, 16, 64), P1 = __shfl_down(Ps, 16, 64);
+      if (tl < 3) { hs += Ps * h1; Ps *= P1; }
+      const double h2 = __shfl_down(hs, 32, 64), P2 = __shfl_down(Ps, 32, 64);
+      if (tl < 2) { hs += Ps * h2; Ps *= P2; }
+    }
+    if (tl == 0) {
+      wh[wave * GI + il] = hs;
+      wp[wave * GI + il] = Ps;
+    }
+    const Ends ec = en;
+    const int base = a.end2[(wg + w) * a.Np + jb0 - 1], n = a.end2[(wg + w) * a.Np + jend - 1] - base;
+    __syncthreads();  // (also: the previous window's tile has been read)
+    stage_entries(es, ent, base, n);
+    double c = cend, cw = cend;
+#pragma unroll 4
+    for (int v = 15; v >= 0; --v) {
+      if (v == wave) cw = c;
+      c = wh[v * GI + il] + wp[v * GI + il] * c;
+    }
+    cend = c;
+    const double hx = __shfl_down(hs, 16, 64), Px = __shfl_down(Ps, 16, 64);
+    double r = tl < 3 ? hx + Px * cw : cw;
+    double* dst = tile + tb * 16 * GI + il;
+#pragma unroll
+    for (int m = 15; m >= 0; --m) {
+      dst[m * GI] = r;
+      r = (double)wn[m] + (EV ? dn[m] : ag) * r;
+    }
+    __syncthreads();
+    if (w > w0) {
+      fetch(w - 1);
+      if (rows) en = load_ends<JB>(a.end2, (wg + w - 1) * a.Np + j0, il);
+    }
+    gather_lists<JB>(acc, tile, ent, base, n, ec, il, rows);
+  }
+  if (blockIdx.x / nib == 0 && tb == 0) a.head[split * a.Np + i] = cend;
+  if (!rows) return;
+  double* out = (double*)a.Gp + split * a.Np * a.Np;
+#pragma unroll
+  for (int k = 0; k < JB; ++k) out[(j0 + k) * a.Np + i] = acc[k];
+}
+
+// G[i][j] (+)= sum over the splits of Gp[p][j][i] + head[p][i] C[start of p][j]
+__global__ __launch_bounds__(256) void k_rec_reduce(RecGArgs a, int first) {
+  __shared__ double t[32][33];
+  const int64_t i0 = (int64_t)blockIdx.x * 32, j0 = (int64_t)blockIdx.y * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  const int64_t i = i0 + tx;
+  for (int p = 0; p < a.n_splits; ++p) {
+    const double hd = i < a.N ? a.head[p * a.Np + i] : 0.0;
+    const double* C = a.C64 + ((a.t0 + p * a.wps * GW) >> 6) * a.Np;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t j = j0 + ty + 8 * q;
+      if (i < a.N) v[q] += ((const double*)a.Gp)[(p * a.Np + j) * a.Np + i] + hd * C[j];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) t[ty + 8 * q][tx] = v[q];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    double* g = a.G64 + (i0 + ty + 8 * q) * a.Np + j0 + tx;
+    *g = (first ? 0.0 : *g) + t[tx][ty + 8 * q];
+  }
+}
+
+// ------------------------------------------------------------------ forward
+constexpr uint32_t ENT_FIRST = 0x80000000u;
+__device__ __forceinline__ int ent_bin(uint32_t e, uint32_t base) { return (int)(((e >> 16) - base) & 0x7fffu); }
+
+template <typename T>
+__device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+  else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+}
+template <typename T>
+__device__ __forceinline__ void buf_store(T v, __amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  if constexpr (sizeof(T) == 8)
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, 0);
+  else
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, 0);
+}
+
+// One wave per 64 rows (lane = row) and segment of g.seg bins (PART: less than
+// a subtile).  A batch is 8 entries (uniform loads, a batch ahead); each
+// entry's row of J^T is loaded as the entry 8 before it is used.  Row offsets
+// are 32-bit scalars of one buffer: with 64-bit addresses and a bin comparison
+// per entry the scalar unit, which a CU's four SIMDs share, set the time (174
+// scalar instructions a bin and wave at N = 1000).
+constexpr int FB8 = 8;
+
+template <typename T, bool EV, bool TAU, bool STORE, bool FUSED, bool PART>
+__global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ ent, const int32_t* __restrict__ off,
+                                                 const T* __restrict__ Jt, const double* __restrict__ Dc,
+                                                 const double* __restrict__ Vc, const double* __restrict__ C64,
+                                                 const double* __restrict__ CY64, const double* __restrict__ edec,
+                                                 const double* __restrict__ delta, const double* __restrict__ eh,
+                                                 T* __restrict__ W, double* __restrict__ rowpart,
+                                                 double* __restrict__ rowpartV, RecFDims g) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t nib = (uint32_t)((g.N + 63) / 64);
+  const int i = (int)(blockIdx.x % nib) * 64 + lane;
+  const int64_t sg = (int64_t)(blockIdx.x / nib) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (sg >= g.n_seg) return;
+  const int64_t t0 = g.t0 + sg * g.seg;              // the segment's first bin
+  const int64_t s0 = t0 >> 6;
+  const int skip = PART ? (int)(t0 & 63) : 0;        // bins of its subtile before it
+  const int64_t left = g.B - s0 * 64;
+  const int tend = (int)(left < skip + g.seg ? left : skip + g.seg);  // bins counted from 64 s0
+  const int pitch = (int)(g.Np * (int64_t)sizeof(T)), voff = i * (int)sizeof(T);
+  const __amdgpu_buffer_rsrc_t jr =
+      __builtin_amdgcn_make_buffer_rsrc((void*)Jt, (short)0, (int)(g.Np * pitch), 0x00020000);
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(STORE ? W + (t0 - g.tw) * g.Np : nullptr), (short)0, STORE ? (int)(g.seg * pitch) : 0, 0x00020000);
+  const double ag = g.a;
+  double D = 0.0, V = 0.0;
+  if (FUSED) {
+    const double* __restrict__ C = C64 + s0 * g.Np;
+    const double* __restrict__ CY = CY64 + s0 * g.Np;
+#pragma unroll 8
+    for (int j = 0; j < (int)g.N; ++j) {
+      const double w = (double)buf_load<T>(jr, voff, j * pitch);
+      D += w * C[j];
+      if (TAU) V += w * CY[j];
+    }
+  } else {
+    D = Dc[(s0 / g.kc - g.row0) * g.Np + i];
+    if (TAU) V = Vc[(s0 / g.kc - g.row0) * g.Np + i];
+  }
+  double sum = 0.0, sumv = 0.0, acc = 0.0;
+  int t = 0, wo = 0;  // bin, and offset of its row in W
+  auto emit = [&]() {
+    if (PART && t < skip) return;
+    double lam;
+    if constexpr (EV) {
+      const double dl = delta[s0 * 64 + t];
+      double F;
+      if (!glmr_ev::interval_short(D, glmr_ev::slot_short(dl, eh[s0 * 64 + t]), &F, &lam))
+        glmr_ev::interval_call(D, dl, &F, &lam);
+      sum += F;
+    } else {
+      lam = exp_f64(D);
+      sum += lam;
+      if (TAU) sumv += lam * V;
+    }
+    if (STORE) {
+      buf_store<T>((T)lam, wr, voff, wo);
+      wo += pitch;
+    }
+  };
+  auto step = [&]() {
+    const double d = EV ? edec[s0 * 64 + t] : ag;
+    if (TAU) V = d * (V + g.ctau * D);
+    D = d * D + acc;
+    acc = 0.0;
+    ++t;
+    emit();
+  };
+  if (tend > skip) {
+    emit();
+    const int e0 = off[s0];
+    const int64_t s1 = (t0 + g.seg + 63) >> 6;
+    const int e1 = off[s1 < g.NS ? s1 : g.NS];
+    const uint32_t base = (uint32_t)(s0 * 64) & 0x7fffu;
+    auto row = [&](uint32_t q) { return buf_load<T>(jr, voff, (int)(q & 0xffffu) * pitch); };
+    if constexpr (EV) {
+      // about one entry a slot, and integrals that dwarf it: four rows ahead
+      // in a shift register, so that the integrals are expanded once
+      int e = e0;
+      uint32_t q0 = ent[e], q1 = ent[e + 1], q2 = ent[e + 2], q3 = ent[e + 3];
+      T r0 = row(q0), r1 = row(q1), r2 = row(q2), r3 = row(q3);
+      while (t < tend - 1) {
+        while (e < e1 && ent_bin(q0, base) <= t) {
+          acc += (double)r0;
+          q0 = q1; q1 = q2; q2 = q3;
+          r0 = r1; r1 = r2; r2 = r3;
+          q3 = ent[e + 4];
+          r3 = row(q3);
+          ++e;
+        }
+        step();
+      }
+    } else {
+      const uint32_t last = ENT_FIRST | ((((uint32_t)(tend - 1) + base) & 0x7fffu) << 16);
+      uint32_t ec[FB8], en[FB8];
+      T rn[FB8];
+      if (e0 < e1) {
+#pragma unroll
+        for (int q = 0; q < FB8; ++q) ec[q] = ent[e0 + q];
+#pragma unroll
+        for (int q = 0; q < FB8; ++q) rn[q] = row(ec[q]);
+#pragma unroll
+        for (int q = 0; q < FB8; ++q) en[q] = ent[e0 + FB8 + q];
+      }
+      for (int e = e0; e < e1; e += FB8) {
+        if (e + FB8 > e1) {
+          // past the segment's entries: a first entry of its last bin, whose
+          // row is added after the last step
+#pragma unroll
+          for (int q = 0; q < FB8; ++q) ec[q] = e + q < e1 ? ec[q] : last;
+        }
+#pragma unroll
+        for (int q = 0; q < FB8; ++q) {
+          if (ec[q] & ENT_FIRST) {
+            const int b = ent_bin(ec[q], base), to = b < tend - 1 ? b : tend - 1;
+            while (t < to) step();
+          }
+          acc += (double)rn[q];
+          rn[q] = row(en[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < FB8; ++q) ec[q] = en[q];
+#pragma unroll
+        for (int q = 0; q < FB8; ++q) en[q] = ent[e + 2 * FB8 + q];
+      }
+      while (t < tend - 1) step();
+    }
+  }
+  rowpart[(g.seg0 + sg) * g.Np + i] = sum;
+  if (TAU) rowpartV[(g.seg0 + sg) * g.Np + i] = sumv;
+}
+
+// Dc[r][i] = sum_j C[(row0 + r) kc][j] J[i][j]: 64 x 64 tiles on the FP64 MFMA,
+// 16 columns j a step through LDS.
+template <typename JT>
+__global__ __launch_bounds__(256) void k_carry_gemm(const double* __restrict__ C, const JT* __restrict__ Jt,
+                                                    double* __restrict__ out, int64_t rows, int64_t row0, int64_t kc,
+                                                    int64_t NS, int64_t Np) {
+  __shared__ double As[64][18], Bs[16][66];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t nt = Np / 64;
+  const int64_t i0 = (int64_t)(blockIdx.x % nt) * 64, r0 = (int64_t)(blockIdx.x / nt) * 64;
+  f64x4 acc[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
+  double an[4], bn[4];
+  auto fetch = [&](int64_t k0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = (tid >> 4) + 16 * q, c = tid & 15;
+      const int64_t s = (row0 + r0 + r) * kc;
+      an[q] = (r0 + r < rows && s < NS) ? C[s * Np + k0 + c] : 0.0;
+      bn[q] = (double)Jt[(k0 + (tid >> 6) + 4 * q) * Np + i0 + lane];
+    }
+  };
+  fetch(0);
+  for (int64_t k0 = 0; k0 < Np; k0 += 16) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      As[(tid >> 4) + 16 * q][tid & 15] = an[q];
+      Bs[(tid >> 6) + 4 * q][lane] = bn[q];
+    }
+    __syncthreads();
+    if (k0 + 16 < Np) fetch(k0 + 16);
+#pragma unroll
+    for (int k = 0; k < 16; k += 4) {
+      const double a = As[wave * 16 + (lane & 15)][k + (lane >> 4)];
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Bs[k + (lane >> 4)][b * 16 + (lane & 15)], acc[b], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = r0 + wave * 16 + (lane >> 4) + 4 * r;
+      if (row < rows) out[row * Np + i0 + b * 16 + (lane & 15)] = acc[b][r];
+    }
+}
+
+// J^T in the mode's type, the weights as used, e^mu
+template <typename JT>
+__global__ __launch_bounds__(256) void k_prepare_t(int N, int64_t Np, const double* J64, const double* mu, JT* Jt,
+                                                   double* Jr, double* rowscale) {
+  __shared__ JT t[32][33];
+  const int64_t i0 = (int64_t)blockIdx.x * 32, j0 = (int64_t)blockIdx.y * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t i = i0 + ty + 8 * q, j = j0 + tx;
+    const JT v = (JT)((i < N && j < N) ? J64[i * Np + j] : 0.0);
+    Jr[i * Np + j] = (double)v;
+    t[ty + 8 * q][tx] = v;
+    if (j == 0) rowscale[i] = (i < N) ? exp(mu[i]) : 0.0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) Jt[(j0 + ty + 8 * q) * Np + i0 + tx] = t[tx][ty + 8 * q];
+}
+
+template <typename WT, bool EV>
+hipError_t rec_gather(const RecGArgs& a, hipStream_t st) {
+  const int jb = gather_jb(a.Np);
+  const int64_t blocks = ((a.N + GI - 1) / GI) * ((a.Np + GG * jb - 1) / (GG * jb));
+  switch (jb) {
+    case 1: return run_gather(k_rec_gather<WT, EV, 1>, a, blocks, a.n_splits, st);
+    case 2: return run_gather(k_rec_gather<WT, EV, 2>, a, blocks, a.n_splits, st);
+    case 4: return run_gather(k_rec_gather<WT, EV, 4>, a, blocks, a.n_splits, st);
+    case 8: return run_gather(k_rec_gather<WT, EV, 8>, a, blocks, a.n_splits, st);
+    default: return run_gather(k_rec_gather<WT, EV, 16>, a, blocks, a.n_splits, st);
+  }
+}
+
+template <typename T, bool EV, bool TAU, bool STORE, bool FUSED, bool PART>
+hipError_t rec_fwd_run(const RecFArgs& a, hipStream_t st) {
+  const RecFDims& g = a.g;
+  const int64_t blocks = (g.N + 63) / 64 * ((g.n_seg + 3) / 4);
+  hipLaunchKernelGGL((k_rec_fwd<T, EV, TAU, STORE, FUSED, PART>), dim3((unsigned)blocks), dim3(256), 0, st, a.ent1,
+                     a.off1, (const T*)a.Jt, a.Dc, a.Vc, a.C64, a.CY64, a.edec, a.delta, a.eh, (T*)a.W, a.rowpart,
+                     a.rowpartV, g);
+  return hipGetLastError();
+}
+
+template <typename T, bool EV, bool TAU, bool STORE>
+hipError_t rec_fwd(const RecFArgs& a, hipStream_t st) {
+  const bool part = a.g.seg < 64;
+  if (a.fused)
+    return part ? rec_fwd_run<T, EV, TAU, STORE, true, true>(a, st) : rec_fwd_run<T, EV, TAU, STORE, true, false>(a, st);
+  return part ? rec_fwd_run<T, EV, TAU, STORE, false, true>(a, st) : rec_fwd_run<T, EV, TAU, STORE, false, false>(a, st);
+}
+
+template <typename T>
+hipError_t carry_gemm(const RecFArgs& a, const double* C, double* out, hipStream_t st) {
+  const int64_t blocks = (a.g.Np / 64) * ((a.rows + 63) / 64);
+  hipLaunchKernelGGL(k_carry_gemm<T>, dim3((unsigned)blocks), dim3(256), 0, st, C, (const T*)a.Jt, out, a.rows,
+                     a.g.row0, a.g.kc, a.g.NS, a.g.Np);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t rec_forward(const RecFArgs& a, hipStream_t st) {
+  const bool tau = a.rowpartV != nullptr, store = a.W != nullptr;
+  if (!a.fused) {
+    hipError_t e = carry_gemm<T>(a, a.C64, a.Dc, st);
+    if (e == hipSuccess && tau) e = carry_gemm<T>(a, a.CY64, a.Vc, st);
+    if (e != hipSuccess) return e;
+  }
+  if (a.edec) return store ? rec_fwd<T, true, false, true>(a, st) : rec_fwd<T, true, false, false>(a, st);
+  if (tau) return store ? rec_fwd<T, false, true, true>(a, st) : rec_fwd<T, false, true, false>(a, st);
+  return store ? rec_fwd<T, false, false, true>(a, st) : rec_fwd<T, false, false, false>(a, st);
+}
+
+}  // namespace
+
+hipError_t launch_rec_forward(int prec, const RecFArgs& a, hipStream_t st) {
+  return prec == PREC_F64 ? rec_forward<double>(a, st) : rec_forward<float>(a, st);
+}
+
+hipError_t launch_rec_gather(int prec, const RecGArgs& a, int first, hipStream_t st) {
+  hipError_t e;
+  if (prec == PREC_F64) e = a.ev.edec ? rec_gather<double, true>(a, st) : rec_gather<double, false>(a, st);
+  else e = a.ev.edec ? rec_gather<float, true>(a, st) : rec_gather<float, false>(a, st);
+  if (e != hipSuccess) return e;
+  const unsigned nb = (unsigned)(a.Np / 32);
+  hipLaunchKernelGGL(k_rec_reduce, dim3(nb, nb), dim3(256), 0, st, a, first);
+  return hipGetLastError();
+}
+
+hipError_t launch_prepare_t(int prec, int N, int64_t Np, const double* J64, const double* mu, void* Jt, double* Jr,
+                            double* rowscale, hipStream_t st) {
+  const unsigned nb = (unsigned)(Np / 32);
+  if (prec == PREC_F64)
+    hipLaunchKernelGGL(k_prepare_t<double>, dim3(nb, nb), dim3(256), 0, st, N, Np, J64, mu, (double*)Jt, Jr, rowscale);
+  else
+    hipLaunchKernelGGL(k_prepare_t<float>, dim3(nb, nb), dim3(256), 0, st, N, Np, J64, mu, (float*)Jt, Jr, rowscale);
+  return hipGetLastError();
+}

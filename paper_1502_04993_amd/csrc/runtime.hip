@@ -1,7 +1,9 @@
 // glmrec runtime: contexts, device memory, the evaluation pipeline, the
 // per-row ascent driver, batching and the C ABI of include/glmrec.h.
 //
-// One evaluation at fixed tau (the carries and dSigma are cached per tau):
+// One evaluation at fixed tau (the carries and dSigma are cached per tau), by
+// the dense contractions (BF16, FP8; FP64 and FP32 of dense rasters or with a
+// self-delay of its own; else FP64 and FP32 go by the recurrence, eval_rec):
 //   for each time chunk of L bins:
 //     kernel U   V = J x  -> W = exp(V) [Np x L], per-tile row sums of W
 //     kernel V   (dL/dtau only) Y-contraction, per-tile row sums of W V
@@ -79,19 +81,27 @@ struct glmr_ctx {
   bool all_spiking = false;
   uint64_t raster_digest = 0;  // digest of the recorded masks (and, on the event grid, the slot times)
 
-  // window-major spike lists of the recorded raster (spikes.hip)
+  // spike lists (spikes.hip, recur.hip): window-major of the raster that the
+  // contractions see and, when it is delayed, of the recorded one; time-major
+  // where the recurrence runs
   struct WinList {
     int32_t* end2 = nullptr;  // allocation; the lists' end2 starts 4 entries in
     uint16_t* ent2 = nullptr;
     bool ok = false;
   };
-  WinList wl;
+  WinList wl, wl0;
+  int32_t* off1 = nullptr;
+  uint32_t* ent1 = nullptr;
+  bool list1 = false;
+  int rec_mode = -1;         // GLMR_RECUR when the precision was set: 0 never, 1 always, else by density
+  bool jc_rec = false;       // Jc holds J transposed for the recurrence
+  double *rec_Dc = nullptr, *rec_Vc = nullptr, *rec_head = nullptr;
 
   // event grid (continuous time): slot start times and per-slot tables
   bool evm = false;
   double T0 = 0, T1 = 0, max_gap = 0;
   double* tslot = nullptr;  // [NS*64 + 1]
-  double* evtab = nullptr;  // [5 * NS*64 + NS]: pw, ainv, left, delta, edec, asub
+  double* evtab = nullptr;  // [6 * NS*64 + NS]: pw, ainv, left, delta, edec, eh, asub
   float* evgl = nullptr;    // BF16: [NS*64][16] per-slot table of kernel U's interval integrals
   double max_span = 0;      // largest 64-slot span / tau of the current tables
 
@@ -390,7 +400,8 @@ EvSlots ev_slots(const glmr_ctx* c) {
   e.left = c->evtab + 2 * n;
   e.delta = c->evtab + 3 * n;
   e.edec = c->evtab + 4 * n;
-  e.asub = c->evtab + 5 * n;
+  e.eh = c->evtab + 5 * n;
+  e.asub = c->evtab + 6 * n;
   return e;
 }
 
@@ -399,7 +410,7 @@ EvSlots ev_slots(const glmr_ctx* c) {
 constexpr double kMaxSpan = 600.0;
 glmr_status build_ev_tables(glmr_ctx* c, Arena* ar) {
   const int64_t n = c->NS * 64;
-  TRY(persist(c, ar, c->evtab, (size_t)(5 * n + c->NS)));
+  TRY(persist(c, ar, c->evtab, (size_t)(6 * n + c->NS)));
   unsigned long long* ms = nullptr;
   TRY(temp_alloc(c, ar, ms, 1));
   if (ar) HIPCHK(c, launch_fill_i32((int32_t*)ms, 2, 0, c->st));  // the static scratch keeps old contents
@@ -413,7 +424,8 @@ glmr_status build_ev_tables(glmr_ctx* c, Arena* ar) {
   ta.left = c->evtab + 2 * n;
   ta.delta = c->evtab + 3 * n;
   ta.edec = c->evtab + 4 * n;
-  ta.asub = c->evtab + 5 * n;
+  ta.eh = c->evtab + 5 * n;
+  ta.asub = c->evtab + 6 * n;
   if (c->prec == PREC_BF16) {
     TRY(persist(c, ar, c->evgl, (size_t)(16 * n)));
     ta.gl = c->evgl;
@@ -447,6 +459,33 @@ bool want_resident(glmr_ctx* c) {
   }
   const size_t have = c->Xtj ? 4 * (size_t)c->Bp * c->Np : 0;  // already held
   return 4 * (size_t)c->Bp * c->Np + (4ull << 30) <= fr + have;
+}
+
+// Whether the FP64 and FP32 modes evaluate by the recurrence on the spike
+// lists (recur.hip) instead of the dense contractions.  Its time grows with
+// the spikes of a bin, theirs hardly: at N = 1000, 1e5 bins (FP32 / FP64, ms)
+// 0.75 / 0.96 against 9.7 / 9.5 with 7 spikes a bin, 9.0 / 11 against
+// 18 / 17 with 100, 26 / 30 against 25 / 24 with 200; at N = 200, 4e5 bins
+// 4.9 / 6.4 against 9.3 / 9.0 even with 80; at N = 30 it is ahead for every
+// raster.  The event grid has at most one spike a slot.
+constexpr double kRecDensity = 0.12, kRecSpikes = 40.0;
+bool use_rec(const glmr_ctx* c) {
+  if ((c->prec != PREC_F64 && c->prec != PREC_F32) || !c->have_spikes || self_delayed(c) || c->rec_mode == 0 ||
+      c->Np > 8192)  // row offsets into J are 32-bit
+    return false;
+  return c->rec_mode == 1 || (double)c->nspk <= (kRecDensity * (double)c->N + kRecSpikes) * (double)c->B;
+}
+
+// Bins of a segment of the recurrence: the longest that leaves 16 waves a
+// SIMD, else 64, and parts of 64 where even those leave the chip idle.
+int64_t rec_seg(const glmr_ctx* c) {
+  const int64_t nib = (c->N + 63) / 64;
+  auto waves = [&](int64_t seg) { return nib * ((c->B + seg - 1) / seg); };
+  for (int64_t seg = 1024; seg > 64; seg /= 2)
+    if (waves(seg) >= 16384) return seg;
+  for (int64_t seg = 64; seg > 16; seg /= 2)
+    if (waves(seg) >= 4096) return seg;
+  return 16;
 }
 
 // Build (or drop) the resident trace for the current tau; needs C64 and tab.
@@ -506,49 +545,76 @@ glmr_status build_resident_trace(glmr_ctx* c, Arena* ar) {
   return GLMR_OK;
 }
 
+void drop_lists(glmr_ctx* c) { c->wl.ok = c->wl0.ok = c->list1 = false; }
 
-// The spike lists of the recorded raster; they depend on the spikes only.
-glmr_status ensure_lists(glmr_ctx* c, Arena* ar) {
-  if (c->wl.ok) return GLMR_OK;
-  if (ar)
-    return fail(c, GLMR_ESTATE, "the spike lists do not exist yet: call glmr_set_kernel once on this "
-                                "context before glmr_set_kernel_noalloc");
+// Lists of the raster `masks`: window-major into wl, time-major too if bins.
+glmr_status build_lists(glmr_ctx* c, const uint64_t* masks, glmr_ctx::WinList* wl, bool bins) {
   const int64_t nw = (c->NS * 64 + GLMR_GW - 1) / GLMR_GW;
   ListArgs a{};
-  a.masks = delayed(c) ? c->masks0 : c->masks;
+  a.masks = masks;
   a.planes = c->planes;
   a.NS = c->NS;
   a.Np = c->Np;
   int64_t* tmp = nullptr;
+  auto cleanup = [&]() {
+    dfree(c, a.wcnt);
+    dfree(c, a.woff);
+    dfree(c, a.scnt);
+    dfree(c, tmp);
+  };
   glmr_status st = GLMR_OK;
   do {
     if ((st = dalloc(c, a.wcnt, (size_t)nw)) != GLMR_OK) break;
     if ((st = dalloc(c, a.woff, (size_t)nw + 1)) != GLMR_OK) break;
-    if ((st = dalloc(c, tmp, (size_t)ingest_scan_tmp_len(nw))) != GLMR_OK) break;
-    int32_t total = 0;
+    if ((st = dalloc(c, tmp, (size_t)ingest_scan_tmp_len(std::max(nw, c->NS)))) != GLMR_OK) break;
+    if (bins) {
+      if ((st = dalloc(c, a.scnt, (size_t)c->NS)) != GLMR_OK) break;
+      if (!c->off1 && (st = dalloc(c, c->off1, (size_t)c->NS + 1)) != GLMR_OK) break;
+      if ((st = dalloc(c, c->ent1, (size_t)c->nspk + 24)) != GLMR_OK) break;
+      a.off1 = c->off1;
+      a.ent1 = c->ent1;
+    }
+    int32_t total = 0, spikes = 0;
     if (launch_list_count(a, c->st) != hipSuccess || launch_scan_i32(a.wcnt, nw, tmp, a.woff, c->st) != hipSuccess ||
+        (bins && launch_scan_i32(a.scnt, c->NS, tmp, a.off1, c->st) != hipSuccess) ||
         hipMemcpyAsync(&total, a.woff + nw, sizeof total, hipMemcpyDeviceToHost, c->st) != hipSuccess ||
+        (bins && hipMemcpyAsync(&spikes, a.off1 + c->NS, sizeof spikes, hipMemcpyDeviceToHost, c->st) != hipSuccess) ||
         hipStreamSynchronize(c->st) != hipSuccess) {
       st = fail(c, GLMR_EDEVICE, "spike lists: %s", hipGetErrorString(hipGetLastError()));
       break;
     }
-    if (!c->wl.end2 && (st = dalloc(c, c->wl.end2, (size_t)(nw * c->Np + 4))) != GLMR_OK) break;
-    if ((st = dalloc(c, c->wl.ent2, 4 * ((size_t)total + 1))) != GLMR_OK) break;
-    a.end2 = c->wl.end2 + 4;
-    a.ent2 = c->wl.ent2;
-    // the entry loads run one group ahead of the lists' end
+    if (!wl->end2 && (st = dalloc(c, wl->end2, (size_t)(nw * c->Np + 4))) != GLMR_OK) break;
+    if ((st = dalloc(c, wl->ent2, 4 * ((size_t)total + 1))) != GLMR_OK) break;
+    a.end2 = wl->end2 + 4;
+    a.ent2 = wl->ent2;
+    // the entry loads run ahead of the lists' ends: what they find there is a valid entry
     if (launch_list_windows(a, c->st) != hipSuccess ||
         launch_fill_i32((int32_t*)(a.ent2 + 4 * (size_t)total), 2, 0, c->st) != hipSuccess ||
+        (bins && (launch_list_bins(a, c->st) != hipSuccess ||
+                  launch_fill_i32((int32_t*)a.ent1 + spikes, 24, 0, c->st) != hipSuccess)) ||
         hipStreamSynchronize(c->st) != hipSuccess) {
       st = fail(c, GLMR_EDEVICE, "spike lists: %s", hipGetErrorString(hipGetLastError()));
       break;
     }
-    c->wl.ok = true;
+    wl->ok = true;
+    if (bins) c->list1 = true;
   } while (false);
-  dfree(c, a.wcnt);
-  dfree(c, a.woff);
-  dfree(c, tmp);
+  cleanup();
   return st;
+}
+
+// The lists that the spike term and the recurrence of the current precision
+// need; they depend on the raster and the delays only.
+glmr_status ensure_lists(glmr_ctx* c, Arena* ar) {
+  const bool bins = c->prec == PREC_F64 || c->prec == PREC_F32;
+  const bool need = (bins && !c->list1) || !c->wl.ok || (delayed(c) && !c->wl0.ok);
+  if (!need) return GLMR_OK;
+  if (ar)
+    return fail(c, GLMR_ESTATE, "the spike lists do not exist yet: call glmr_set_kernel once on this "
+                                "context before glmr_set_kernel_noalloc");
+  if (!c->wl.ok || (bins && !c->list1)) TRY(build_lists(c, c->masks, &c->wl, bins));
+  if (delayed(c) && !c->wl0.ok) TRY(build_lists(c, c->masks0, &c->wl0, false));
+  return GLMR_OK;
 }
 
 // The per-tau caches: carries, resident trace, spike term.  ar != nullptr:
@@ -637,8 +703,9 @@ glmr_status build_kernel_caches(glmr_ctx* c, bool want_y, Arena* ar = nullptr) {
   SpikeTermArgs sa{};
   sa.masks = c->masks;
   sa.planes = c->planes;
-  sa.end2 = c->wl.end2 + 4;  // the rows' spikes stay at their recorded bins
-  sa.ent2 = c->wl.ent2;
+  const glmr_ctx::WinList& rec = delayed(c) ? c->wl0 : c->wl;  // the rows' spikes stay at their recorded bins
+  sa.end2 = rec.end2 + 4;
+  sa.ent2 = rec.ent2;
   sa.C64 = c->C64;
   sa.CY64 = want_y ? c->CY64 : nullptr;
   sa.tab = c->tab;
@@ -685,7 +752,14 @@ glmr_status ensure_workspace(glmr_ctx* c, bool want_grad, bool want_tau) {
     TRY(dalloc(c, (unsigned char*&)p, (size_t)Np * c->L * wb));
     c->W = p;
   }
-  const int64_t ntiles_t = c->Bp / c->bt1;
+  const int64_t seg = rec_seg(c), nseg = (c->B + seg - 1) / seg;
+  const int64_t ntiles_t = std::max(c->Bp / c->bt1, c->prec == PREC_F64 || c->prec == PREC_F32 ? nseg : 0);
+  if (use_rec(c)) {
+    const size_t rows = (size_t)(c->NS / std::max<int64_t>(1, seg / 64) + 1);
+    if (!c->rec_Dc) TRY(dalloc(c, c->rec_Dc, rows * Np));
+    if (want_tau && !c->rec_Vc) TRY(dalloc(c, c->rec_Vc, rows * Np));
+    if (want_grad && !c->rec_head) TRY(dalloc(c, c->rec_head, (size_t)c->max_splits * Np));
+  }
   if (!c->rowpart) TRY(dalloc(c, c->rowpart, (size_t)ntiles_t * Np));
   if (want_tau && !c->rowpartV) TRY(dalloc(c, c->rowpartV, (size_t)ntiles_t * Np));
   if (!c->rowsum) TRY(dalloc(c, c->rowsum, (size_t)Np));
@@ -824,11 +898,86 @@ hipError_t launch_g_chunk(glmr_ctx* c, int k, int64_t t0, int64_t Lc, int* n_spl
   return launch_res_g(k, c->prec == PREC_FP8 ? 1 : 0, ga, c->st);
 }
 
-glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau);
+glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau, int64_t row_tiles);
+glmr_status prepare_params(glmr_ctx* c);
+
+// One evaluation by the recurrence: the whole recording at once for the
+// likelihood alone, in chunks of W's length with the gradient.
+glmr_status eval_rec(glmr_ctx* c, bool want_grad, bool want_tau) {
+  const int64_t seg = rec_seg(c), kc = std::max<int64_t>(1, seg / 64);
+  const int64_t nseg = (c->B + seg - 1) / seg;
+  const EvSlots ev = ev_slots(c);
+  const int64_t L = want_grad ? c->L : c->Bp;
+  for (int64_t t0 = 0, ci = 0; t0 < c->B; t0 += L, ++ci) {
+    const int64_t Lc = std::min<int64_t>(L, c->Bp - t0);
+    RecFArgs f{};
+    f.g.N = c->N;
+    f.g.Np = c->Np;
+    f.g.NS = c->NS;
+    f.g.B = c->B;
+    f.g.t0 = t0;
+    f.g.seg = seg;
+    f.g.seg0 = t0 / seg;
+    f.g.n_seg = std::min<int64_t>(nseg - f.g.seg0, (Lc + seg - 1) / seg);
+    f.g.tw = t0;
+    f.g.kc = kc;
+    f.g.row0 = t0 / 64 / kc;
+    f.g.a = c->a;
+    f.g.ctau = c->dt / (c->tau * c->tau);
+    f.ent1 = c->ent1;
+    f.off1 = c->off1;
+    f.Jt = c->Jc;
+    f.Dc = c->rec_Dc;
+    f.Vc = c->rec_Vc;
+    f.rows = (Lc / 64 + kc - 1) / kc;
+    f.fused = c->N <= 128 ? 1 : 0;
+    f.C64 = c->C64;
+    f.CY64 = c->CY64;
+    f.edec = ev.edec;
+    f.delta = ev.delta;
+    f.eh = ev.eh;
+    f.W = want_grad ? c->W : nullptr;
+    f.rowpart = c->rowpart;
+    f.rowpartV = want_tau ? c->rowpartV : nullptr;
+    {
+      ProfScope ps(c, K_U);
+      HIPCHK(c, launch_rec_forward(c->prec, f, c->st));
+    }
+    if (!want_grad) continue;
+    RecGArgs g{};
+    g.W = c->W;
+    g.N = c->N;
+    g.Np = c->Np;
+    g.B = c->B;
+    g.t0 = t0;
+    g.Lc = Lc;
+    g.a = c->a;
+    g.ev = ev;
+    g.end2 = c->wl.end2 + 4;
+    g.ent2 = c->wl.ent2;
+    // four rounds of workgroups over the 256 CUs (one a CU)
+    const int64_t nw = (Lc + GLMR_GW - 1) / GLMR_GW, blocks = gather_blocks(c->N, c->Np);
+    const int64_t want = std::min<int64_t>({nw, c->max_splits, std::max<int64_t>(1, (1024 + blocks - 1) / blocks)});
+    g.wps = (nw + want - 1) / want;
+    g.n_splits = (int)((nw + g.wps - 1) / g.wps);
+    g.Gp = c->Gp;
+    g.head = c->rec_head;
+    g.C64 = c->C64;
+    g.G64 = c->G64;
+    g.NS64 = c->NS * 64;
+    ProfScope ps(c, K_G);
+    HIPCHK(c, launch_rec_gather(c->prec, g, ci == 0, c->st));
+  }
+  return eval_finish(c, want_grad, want_tau, nseg);
+}
 
 glmr_status eval_core(glmr_ctx* c, bool want_grad, bool want_tau) {
   TRY(ensure_workspace(c, want_grad, want_tau));
   const int64_t Np = c->Np;
+  if (c->prec == PREC_F64 || c->prec == PREC_F32) {
+    if (use_rec(c) != c->jc_rec) TRY(prepare_params(c));  // the weights were staged for the other path
+    if (c->jc_rec) return eval_rec(c, want_grad, want_tau);
+  }
   for (int64_t t0 = 0, ci = 0; t0 < c->Bp; t0 += c->L, ++ci) {
     const int64_t Lc = std::min<int64_t>(c->L, c->Bp - t0);
     Gemm1Args g1{};
@@ -916,14 +1065,14 @@ glmr_status eval_core(glmr_ctx* c, bool want_grad, bool want_tau) {
       HIPCHK(c, launch_gp_reduce(c->prec, c->Gp, g2.n_splits, Np, c->G64, ci == 0, c->st));
     }
   }
-  return eval_finish(c, want_grad, want_tau);
+  return eval_finish(c, want_grad, want_tau, c->Bp / c->bt1);
 }
 
-// Row sums of the weights over all bins, then L_i, dL/dmu, dL/dJ (dL/dtau) in FP64.
-glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau) {
+// Row sums of the weights over all bins (ntiles_t partials a row), then L_i,
+// dL/dmu, dL/dJ (dL/dtau) in FP64.
+glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau, int64_t ntiles_t) {
   const int64_t Np = c->Np;
   ProfScope ps(c, K_ASM);
-  const int64_t ntiles_t = c->Bp / c->bt1;
   HIPCHK(c, launch_rowpart_reduce(c->rowpart, ntiles_t, Np, c->rowsum, c->rp_tmp, c->st));
   if (want_tau)
     HIPCHK(c, launch_rowpart_reduce(c->rowpartV, ntiles_t, Np, c->rowsumV, c->rp_tmp, c->st));
@@ -956,6 +1105,11 @@ glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau) {
 glmr_status prepare_params(glmr_ctx* c) {
   ProfScope ps(c, K_PREP);
   if (c->prec == PREC_FP8 && !c->jscale) TRY(dalloc(c, c->jscale, (size_t)c->Np));
+  c->jc_rec = use_rec(c);
+  if (c->jc_rec) {
+    HIPCHK(c, launch_prepare_t(c->prec, c->N, c->Np, c->J64, c->mu, c->Jc, c->Jr, c->rowscale, c->st));
+    return GLMR_OK;
+  }
   HIPCHK(c, launch_prepare_params(c->prec, c->j2 ? 1 : 0, c->N, c->Np, c->J64, c->mu, c->Jc, c->Jr, c->rowscale,
                                   c->prec == PREC_FP8 ? c->jscale : nullptr, c->st));
   return GLMR_OK;
@@ -972,6 +1126,9 @@ void setup_precision(glmr_ctx* c) {
   // resident-trace shapes: in BF16 the fragment-major kernels (unless
   // GLMR_XFRAG=0), else the row-major ones with 256-neuron tiles when the
   // padding allows
+  // FP64 and FP32: GLMR_RECUR=0 / 1 keeps to the dense contractions / the recurrence
+  const char* rc = std::getenv("GLMR_RECUR");
+  c->rec_mode = rc && rc[0] == '0' ? 0 : rc && rc[0] == '1' ? 1 : -1;
   const char* xf = std::getenv("GLMR_XFRAG");
   c->xfrag = (c->prec == PREC_BF16 && !(xf && std::strcmp(xf, "0") == 0)) ? 1 : 0;
   if (c->xfrag) {
@@ -1493,7 +1650,7 @@ glmr_status batch_eval_core(glmr_batch* b) {
         HIPCHK(c, launch_gp_reduce(c->prec, c->Gp, gr.nsplits[q], c->Np, c->G64, ci == 0, b->st));
       }
   }
-  for (glmr_ctx* c : b->ctxs) TRY(eval_finish(c, true, false));
+  for (glmr_ctx* c : b->ctxs) TRY(eval_finish(c, true, false, c->Bp / c->bt1));
   return GLMR_OK;
 }
 
@@ -2021,7 +2178,8 @@ glmr_status glmr_create(const glmr_config* cfg, glmr_ctx** out) {
   c->j2 = cfg->precision == GLMR_BF16_J2;
   c->prec = c->j2 ? GLMR_BF16 : cfg->precision;
   int tile = cfg->tile_n;
-  if (tile == 0) tile = ((c->prec == GLMR_BF16 || c->prec == GLMR_FP8) && c->N <= 384) ? 128 : 256;
+  // FP64 and FP32 kernels take multiples of 128
+  if (tile == 0) tile = (c->prec == GLMR_FP64 || c->prec == GLMR_FP32 || c->N <= 384) ? 128 : 256;
   c->Np = rup(c->N, tile);
   c->Bp = rup(c->B, GLMR_TT);
   c->NS = c->Bp / GLMR_SUB;
@@ -2136,7 +2294,7 @@ glmr_status ingest_pairs(glmr_ctx* c, const int64_t* bin, const int32_t* neuron,
   dfree(c, scan_tmp);
   c->nspk = n;
   c->have_spikes = true;
-  c->wl.ok = false;
+  drop_lists(c);
   TRY(apply_delays(c));
   c->all_spiking = true;
   for (int i = 0; i < c->N; ++i)
@@ -2346,6 +2504,7 @@ glmr_status glmr_set_delays(glmr_ctx* c, int64_t d, int64_t d_self) {
   c->dly_s = d_self;
   if (!c->have_spikes) return GLMR_OK;  // applied when the spikes arrive
   c->have_kernel = false;
+  drop_lists(c);
   TRY(apply_delays(c));
   if (c->tau > 0) TRY(build_kernel_caches(c, c->keep_y));
   return GLMR_OK;
@@ -2425,6 +2584,7 @@ glmr_status glmr_set_precision(glmr_ctx* c, int32_t precision) {
   dfree(c, c->rowpart);
   dfree(c, c->rowpartV);
   dfree(c, c->gpart);
+  dfree(c, c->rec_head);
   if (c->Jc) {
     unsigned char* jc = (unsigned char*)c->Jc;
     dfree(c, jc);

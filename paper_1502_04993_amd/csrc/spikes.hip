@@ -4,7 +4,10 @@
 //   window-major  ent2[]: for every window of 1024 bins and neuron j its bins
 //                 in order as offsets 16 (t mod 1024) into the window's tile
 //                 (gather.h), padded to groups of four with the offset of a
-//                 zero row; end2[w Np + j] the end of j's groups (end2[-1] = 0).
+//                 zero row; end2[w Np + j] the end of j's groups (end2[-1] = 0);
+//   time-major    ent1[]: j | (bin mod 2^15) << 16 in (bin, neuron) order, bit
+//                 31 set in a bin's first entry; off1[s] the first entry of
+//                 subtile s (64 bins); for the recurrence (recur.hip).
 //
 // Spike term: dSigma[i][j] = sum_t s_i[t] x_j[t] (Eq. (12)), and dSigmaY with
 // y = dx/dtau, in FP64, once per tau.  A workgroup holds 16 columns j of the
@@ -25,27 +28,37 @@ namespace {
 using namespace glmr_gather;
 
 // ------------------------------------------------------------------ lists
-// per window: groups of four of all its neurons
+// per window: groups of four of all its neurons; per subtile: spikes
 __global__ __launch_bounds__(256) void k_list_count(ListArgs a) {
-  __shared__ int quads;
+  __shared__ int sub[GW / 64], quads;
   const int64_t w = blockIdx.x;
   const int tid = threadIdx.x;
+  if (tid < GW / 64) sub[tid] = 0;
   if (tid == 0) quads = 0;
   __syncthreads();
-  int q = 0;
+  int mine[GW / 64], q = 0;
+#pragma unroll
+  for (int k = 0; k < GW / 64; ++k) mine[k] = 0;
   for (int64_t j = tid; j < a.Np; j += 256) {
     int c = 0;
 #pragma unroll
     for (int k = 0; k < GW / 64; ++k) {
       const int64_t s = w * (GW / 64) + k;
       if (s >= a.NS) continue;
-      for (int p = 0; p < a.planes; ++p) c += __builtin_popcountll(a.masks[((int64_t)p * a.NS + s) * a.Np + j]);
+      int n = 0;
+      for (int p = 0; p < a.planes; ++p) n += __builtin_popcountll(a.masks[((int64_t)p * a.NS + s) * a.Np + j]);
+      mine[k] += n;
+      c += n;
     }
     q += (c + 3) >> 2;
   }
   if (q) atomicAdd(&quads, q);
+#pragma unroll
+  for (int k = 0; k < GW / 64; ++k)
+    if (mine[k]) atomicAdd(&sub[k], mine[k]);
   __syncthreads();
   if (tid == 0) a.wcnt[w] = quads;
+  if (a.scnt && tid < GW / 64 && w * (GW / 64) + tid < a.NS) a.scnt[w * (GW / 64) + tid] = sub[tid];
 }
 
 // window-major lists: the neurons of a window in order, 256 at a time
@@ -105,6 +118,54 @@ __global__ __launch_bounds__(256) void k_list_windows(ListArgs a) {
   }
 }
 
+// time-major lists: one wave per subtile, lane = bin; the columns with spikes
+// are walked in order, each lane counting (then writing) those of its bin
+__global__ __launch_bounds__(256) void k_list_bins(ListArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int64_t s = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (s >= a.NS) return;
+  auto word = [&](uint64_t v, int l) {
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, l);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), l);
+    return ((uint64_t)hi << 32) | lo;
+  };
+  int pos = 0, first = 0;
+  for (int pass = 0; pass < 2; ++pass) {
+    for (int64_t j0 = 0; j0 < a.Np; j0 += 64) {
+      for (int p = 0; p < a.planes; ++p) {
+        if (p && pass) break;
+        const uint64_t m = a.masks[((int64_t)p * a.NS + s) * a.Np + j0 + lane];
+        uint64_t nz = __ballot(m != 0);
+        while (nz) {
+          const int l = __builtin_ctzll(nz);
+          nz &= nz - 1;
+          const bool hit = (word(m, l) >> lane) & 1ull;
+          if (!hit) continue;
+          if (pass == 0) {
+            ++pos;
+          } else {
+            // the bin's first entry carries the flag
+            const uint32_t e = (uint32_t)(j0 + l) | (((uint32_t)(s * 64 + lane) & 0x7fffu) << 16);
+            a.ent1[pos] = pos == first ? e | 0x80000000u : e;
+            ++pos;
+            for (int q = 1; q < a.planes; ++q)
+              if ((a.masks[((int64_t)q * a.NS + s) * a.Np + j0 + l] >> lane) & 1ull) a.ent1[pos++] = e;
+          }
+        }
+      }
+    }
+    if (pass == 0) {
+      int incl = pos;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+      }
+      pos = first = a.off1[s] + incl - pos;
+    }
+  }
+}
+
 // Spike term: columns j0 .. j0 + 15 of x (Y: of dx/dtau) over a window in LDS,
 // every row i adds up the columns at its spikes.  On the event grid the trace
 // at a spike is its left limit, x decayed over the whole slot.
@@ -124,7 +185,7 @@ __global__ __launch_bounds__(GNT) void k_spk_gather(SpikeTermArgs a) {
 #pragma unroll
   for (int k = 0; k < JB; ++k) acc[k] = 0.0;
   if (tid < GI) tile[GW * GI + tid] = 0.0;
-  uint2* es = (uint2*)(tile + TILE);
+  uint2* es = (uint2*)(tile + ENTRIES);
   const uint2* __restrict__ ent = (const uint2*)a.ent2;
   const int64_t iend = ib0 + GG * JB < a.Np ? ib0 + GG * JB : a.Np;
   const int m0 = 16 * (tb & 3);
@@ -185,7 +246,7 @@ __global__ __launch_bounds__(GNT) void k_spk_gather(SpikeTermArgs a) {
     }
     __syncthreads();
     if (w + 1 < w1) fetch(w + 1);
-    gather_lists<JB>(acc, tile, es, ent, base, n, ec, il, rows);
+    gather_lists<JB>(acc, tile, ent, base, n, ec, il, rows);
   }
   if (!rows) return;
   double* out = a.part + split * a.Np * a.Np;
@@ -224,6 +285,11 @@ hipError_t launch_list_count(const ListArgs& a, hipStream_t st) {
 
 hipError_t launch_list_windows(const ListArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(k_list_windows, dim3((unsigned)((a.NS * 64 + GW - 1) / GW)), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_list_bins(const ListArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(k_list_bins, dim3((unsigned)((a.NS + 3) / 4)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
