@@ -70,7 +70,6 @@ struct EvSlots {
   const double* left;      // [NS*64] e^{-(t_{k+1} - t_k0)/tau}
   const double* delta;     // [NS*64] (t_{k+1} - t_k)/tau
   const double* edec;      // [NS*64] e^{-(t_{k+1} - t_k)/tau}  (decay over slot k)
-  const double* eh;        // [NS*64] e^{-(t_{k+1} - t_k)/(2 tau)}
   const double* asub;      // [NS]    e^{-(t_{k0+64} - t_k0)/tau}
 };
 
@@ -128,7 +127,7 @@ struct EvTableArgs {
   const double* tslot;
   double tau;
   int64_t NS;
-  double *pw, *ainv, *left, *delta, *edec, *eh, *asub;
+  double *pw, *ainv, *left, *delta, *edec, *asub;
   float* gl;                    // [NS*64][16]: the FP32 evaluation's per-slot table (null: none)
   unsigned long long* maxspan;  // max over subtiles of the span / tau (double bits), zero on entry
 };
@@ -161,7 +160,7 @@ struct ListArgs {
   int32_t* woff;           // [windows + 1] their exclusive scan
   int32_t* scnt;           // [NS] spikes of a subtile (null: not counted)
   int32_t* off1;           // [NS + 1] their exclusive scan
-  uint32_t* ent1;          // [spikes + 24] time-major entries (the last 24 zero)
+  uint32_t* ent1;          // [spikes + 192] time-major entries (the last 192 zero)
   int32_t* end2;           // [windows][Np] end of a neuron's groups (end2[-1] = 0)
   uint16_t* ent2;          // [groups + 1][4] window-major entries
 };
@@ -288,7 +287,7 @@ struct RecFArgs {
   int64_t rows;
   int fused;               // the segments form theirs themselves (few neurons)
   const double *C64, *CY64;
-  const double *edec, *delta, *eh;  // event grid (null on the regular grid)
+  const double *edec, *delta;  // event grid (null on the regular grid)
   void* W;                 // [L][Np] double or float, null: not kept
   double* rowpart;         // [segments][Np]
   double* rowpartV;        // dL/dtau (null: not computed)

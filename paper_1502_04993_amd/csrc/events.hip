@@ -168,7 +168,6 @@ __global__ void k_ev_tables(EvTableArgs a) {
     a.left[k] = exp(-(tk1 - tb) * r);
     a.delta[k] = (tk1 - tk) * r;
     a.edec[k] = exp(-(tk1 - tk) * r);
-    a.eh[k] = exp(-0.5 * ((tk1 - tk) * r));
     if (a.gl) {
       float o[16];
       glmr_ev::table_f((tk1 - tk) * r, o);

@@ -28,7 +28,11 @@
 // gradient): k_rec_fwd 2.5 ms (FP32) and 4.9 ms (FP64: twice the bytes of J
 // from the L2), half of it vector and scalar issue (20 of the instructions a
 // bin are the exponential, 7 a spike); k_rec_gather 3.7 ms, LDS reads and the
-// phases that form a tile.  The dense kernels took 56 and 58 ms.
+// phases that form a tile.  The dense kernels took 56 and 58 ms.  On the event
+// grid (FP64): k_rec_fwd_ev 0.145 ms at N = 150, 6.6e4 slots and 2.1 ms at
+// N = 1000, 4.4e5 slots, the FP64 arithmetic of the integrals and, with four
+// waves a SIMD, its latency (written out per lane, with the closed forms as a
+// call: 0.47 and 5.2 ms).
 #include <algorithm>
 
 #include "evfun.h"
@@ -155,30 +159,27 @@ __global__ __launch_bounds__(GNT) void k_rec_gather(RecGArgs a) {
   for (int k = 0; k < JB; ++k) out[(j0 + k) * a.Np + i] = acc[k];
 }
 
-// G[i][j] (+)= sum over the splits of Gp[p][j][i] + head[p][i] C[start of p][j]
+// G[i][j] (+)= sum over the splits of Gp[p][j][i] + head[p][i] C[start of p][j]:
+// 32 rows x 8 columns a workgroup, eight splits' loads in flight (with 32 x 32
+// a workgroup and a split at a time the few workgroups of a small network
+// waited on memory: 87 us at 256 rows and 65 splits)
 __global__ __launch_bounds__(256) void k_rec_reduce(RecGArgs a, int first) {
-  __shared__ double t[32][33];
-  const int64_t i0 = (int64_t)blockIdx.x * 32, j0 = (int64_t)blockIdx.y * 32;
+  __shared__ double t[8][33];
+  const int64_t i0 = (int64_t)blockIdx.x * 32, j0 = (int64_t)blockIdx.y * 8;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  double v[4] = {0.0, 0.0, 0.0, 0.0};
-  const int64_t i = i0 + tx;
-  for (int p = 0; p < a.n_splits; ++p) {
-    const double hd = i < a.N ? a.head[p * a.Np + i] : 0.0;
-    const double* C = a.C64 + ((a.t0 + p * a.wps * GW) >> 6) * a.Np;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int64_t j = j0 + ty + 8 * q;
-      if (i < a.N) v[q] += ((const double*)a.Gp)[(p * a.Np + j) * a.Np + i] + hd * C[j];
-    }
+  const int64_t i = i0 + tx, j = j0 + ty, cstep = a.wps * (GW / 64) * a.Np, gstep = a.Np * a.Np;
+  const double* __restrict__ gp = (const double*)a.Gp + j * a.Np + i;
+  const double* __restrict__ C = a.C64 + (a.t0 >> 6) * a.Np + j;
+  const double* __restrict__ hd = a.head + i;
+  double v = 0.0;
+  if (i < a.N) {
+#pragma unroll 8
+    for (int p = 0; p < a.n_splits; ++p) v += gp[p * gstep] + hd[p * a.Np] * C[p * cstep];
   }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) t[ty + 8 * q][tx] = v[q];
+  t[ty][tx] = v;
   __syncthreads();
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    double* g = a.G64 + (i0 + ty + 8 * q) * a.Np + j0 + tx;
-    *g = (first ? 0.0 : *g) + t[tx][ty + 8 * q];
-  }
+  double* g = a.G64 + (i0 + (threadIdx.x >> 3)) * a.Np + j0 + (threadIdx.x & 7);
+  *g = (first ? 0.0 : *g) + t[threadIdx.x & 7][threadIdx.x >> 3];
 }
 
 // ------------------------------------------------------------------ forward
@@ -206,14 +207,13 @@ __device__ __forceinline__ void buf_store(T v, __amdgpu_buffer_rsrc_t r, int vof
 // scalar instructions a bin and wave at N = 1000).
 constexpr int FB8 = 8;
 
-template <typename T, bool EV, bool TAU, bool STORE, bool FUSED, bool PART>
+template <typename T, bool TAU, bool STORE, bool FUSED, bool PART>
 __global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ ent, const int32_t* __restrict__ off,
                                                  const T* __restrict__ Jt, const double* __restrict__ Dc,
                                                  const double* __restrict__ Vc, const double* __restrict__ C64,
-                                                 const double* __restrict__ CY64, const double* __restrict__ edec,
-                                                 const double* __restrict__ delta, const double* __restrict__ eh,
-                                                 T* __restrict__ W, double* __restrict__ rowpart,
-                                                 double* __restrict__ rowpartV, RecFDims g) {
+                                                 const double* __restrict__ CY64, T* __restrict__ W,
+                                                 double* __restrict__ rowpart, double* __restrict__ rowpartV,
+                                                 RecFDims g) {
   const int lane = threadIdx.x & 63;
   const uint32_t nib = (uint32_t)((g.N + 63) / 64);
   const int i = (int)(blockIdx.x % nib) * 64 + lane;
@@ -248,27 +248,17 @@ __global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ en
   int t = 0, wo = 0;  // bin, and offset of its row in W
   auto emit = [&]() {
     if (PART && t < skip) return;
-    double lam;
-    if constexpr (EV) {
-      const double dl = delta[s0 * 64 + t];
-      double F;
-      if (!glmr_ev::interval_short(D, glmr_ev::slot_short(dl, eh[s0 * 64 + t]), &F, &lam))
-        glmr_ev::interval_call(D, dl, &F, &lam);
-      sum += F;
-    } else {
-      lam = exp_f64(D);
-      sum += lam;
-      if (TAU) sumv += lam * V;
-    }
+    const double lam = exp_f64(D);
+    sum += lam;
+    if (TAU) sumv += lam * V;
     if (STORE) {
       buf_store<T>((T)lam, wr, voff, wo);
       wo += pitch;
     }
   };
   auto step = [&]() {
-    const double d = EV ? edec[s0 * 64 + t] : ag;
-    if (TAU) V = d * (V + g.ctau * D);
-    D = d * D + acc;
+    if (TAU) V = ag * (V + g.ctau * D);
+    D = ag * D + acc;
     acc = 0.0;
     ++t;
     emit();
@@ -280,61 +270,259 @@ __global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ en
     const int e1 = off[s1 < g.NS ? s1 : g.NS];
     const uint32_t base = (uint32_t)(s0 * 64) & 0x7fffu;
     auto row = [&](uint32_t q) { return buf_load<T>(jr, voff, (int)(q & 0xffffu) * pitch); };
-    if constexpr (EV) {
-      // about one entry a slot, and integrals that dwarf it: four rows ahead
-      // in a shift register, so that the integrals are expanded once
-      int e = e0;
-      uint32_t q0 = ent[e], q1 = ent[e + 1], q2 = ent[e + 2], q3 = ent[e + 3];
-      T r0 = row(q0), r1 = row(q1), r2 = row(q2), r3 = row(q3);
-      while (t < tend - 1) {
-        while (e < e1 && ent_bin(q0, base) <= t) {
-          acc += (double)r0;
-          q0 = q1; q1 = q2; q2 = q3;
-          r0 = r1; r1 = r2; r2 = r3;
-          q3 = ent[e + 4];
-          r3 = row(q3);
-          ++e;
-        }
-        step();
-      }
-    } else {
-      const uint32_t last = ENT_FIRST | ((((uint32_t)(tend - 1) + base) & 0x7fffu) << 16);
-      uint32_t ec[FB8], en[FB8];
-      T rn[FB8];
-      if (e0 < e1) {
+    const uint32_t last = ENT_FIRST | ((((uint32_t)(tend - 1) + base) & 0x7fffu) << 16);
+    uint32_t ec[FB8], en[FB8];
+    T rn[FB8];
+    if (e0 < e1) {
 #pragma unroll
-        for (int q = 0; q < FB8; ++q) ec[q] = ent[e0 + q];
+      for (int q = 0; q < FB8; ++q) ec[q] = ent[e0 + q];
 #pragma unroll
-        for (int q = 0; q < FB8; ++q) rn[q] = row(ec[q]);
+      for (int q = 0; q < FB8; ++q) rn[q] = row(ec[q]);
 #pragma unroll
-        for (int q = 0; q < FB8; ++q) en[q] = ent[e0 + FB8 + q];
-      }
-      for (int e = e0; e < e1; e += FB8) {
-        if (e + FB8 > e1) {
-          // past the segment's entries: a first entry of its last bin, whose
-          // row is added after the last step
-#pragma unroll
-          for (int q = 0; q < FB8; ++q) ec[q] = e + q < e1 ? ec[q] : last;
-        }
-#pragma unroll
-        for (int q = 0; q < FB8; ++q) {
-          if (ec[q] & ENT_FIRST) {
-            const int b = ent_bin(ec[q], base), to = b < tend - 1 ? b : tend - 1;
-            while (t < to) step();
-          }
-          acc += (double)rn[q];
-          rn[q] = row(en[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < FB8; ++q) ec[q] = en[q];
-#pragma unroll
-        for (int q = 0; q < FB8; ++q) en[q] = ent[e + 2 * FB8 + q];
-      }
-      while (t < tend - 1) step();
+      for (int q = 0; q < FB8; ++q) en[q] = ent[e0 + FB8 + q];
     }
+    for (int e = e0; e < e1; e += FB8) {
+      if (e + FB8 > e1) {
+        // past the segment's entries: a first entry of its last bin, whose
+        // row is added after the last step
+#pragma unroll
+        for (int q = 0; q < FB8; ++q) ec[q] = e + q < e1 ? ec[q] : last;
+      }
+#pragma unroll
+      for (int q = 0; q < FB8; ++q) {
+        if (ec[q] & ENT_FIRST) {
+          const int b = ent_bin(ec[q], base), to = b < tend - 1 ? b : tend - 1;
+          while (t < to) step();
+        }
+        acc += (double)rn[q];
+        rn[q] = row(en[q]);
+      }
+#pragma unroll
+      for (int q = 0; q < FB8; ++q) ec[q] = en[q];
+#pragma unroll
+      for (int q = 0; q < FB8; ++q) en[q] = ent[e + 2 * FB8 + q];
+    }
+    while (t < tend - 1) step();
   }
   rowpart[(g.seg0 + sg) * g.Np + i] = sum;
   if (TAU) rowpartV[(g.seg0 + sg) * g.Np + i] = sumv;
+}
+
+// ------------------------------------------------------------------ forward, event grid
+// The interval integrals F, H (evfun.h) of a slot of length delta, over p equal
+// pieces of length d = delta / p <= 1/16: the midpoint expansion holds where
+// d max(1, |u|) <= 0.25, so up to |u| = 4 for the longest pieces (p = 1 between
+// the events of a large network).  Its sums over k are polynomials of degree
+// 12 in u whose coefficients depend on the slot only: with S the Stirling
+// numbers of the second kind and c_k = d^2k / (4^k (2k+1)!),
+//   F = d e^u sum_j u^j sum_k c_k S(2k, j),
+//   H = d e^{-d/2} e^u sum_j u^j sum_k c_k S(2k+1, j+1).
+// A wave forms those of 32 slots at a time, a slot a lane, in LDS; a step then
+// reads them at one address and takes an exponential and two Horner sums a
+// piece.  The expansion as written out per slot and lane took three times the
+// multiplications, and the closed forms past its bound, which some lane of a
+// wave takes at nearly every slot of a small network, a thousand
+// instructions and, as a call, 247 registers.
+constexpr int EVS = 32;  // slots in LDS
+constexpr int EVC = 34;  // doubles a slot: F's 13 coefficients, H's, e^{-d/2}, e^{-d}, 0.25 / d, p, delta, decay, (pad)
+constexpr double kEvPiece = 1.0 / 16.0;
+
+struct EvStirling {
+  double f[7][13], h[7][13];  // S(2k, j), S(2k+1, j+1)
+};
+constexpr EvStirling ev_stirling() {
+  double S[14][14] = {};
+  S[0][0] = 1.0;
+  for (int n = 1; n < 14; ++n)
+    for (int k = 1; k <= n; ++k) S[n][k] = k * S[n - 1][k] + S[n - 1][k - 1];
+  EvStirling e{};
+  for (int k = 0; k < 7; ++k)
+    for (int j = 0; j < 13; ++j) {
+      e.f[k][j] = S[2 * k][j];
+      e.h[k][j] = S[2 * k + 1][j + 1];
+    }
+  return e;
+}
+
+__device__ __forceinline__ void ev_coefficients(double delta, double edec, double* o) {
+  constexpr EvStirling S = ev_stirling();
+  // past 16 pieces ev_rare is cheaper: one piece, out of its bound
+  const double p = delta > kEvPiece && delta <= 1.0 ? __builtin_ceil(delta * (1.0 / kEvPiece)) : 1.0;
+  const double d = delta / p, eh = exp_f64(-0.5 * d);
+  double c[7] = {1.0};
+#pragma unroll
+  for (int k = 1; k < 7; ++k) c[k] = c[k - 1] * (d * d) * (1.0 / (4.0 * (2 * k) * (2 * k + 1)));
+#pragma unroll
+  for (int j = 0; j < 13; ++j) {
+    double f = 0.0, h = 0.0;
+#pragma unroll
+    for (int k = 6; k >= 0; --k) {
+      if (S.f[k][j] != 0.0) f = fma(c[k], S.f[k][j], f);
+      if (S.h[k][j] != 0.0) h = fma(c[k], S.h[k][j], h);
+    }
+    o[j] = d * f;
+    o[13 + j] = d * eh * h;
+  }
+  o[26] = eh;
+  o[27] = eh * eh;
+  o[28] = d > 0.0 ? 0.25 / d : 0.0;  // an empty slot's coefficients are zero: any u will do
+  o[29] = p;
+  o[30] = delta;
+  o[31] = edec;
+}
+
+// Past the bound of the staged pieces: the expansion over pieces of 0.25 / |D|
+// until the potential has decayed to |D| <= 2 (4 (|D| - 2) of them), then the
+// series of the rest, of length delta and 1 - xi = e1:
+//   F = delta + e1 sum_{n>=1} D^n S_n / (n n!),  S_n = 1 + xi + ... + xi^{n-1},
+//   H = e^{D xi} e1 sum_{n>=0} (D e1)^n / (n+1)!.
+// No call, so that the kernel keeps its registers.
+__device__ __forceinline__ void ev_rare(double D, double delta, double* F, double* H) {
+  double sf = 0.0, sh = 0.0, w = 1.0;
+#pragma unroll 1
+  while (fabs(D) > 2.0 && delta > 0.0) {
+    const double d = fmin(delta, 0.25 / fabs(D)), eh = exp_f64(-0.5 * d);
+    double f, h;
+    (void)glmr_ev::interval_short(D, glmr_ev::slot_short(d, eh), &f, &h);
+    sf += f;
+    sh = fma(w, h, sh);
+    D *= eh * eh;
+    w *= eh * eh;
+    delta -= d;
+  }
+  if (delta > 0.0) {
+    double e1 = 1.0 - exp_f64(-delta);
+    if (delta < 0.25) {  // without the cancellation: delta - delta^2 / 2! + ...
+      double q = 1.0;
+#pragma unroll 1
+      for (double n = 14.0; n >= 2.0; n -= 1.0) q = 1.0 - delta / n * q;
+      e1 = delta * q;
+    }
+    const double xi = 1.0 - e1, y = D * e1;
+    double p = 1.0, S = 1.0, acc = 0.0;
+#pragma unroll 1
+    for (double n = 1.0; n <= 26.0; n += 1.0) {
+      const double r = 1.0 / n;
+      p *= D * r;                 // D^n / n!
+      acc = fma(p * r, S, acc);   // D^n S_n / (n n!)
+      S = fma(xi, S, 1.0);        // S_{n+1}
+    }
+    double q = 1.0;
+#pragma unroll 1
+    for (double n = 26.0; n >= 2.0; n -= 1.0) q = fma(y / n, q, 1.0);
+    sf += fma(e1, acc, delta);
+    sh = fma(w * exp_f64(D * xi), e1 * q, sh);
+  }
+  *F = sf;
+  *H = sh;
+}
+
+template <typename T, bool STORE, bool FUSED, bool PART>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_rec_fwd_ev(
+    const uint32_t* __restrict__ ent, const int32_t* __restrict__ off, const T* __restrict__ Jt,
+    const double* __restrict__ Dc, const double* __restrict__ C64, const double* __restrict__ edec,
+    const double* __restrict__ delta, T* __restrict__ W, double* __restrict__ rowpart, RecFDims g) {
+  __shared__ __align__(16) double coef[4][EVS * EVC];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t nib = (uint32_t)((g.N + 63) / 64);
+  const int i = (int)(blockIdx.x % nib) * 64 + lane;
+  const int64_t sg = (int64_t)(blockIdx.x / nib) * 4 + wave;
+  if (sg >= g.n_seg) return;
+  const int64_t t0 = g.t0 + sg * g.seg;
+  const int64_t s0 = t0 >> 6;
+  const int skip = PART ? (int)(t0 & 63) : 0;
+  const int64_t left = g.B - s0 * 64;
+  const int tend = (int)(left < skip + g.seg ? left : skip + g.seg);
+  const int pitch = (int)(g.Np * (int64_t)sizeof(T)), voff = i * (int)sizeof(T);
+  const __amdgpu_buffer_rsrc_t jr =
+      __builtin_amdgcn_make_buffer_rsrc((void*)Jt, (short)0, (int)(g.Np * pitch), 0x00020000);
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(STORE ? W + (t0 - g.tw) * g.Np : nullptr), (short)0, STORE ? (int)(g.seg * pitch) : 0, 0x00020000);
+  double D = 0.0;
+  if (FUSED) {
+    const double* __restrict__ C = C64 + s0 * g.Np;
+#pragma unroll 8
+    for (int j = 0; j < (int)g.N; ++j) D += (double)buf_load<T>(jr, voff, j * pitch) * C[j];
+  } else {
+    D = Dc[(s0 / g.kc - g.row0) * g.Np + i];
+  }
+  double sum = 0.0;
+  if (tend > skip) {
+    double* mine = coef[wave];
+    int e = off[s0];
+    const int64_t s1 = (t0 + g.seg + 63) >> 6;
+    const int e1 = off[s1 < g.NS ? s1 : g.NS];
+    const uint32_t base = (uint32_t)(s0 * 64) & 0x7fffu;
+    // about one entry a slot: 64 entries a load, one a lane, and four rows
+    // ahead in a shift register
+    auto row = [&](uint32_t q) { return buf_load<T>(jr, voff, (int)(q & 0xffffu) * pitch); };
+    uint32_t ev = ent[e + lane], evn = ent[e + 64 + lane];
+    int at = 0;  // of entry e in ev
+    auto entry = [&](int k) {
+      return (uint32_t)(k < 64 ? __builtin_amdgcn_readlane((int)ev, k) : __builtin_amdgcn_readlane((int)evn, k - 64));
+    };
+    uint32_t q0 = entry(0), q1 = entry(1), q2 = entry(2), q3 = entry(3);
+    T r0 = row(q0), r1 = row(q1), r2 = row(q2), r3 = row(q3);
+    int wo = 0;
+    for (int t = 0;;) {
+      if ((t & (EVS - 1)) == 0) {  // a wave's LDS operations are in order: no barrier
+        __builtin_amdgcn_wave_barrier();
+        if (lane < EVS) ev_coefficients(delta[s0 * 64 + t + lane], edec[s0 * 64 + t + lane], mine + lane * EVC);
+        __builtin_amdgcn_wave_barrier();
+      }
+      const double dec = mine[(t & (EVS - 1)) * EVC + 31];
+      if (!PART || t >= skip) {
+        const double2* src = (const double2*)(mine + (t & (EVS - 1)) * EVC);
+        double c[32];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const double2 x = src[v];
+          c[2 * v] = x.x;
+          c[2 * v + 1] = x.y;
+        }
+        double F = 0.0, H = 0.0, Dk = D, w = 1.0;
+        const int p = __builtin_amdgcn_readfirstlane((int)c[29]);
+        const bool out = c[28] > 0.0 && !(fmax(1.0, fabs(D * c[26])) <= c[28]);
+        for (int k = 0; k < p; ++k) {
+          const double u = Dk * c[26], E = exp_f64(u);
+          double f = c[12], h = c[25];
+#pragma unroll
+          for (int v = 11; v >= 0; --v) {
+            f = fma(f, u, c[v]);
+            h = fma(h, u, c[13 + v]);
+          }
+          F = fma(E, f, F);
+          H = fma(w * E, h, H);
+          Dk *= c[27];
+          w *= c[27];
+        }
+        if (out) ev_rare(D, c[30], &F, &H);
+        sum += F;
+        if (STORE) {
+          buf_store<T>((T)H, wr, voff, wo);
+          wo += pitch;
+        }
+      }
+      if (t >= tend - 1) break;
+      double acc = 0.0;
+      while (e < e1 && ent_bin(q0, base) <= t) {
+        acc += (double)r0;
+        q0 = q1; q1 = q2; q2 = q3;
+        r0 = r1; r1 = r2; r2 = r3;
+        q3 = entry(at + 4);
+        r3 = row(q3);
+        ++e;
+        if (++at == 64) {
+          ev = evn;
+          evn = ent[e + 64 + lane];
+          at = 0;
+        }
+      }
+      D = fma(dec, D, acc);
+      ++t;
+    }
+  }
+  rowpart[(g.seg0 + sg) * g.Np + i] = sum;
 }
 
 // Dc[r][i] = sum_j C[(row0 + r) kc][j] J[i][j]: 64 x 64 tiles on the FP64 MFMA,
@@ -420,22 +608,25 @@ hipError_t rec_gather(const RecGArgs& a, hipStream_t st) {
   }
 }
 
-template <typename T, bool EV, bool TAU, bool STORE, bool FUSED, bool PART>
+template <typename T, bool TAU, bool STORE, bool FUSED, bool PART>
 hipError_t rec_fwd_run(const RecFArgs& a, hipStream_t st) {
   const RecFDims& g = a.g;
-  const int64_t blocks = (g.N + 63) / 64 * ((g.n_seg + 3) / 4);
-  hipLaunchKernelGGL((k_rec_fwd<T, EV, TAU, STORE, FUSED, PART>), dim3((unsigned)blocks), dim3(256), 0, st, a.ent1,
-                     a.off1, (const T*)a.Jt, a.Dc, a.Vc, a.C64, a.CY64, a.edec, a.delta, a.eh, (T*)a.W, a.rowpart,
-                     a.rowpartV, g);
+  const unsigned blocks = (unsigned)((g.N + 63) / 64 * ((g.n_seg + 3) / 4));
+  if (a.edec)
+    hipLaunchKernelGGL((k_rec_fwd_ev<T, STORE, FUSED, PART>), dim3(blocks), dim3(256), 0, st, a.ent1, a.off1,
+                       (const T*)a.Jt, a.Dc, a.C64, a.edec, a.delta, (T*)a.W, a.rowpart, g);
+  else
+    hipLaunchKernelGGL((k_rec_fwd<T, TAU, STORE, FUSED, PART>), dim3(blocks), dim3(256), 0, st, a.ent1, a.off1,
+                       (const T*)a.Jt, a.Dc, a.Vc, a.C64, a.CY64, (T*)a.W, a.rowpart, a.rowpartV, g);
   return hipGetLastError();
 }
 
-template <typename T, bool EV, bool TAU, bool STORE>
+template <typename T, bool TAU, bool STORE>
 hipError_t rec_fwd(const RecFArgs& a, hipStream_t st) {
   const bool part = a.g.seg < 64;
   if (a.fused)
-    return part ? rec_fwd_run<T, EV, TAU, STORE, true, true>(a, st) : rec_fwd_run<T, EV, TAU, STORE, true, false>(a, st);
-  return part ? rec_fwd_run<T, EV, TAU, STORE, false, true>(a, st) : rec_fwd_run<T, EV, TAU, STORE, false, false>(a, st);
+    return part ? rec_fwd_run<T, TAU, STORE, true, true>(a, st) : rec_fwd_run<T, TAU, STORE, true, false>(a, st);
+  return part ? rec_fwd_run<T, TAU, STORE, false, true>(a, st) : rec_fwd_run<T, TAU, STORE, false, false>(a, st);
 }
 
 template <typename T>
@@ -454,9 +645,8 @@ hipError_t rec_forward(const RecFArgs& a, hipStream_t st) {
     if (e == hipSuccess && tau) e = carry_gemm<T>(a, a.CY64, a.Vc, st);
     if (e != hipSuccess) return e;
   }
-  if (a.edec) return store ? rec_fwd<T, true, false, true>(a, st) : rec_fwd<T, true, false, false>(a, st);
-  if (tau) return store ? rec_fwd<T, false, true, true>(a, st) : rec_fwd<T, false, true, false>(a, st);
-  return store ? rec_fwd<T, false, false, true>(a, st) : rec_fwd<T, false, false, false>(a, st);
+  if (tau) return store ? rec_fwd<T, true, true>(a, st) : rec_fwd<T, true, false>(a, st);
+  return store ? rec_fwd<T, false, true>(a, st) : rec_fwd<T, false, false>(a, st);
 }
 
 }  // namespace
@@ -470,8 +660,7 @@ hipError_t launch_rec_gather(int prec, const RecGArgs& a, int first, hipStream_t
   if (prec == PREC_F64) e = a.ev.edec ? rec_gather<double, true>(a, st) : rec_gather<double, false>(a, st);
   else e = a.ev.edec ? rec_gather<float, true>(a, st) : rec_gather<float, false>(a, st);
   if (e != hipSuccess) return e;
-  const unsigned nb = (unsigned)(a.Np / 32);
-  hipLaunchKernelGGL(k_rec_reduce, dim3(nb, nb), dim3(256), 0, st, a, first);
+  hipLaunchKernelGGL(k_rec_reduce, dim3((unsigned)(a.Np / 32), (unsigned)(a.Np / 8)), dim3(256), 0, st, a, first);
   return hipGetLastError();
 }
 

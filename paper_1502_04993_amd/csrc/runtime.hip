@@ -101,7 +101,7 @@ struct glmr_ctx {
   bool evm = false;
   double T0 = 0, T1 = 0, max_gap = 0;
   double* tslot = nullptr;  // [NS*64 + 1]
-  double* evtab = nullptr;  // [6 * NS*64 + NS]: pw, ainv, left, delta, edec, eh, asub
+  double* evtab = nullptr;  // [5 * NS*64 + NS]: pw, ainv, left, delta, edec, asub
   float* evgl = nullptr;    // BF16: [NS*64][16] per-slot table of kernel U's interval integrals
   double max_span = 0;      // largest 64-slot span / tau of the current tables
 
@@ -400,8 +400,7 @@ EvSlots ev_slots(const glmr_ctx* c) {
   e.left = c->evtab + 2 * n;
   e.delta = c->evtab + 3 * n;
   e.edec = c->evtab + 4 * n;
-  e.eh = c->evtab + 5 * n;
-  e.asub = c->evtab + 6 * n;
+  e.asub = c->evtab + 5 * n;
   return e;
 }
 
@@ -410,7 +409,7 @@ EvSlots ev_slots(const glmr_ctx* c) {
 constexpr double kMaxSpan = 600.0;
 glmr_status build_ev_tables(glmr_ctx* c, Arena* ar) {
   const int64_t n = c->NS * 64;
-  TRY(persist(c, ar, c->evtab, (size_t)(6 * n + c->NS)));
+  TRY(persist(c, ar, c->evtab, (size_t)(5 * n + c->NS)));
   unsigned long long* ms = nullptr;
   TRY(temp_alloc(c, ar, ms, 1));
   if (ar) HIPCHK(c, launch_fill_i32((int32_t*)ms, 2, 0, c->st));  // the static scratch keeps old contents
@@ -424,8 +423,7 @@ glmr_status build_ev_tables(glmr_ctx* c, Arena* ar) {
   ta.left = c->evtab + 2 * n;
   ta.delta = c->evtab + 3 * n;
   ta.edec = c->evtab + 4 * n;
-  ta.eh = c->evtab + 5 * n;
-  ta.asub = c->evtab + 6 * n;
+  ta.asub = c->evtab + 5 * n;
   if (c->prec == PREC_BF16) {
     TRY(persist(c, ar, c->evgl, (size_t)(16 * n)));
     ta.gl = c->evgl;
@@ -570,7 +568,7 @@ glmr_status build_lists(glmr_ctx* c, const uint64_t* masks, glmr_ctx::WinList* w
     if (bins) {
       if ((st = dalloc(c, a.scnt, (size_t)c->NS)) != GLMR_OK) break;
       if (!c->off1 && (st = dalloc(c, c->off1, (size_t)c->NS + 1)) != GLMR_OK) break;
-      if ((st = dalloc(c, c->ent1, (size_t)c->nspk + 24)) != GLMR_OK) break;
+      if ((st = dalloc(c, c->ent1, (size_t)c->nspk + 192)) != GLMR_OK) break;
       a.off1 = c->off1;
       a.ent1 = c->ent1;
     }
@@ -591,7 +589,7 @@ glmr_status build_lists(glmr_ctx* c, const uint64_t* masks, glmr_ctx::WinList* w
     if (launch_list_windows(a, c->st) != hipSuccess ||
         launch_fill_i32((int32_t*)(a.ent2 + 4 * (size_t)total), 2, 0, c->st) != hipSuccess ||
         (bins && (launch_list_bins(a, c->st) != hipSuccess ||
-                  launch_fill_i32((int32_t*)a.ent1 + spikes, 24, 0, c->st) != hipSuccess)) ||
+                  launch_fill_i32((int32_t*)a.ent1 + spikes, 192, 0, c->st) != hipSuccess)) ||
         hipStreamSynchronize(c->st) != hipSuccess) {
       st = fail(c, GLMR_EDEVICE, "spike lists: %s", hipGetErrorString(hipGetLastError()));
       break;
@@ -935,7 +933,6 @@ glmr_status eval_rec(glmr_ctx* c, bool want_grad, bool want_tau) {
     f.CY64 = c->CY64;
     f.edec = ev.edec;
     f.delta = ev.delta;
-    f.eh = ev.eh;
     f.W = want_grad ? c->W : nullptr;
     f.rowpart = c->rowpart;
     f.rowpartV = want_tau ? c->rowpartV : nullptr;
