@@ -395,8 +395,15 @@ hipError_t launch_res_g(int shape, int fp8, const ResGArgs& a, hipStream_t st);
 // Reductions and assembly (FP64) -------------------------------------------
 hipError_t launch_gp_reduce(int prec, const void* Gp, int n_splits, int64_t Np, double* G64,
                             int first, hipStream_t st);
-hipError_t launch_rowpart_reduce(const double* rowpart, int64_t n_tiles, int64_t Np, double* out,
-                                 double* tmp, hipStream_t st);
+struct GpReduceArgs {     // FP32 partials of one recording
+  const void* Gp;         // [n_splits][n]
+  double* G64;            // [n]
+  int64_t n;
+  int n_splits, first;    // first: G64 is set, else added to
+};
+// list: device array of n_rec (the largest n is max_n), or null: `one`
+hipError_t launch_gp_reduce_group(const GpReduceArgs* list, const GpReduceArgs& one, int n_rec, int64_t max_n,
+                                  hipStream_t st);
 struct AssembleArgs {
   int N;
   int64_t Np;
@@ -406,18 +413,23 @@ struct AssembleArgs {
   const double* Jr;       // [Np][Np] parameters as used (rounded to the compute precision)
   const double* dsig;
   const double* dsigY;    // nullable
-  const double* rowsum;   // sum_t W  [Np]
-  const double* rowsumV;  // nullable
+  int64_t n_tiles;
+  const double* rowpart;  // [n_tiles][Np] partials of sum_t W
+  const double* rowpartV; // nullable: of sum_t W V
+  const double* gpart;    // nullable: of the self-delay correction of G_ii
+  double* rp_tmp;         // [rowpart_tmp_len(Np)]
   const double* G64;      // nullable (no gradient)
-  const double* gself;    // nullable: per-row correction of G_ii (self-delay)
-  const double* rowscale; // [Np] multiplier of rowsum/G (e^mu, FP8 scales folded in)
+  const double* rowscale; // [Np] multiplier of the row sums and G (e^mu, FP8 scales folded in)
   double* ll_rows;        // [Np]
   double* gJ;             // [Np][Np] or null
   double* gmu;            // [Np] or null
   double* tau_rows;       // [Np] or null
+  double* scal;           // [2] L, dL/dtau
+  double *out_rows, *out_gJ, *out_gmu;  // nullable: the same, N and N x N without padding
 };
-hipError_t launch_assemble(const AssembleArgs& a, hipStream_t st);
-hipError_t launch_sum_rows(const double* v, int n, double* out, hipStream_t st);
+// row sums, rows and gradient, totals (list as above)
+hipError_t launch_finish(const AssembleArgs* list, const AssembleArgs& one, int n_rec, int max_N, int64_t max_Np,
+                         hipStream_t st);
 
 // Parameter preparation
 hipError_t launch_prepare_params(int prec, int j2, int N, int64_t Np, const double* J64, const double* mu,

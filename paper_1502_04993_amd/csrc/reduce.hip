@@ -34,22 +34,45 @@ __device__ double block_sum(double v, double* sh) {
   return r;
 }
 
-// four consecutive entries a thread (16-byte loads; n is a multiple of 4),
-// each summed over the splits in split order
-__global__ void k_gp_reduce_f(const float* Gp, int n_splits, int64_t n, double* G, int first) {
-  const int64_t n4 = n / 4;
-  for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n4;
-       k += (int64_t)gridDim.x * blockDim.x) {
-    double4 v = first ? double4{0.0, 0.0, 0.0, 0.0} : ((const double4*)G)[k];
-    for (int s = 0; s < n_splits; ++s) {
-      const float4 p = ((const float4*)(Gp + s * n))[k];
+// The FP32 partials of kernel G: 64 x 4 consecutive entries a workgroup, each
+// by four threads that take a quarter of the splits (in order; the quarters are
+// then added in order) with eight 16-byte loads in flight.  HBM- or
+// MALL-bound: 268 MB (N = 500, 256 splits) in a third of the time that one
+// thread an entry, walking all splits, took (117 us).  One launch serves the
+// recordings of a batch (blockIdx.y).
+__global__ __launch_bounds__(256) void k_gp_reduce_f(const GpReduceArgs* __restrict__ list, GpReduceArgs one) {
+  __shared__ double4 part[3][64];
+  const GpReduceArgs a = list ? list[blockIdx.y] : one;
+  const int tx = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int64_t k = (int64_t)blockIdx.x * 64 + tx, n4 = a.n / 4;
+  const bool in = k < n4;
+  const int per = (a.n_splits + 3) / 4, s0 = q * per, s1 = s0 + per < a.n_splits ? s0 + per : a.n_splits;
+  double4 v{0.0, 0.0, 0.0, 0.0};
+  if (in) {
+    const float4* __restrict__ src = (const float4*)a.Gp + k;
+#pragma unroll 8
+    for (int s = s0; s < s1; ++s) {
+      const float4 p = src[s * n4];
       v.x += (double)p.x;
       v.y += (double)p.y;
       v.z += (double)p.z;
       v.w += (double)p.w;
     }
-    ((double4*)G)[k] = v;
   }
+  if (q) part[q - 1][tx] = v;
+  __syncthreads();
+  if (q || !in) return;
+  double4 g{0.0, 0.0, 0.0, 0.0};
+  if (!a.first) g = ((const double4*)a.G64)[k];
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    const double4 o = part[r][tx];
+    v.x += o.x;
+    v.y += o.y;
+    v.z += o.z;
+    v.w += o.w;
+  }
+  ((double4*)a.G64)[k] = double4{g.x + v.x, g.y + v.y, g.z + v.z, g.w + v.w};
 }
 __global__ void k_gp_reduce_d(const double* Gp, int n_splits, int64_t n, double* G, int first) {
   for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
@@ -60,29 +83,39 @@ __global__ void k_gp_reduce_d(const double* Gp, int n_splits, int64_t n, double*
   }
 }
 
-// rowpart[tile][i]: two passes, splits over tiles then a fixed-order merge
+// rowpart[tile][i] (and the tau and self-delay partials, blockIdx.z % 3): split
+// sums over tiles, which k_assemble merges
 constexpr int RP_SPLITS = 64;
-__global__ void k_rowpart_a(const double* rp, int64_t n_tiles, int64_t Np, double* tmp) {
+__global__ __launch_bounds__(256) void k_rowpart(const AssembleArgs* __restrict__ list, AssembleArgs one) {
+  const AssembleArgs a = list ? list[blockIdx.z / 3] : one;
+  const int which = (int)(blockIdx.z % 3);
+  const double* __restrict__ rp = which == 0 ? a.rowpart : which == 1 ? a.rowpartV : a.gpart;
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t sp = blockIdx.y;
-  if (i >= Np) return;
-  const int64_t per = (n_tiles + RP_SPLITS - 1) / RP_SPLITS;
-  const int64_t t0 = sp * per, t1 = (t0 + per < n_tiles) ? t0 + per : n_tiles;
+  if (!rp || i >= a.Np) return;
+  const int64_t per = (a.n_tiles + RP_SPLITS - 1) / RP_SPLITS;
+  const int64_t t0 = sp * per, t1 = (t0 + per < a.n_tiles) ? t0 + per : a.n_tiles;
   double v = 0.0;
-  for (int64_t t = t0; t < t1; ++t) v += rp[t * Np + i];
-  tmp[sp * Np + i] = v;
-}
-__global__ void k_rowpart_b(const double* tmp, int64_t Np, double* out) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= Np) return;
-  double v = 0.0;
-  for (int sp = 0; sp < RP_SPLITS; ++sp) v += tmp[sp * Np + i];
-  out[i] = v;
+#pragma unroll 8
+  for (int64_t t = t0; t < t1; ++t) v += rp[t * a.Np + i];
+  a.rp_tmp[(which * RP_SPLITS + sp) * a.Np + i] = v;
 }
 
-__global__ __launch_bounds__(RT) void k_assemble(AssembleArgs a) {
+// sum over the splits of row i's partials, the same in every lane (a fixed tree)
+__device__ inline double row_total(const AssembleArgs& a, int which, int64_t i) {
+  const int lane = threadIdx.x & 63;
+  double v = a.rp_tmp[(which * RP_SPLITS + lane) * a.Np + i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// one workgroup per row (blockIdx.x) and recording (blockIdx.y)
+__global__ __launch_bounds__(RT) void k_assemble(const AssembleArgs* __restrict__ list, AssembleArgs one) {
   __shared__ double sh[RT];
+  const AssembleArgs a = list ? list[blockIdx.y] : one;
   const int64_t i = blockIdx.x;
+  if (i >= a.N) return;
   const int tid = threadIdx.x;
   const double* Jr = a.Jr + i * a.Np;
   const double* ds = a.dsig + i * a.Np;
@@ -91,34 +124,46 @@ __global__ __launch_bounds__(RT) void k_assemble(AssembleArgs a) {
     v += Jr[j] * ds[j];
     if (a.dsigY) vy += Jr[j] * a.dsigY[i * a.Np + j];
   }
+  const double sc = a.dt * a.rowscale[i];
+  const double integ = sc * row_total(a, 0, i);
+  const double gself = a.gpart ? row_total(a, 2, i) : 0.0;
+  if (a.gJ) {
+    for (int64_t j = tid; j < a.Np; j += RT) {
+      const double g = (j < a.N) ? ds[j] - sc * (a.G64[i * a.Np + j] + (j == i ? gself : 0.0)) : 0.0;
+      a.gJ[i * a.Np + j] = g;
+      if (a.out_gJ && j < a.N) a.out_gJ[i * a.N + j] = g;
+    }
+  }
   const double dot = block_sum(v, sh);
   const double doty = a.dsigY ? block_sum(vy, sh) : 0.0;
-  const double sc = a.dt * a.rowscale[i];
-  const double integ = sc * a.rowsum[i];
   if (tid == 0) {
-    const double spike = (double)a.q[i] * a.mu[i] + dot;
-    a.ll_rows[i] = spike - integ;
-    if (a.gmu) a.gmu[i] = (double)a.q[i] - integ;
-    if (a.tau_rows) a.tau_rows[i] = doty - (a.rowsumV ? sc * a.rowsumV[i] : 0.0);
+    const double spike = (double)a.q[i] * a.mu[i] + dot, ll = spike - integ, gm = (double)a.q[i] - integ;
+    a.ll_rows[i] = ll;
+    if (a.out_rows) a.out_rows[i] = ll;
+    if (a.gmu) a.gmu[i] = gm;
+    if (a.out_gmu) a.out_gmu[i] = gm;
   }
-  if (a.gJ) {
-    for (int64_t j = tid; j < a.Np; j += RT)
-      a.gJ[i * a.Np + j] =
-          (j < a.N) ? ds[j] - sc * (a.G64[i * a.Np + j] + ((a.gself && j == i) ? a.gself[i] : 0.0)) : 0.0;
+  if (a.tau_rows && tid < 64) {
+    const double tv = a.rowpartV ? sc * row_total(a, 1, i) : 0.0;
+    if (tid == 0) a.tau_rows[i] = doty - tv;
   }
 }
 
-__global__ __launch_bounds__(RT) void k_sum_rows(const double* v, int n, double* out) {
+// L (and dL/dtau, blockIdx.x = 1) of each recording (blockIdx.y) from its rows
+__global__ __launch_bounds__(RT) void k_sum_rows(const AssembleArgs* __restrict__ list, AssembleArgs one) {
   __shared__ double sh[RT];
+  const AssembleArgs a = list ? list[blockIdx.y] : one;
+  const double* v = blockIdx.x ? a.tau_rows : a.ll_rows;
+  if (!v) return;
   // Neumaier-compensated per-thread partials, then a fixed tree
   double s = 0.0, c = 0.0;
-  for (int k = threadIdx.x; k < n; k += RT) {
+  for (int k = threadIdx.x; k < a.N; k += RT) {
     double x = v[k], t = s + x;
     c += (fabs(s) >= fabs(x)) ? (s - t) + x : (x - t) + s;
     s = t;
   }
   double tot = block_sum(s + c, sh);
-  if (threadIdx.x == 0) out[0] = tot;
+  if (threadIdx.x == 0) a.scal[blockIdx.x] = tot;
 }
 
 template <typename T> __device__ inline T to_prec(double x);
@@ -527,32 +572,30 @@ int grid_for(int64_t n, int threads) {
 hipError_t launch_gp_reduce(int prec, const void* Gp, int n_splits, int64_t Np, double* G64,
                             int first, hipStream_t st) {
   const int64_t n = Np * Np;
-  if (prec == PREC_F64 || prec == PREC_F32)  // FP64 partials in both modes
+  if (prec == PREC_F64 || prec == PREC_F32) {  // FP64 partials in both modes
     hipLaunchKernelGGL(k_gp_reduce_d, dim3(grid_for(n, 256)), dim3(256), 0, st, (const double*)Gp,
                        n_splits, n, G64, first);
-  else
-    hipLaunchKernelGGL(k_gp_reduce_f, dim3(grid_for(n / 4, 256)), dim3(256), 0, st, (const float*)Gp,
-                       n_splits, n, G64, first);
+    return hipGetLastError();
+  }
+  return launch_gp_reduce_group(nullptr, GpReduceArgs{Gp, G64, n, n_splits, first}, 1, n, st);
+}
+
+hipError_t launch_gp_reduce_group(const GpReduceArgs* list, const GpReduceArgs& one, int n_rec, int64_t max_n,
+                                  hipStream_t st) {
+  hipLaunchKernelGGL(k_gp_reduce_f, dim3((unsigned)((max_n / 4 + 63) / 64), (unsigned)n_rec), dim3(256), 0, st, list,
+                     one);
   return hipGetLastError();
 }
 
-hipError_t launch_rowpart_reduce(const double* rowpart, int64_t n_tiles, int64_t Np, double* out,
-                                 double* tmp, hipStream_t st) {
-  hipLaunchKernelGGL(k_rowpart_a, dim3((unsigned)((Np + 255) / 256), RP_SPLITS), dim3(256), 0, st,
-                     rowpart, n_tiles, Np, tmp);
-  hipLaunchKernelGGL(k_rowpart_b, dim3((unsigned)((Np + 255) / 256)), dim3(256), 0, st, tmp, Np, out);
-  return hipGetLastError();
-}
+int64_t rowpart_tmp_len(int64_t Np) { return 3 * RP_SPLITS * Np; }
 
-int64_t rowpart_tmp_len(int64_t Np) { return RP_SPLITS * Np; }
-
-hipError_t launch_assemble(const AssembleArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_assemble, dim3((unsigned)a.N), dim3(RT), 0, st, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_sum_rows(const double* v, int n, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_sum_rows, dim3(1), dim3(RT), 0, st, v, n, out);
+hipError_t launch_finish(const AssembleArgs* list, const AssembleArgs& one, int n_rec, int max_N, int64_t max_Np,
+                         hipStream_t st) {
+  const unsigned parts = list || (!one.rowpartV && !one.gpart) ? 1 : 3;  // a batch has neither
+  hipLaunchKernelGGL(k_rowpart, dim3((unsigned)((max_Np + 255) / 256), RP_SPLITS, (unsigned)(3 * (n_rec - 1) + parts)),
+                     dim3(256), 0, st, list, one);
+  hipLaunchKernelGGL(k_assemble, dim3((unsigned)max_N, (unsigned)n_rec), dim3(RT), 0, st, list, one);
+  hipLaunchKernelGGL(k_sum_rows, dim3(one.tau_rows && !list ? 2 : 1, (unsigned)n_rec), dim3(RT), 0, st, list, one);
   return hipGetLastError();
 }
 

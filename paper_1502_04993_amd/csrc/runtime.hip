@@ -110,7 +110,6 @@ struct glmr_ctx {
   uint64_t* masks0 = nullptr;  // recorded raster's masks when delayed (masks is the shifted one)
   double* C0 = nullptr;        // its carries when d_s != d
   double* gpart = nullptr;     // [Bp/bt1][Np] self-delay correction of G_ii per tile
-  double* gself = nullptr;     // [Np]
 
   // kernel
   bool have_kernel = false, have_y = false, keep_y = false;
@@ -150,8 +149,6 @@ struct glmr_ctx {
   double* G64 = nullptr;
   double* rowpart = nullptr;
   double* rowpartV = nullptr;
-  double* rowsum = nullptr;
-  double* rowsumV = nullptr;
   double* rp_tmp = nullptr;
   double* ll_rows = nullptr;
   double* gJ = nullptr;
@@ -760,10 +757,7 @@ glmr_status ensure_workspace(glmr_ctx* c, bool want_grad, bool want_tau) {
   }
   if (!c->rowpart) TRY(dalloc(c, c->rowpart, (size_t)ntiles_t * Np));
   if (want_tau && !c->rowpartV) TRY(dalloc(c, c->rowpartV, (size_t)ntiles_t * Np));
-  if (!c->rowsum) TRY(dalloc(c, c->rowsum, (size_t)Np));
   if (self_delayed(c) && !c->gpart) TRY(dalloc(c, c->gpart, (size_t)ntiles_t * Np));
-  if (self_delayed(c) && !c->gself) TRY(dalloc(c, c->gself, (size_t)Np));
-  if (want_tau && !c->rowsumV) TRY(dalloc(c, c->rowsumV, (size_t)Np));
   if (!c->rp_tmp) TRY(dalloc(c, c->rp_tmp, (size_t)rowpart_tmp_len(Np)));
   if (!c->ll_rows) TRY(dalloc(c, c->ll_rows, (size_t)Np));
   if (!c->tau_rows) TRY(dalloc(c, c->tau_rows, (size_t)Np));
@@ -832,6 +826,14 @@ bool shape_tune_u(const glmr_ctx* c, int k) {
   int n = 0;
   const ResShape* sh = res_shapes(&n);
   return shape_ok_u(c, k) && sh[k].u_own;
+}
+
+// the shape that stands for the fragment-major kernel U
+int frag_u_shape() {
+  int n = 0, k = 0;
+  const ResShape* sh = res_shapes(&n);
+  while (k < n && !(sh[k].frag && sh[k].u_own)) ++k;
+  return k;
 }
 
 ResShape res_shape(int k) {
@@ -1065,37 +1067,36 @@ glmr_status eval_core(glmr_ctx* c, bool want_grad, bool want_tau) {
   return eval_finish(c, want_grad, want_tau, c->Bp / c->bt1);
 }
 
-// Row sums of the weights over all bins (ntiles_t partials a row), then L_i,
-// dL/dmu, dL/dJ (dL/dtau) in FP64.
-glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau, int64_t ntiles_t) {
-  const int64_t Np = c->Np;
-  ProfScope ps(c, K_ASM);
-  HIPCHK(c, launch_rowpart_reduce(c->rowpart, ntiles_t, Np, c->rowsum, c->rp_tmp, c->st));
-  if (want_tau)
-    HIPCHK(c, launch_rowpart_reduce(c->rowpartV, ntiles_t, Np, c->rowsumV, c->rp_tmp, c->st));
-  if (want_grad && self_delayed(c))
-    HIPCHK(c, launch_rowpart_reduce(c->gpart, ntiles_t, Np, c->gself, c->rp_tmp, c->st));
+// Arguments of the last kernels of an evaluation: row sums of the weights over
+// all bins (n_tiles partials a row), then L_i, dL/dmu, dL/dJ (dL/dtau) in FP64.
+AssembleArgs make_assemble_args(glmr_ctx* c, bool want_grad, bool want_tau, int64_t n_tiles) {
   AssembleArgs aa{};
   aa.N = c->N;
-  aa.Np = Np;
+  aa.Np = c->Np;
   aa.dt = c->evm ? c->tau : c->dt;  // the event grid's integrals are in units of tau
   aa.q = c->q;
   aa.mu = c->mu;
   aa.Jr = c->Jr;
   aa.dsig = c->dsig;
   aa.dsigY = want_tau ? c->dsigY : nullptr;
-  aa.rowsum = c->rowsum;
-  aa.rowsumV = want_tau ? c->rowsumV : nullptr;
+  aa.n_tiles = n_tiles;
+  aa.rowpart = c->rowpart;
+  aa.rowpartV = want_tau ? c->rowpartV : nullptr;
+  aa.gpart = (want_grad && self_delayed(c)) ? c->gpart : nullptr;
+  aa.rp_tmp = c->rp_tmp;
   aa.G64 = want_grad ? c->G64 : nullptr;
-  aa.gself = (want_grad && self_delayed(c)) ? c->gself : nullptr;
   aa.rowscale = c->rowscale;
   aa.ll_rows = c->ll_rows;
   aa.gJ = want_grad ? c->gJ : nullptr;
   aa.gmu = want_grad ? c->gmu : nullptr;
   aa.tau_rows = want_tau ? c->tau_rows : nullptr;
-  HIPCHK(c, launch_assemble(aa, c->st));
-  HIPCHK(c, launch_sum_rows(c->ll_rows, c->N, c->scal, c->st));
-  if (want_tau) HIPCHK(c, launch_sum_rows(c->tau_rows, c->N, c->scal + 1, c->st));
+  aa.scal = c->scal;
+  return aa;
+}
+
+glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau, int64_t n_tiles) {
+  ProfScope ps(c, K_ASM);
+  HIPCHK(c, launch_finish(nullptr, make_assemble_args(c, want_grad, want_tau, n_tiles), 1, c->N, c->Np, c->st));
   return GLMR_OK;
 }
 
@@ -1470,46 +1471,35 @@ struct glmr_batch {
   // context's own.  Recordings with the same pair share one launch.
   int tuned_u[2] = {-1, -1}, tuned_g[2] = {-1, -1};
   std::vector<int> rec_u, rec_g;
-  struct Group {         // recordings of one chunk with the same shapes, as work queues
-    int su = -1, sg = -1;
-    std::vector<int> recs, nsplits;
-    ResUArgs* du = nullptr;
-    ResGArgs* dg = nullptr;
-    int64_t *pu = nullptr, *pg = nullptr;
-    int64_t tu = 0, tg = 0;
-    int64_t *xu = nullptr, *xg = nullptr;  // [8][m + 1] per-XCD tile prefixes (fragment-major kernels)
-    int64_t gu = 0, gg = 0;                // their launch grids
+  // Work queues of one launch: the recordings of a chunk with the same shape of
+  // kernel U (or of kernel G).  Offsets are into the plan's device memory.
+  struct Queue {
+    int shape = -1, n = 0;
+    size_t args = 0, prefix = 0, xprefix = 0;  // args, [n + 1], [8][n + 1]
+    int64_t total = 0, grid = 0;               // tiles; workgroups of the fragment-major kernels
   };
   struct Chunk {         // the recordings that have time chunk ci
-    std::vector<Group> groups;
+    std::vector<Queue> u, g;
+    size_t red = 0;      // their GpReduceArgs
+    int n_red = 0;
+    int64_t max_n = 0;
   };
   std::vector<Chunk> chunks;
-  int32_t** dcnt = nullptr;  // [n] each context's counters
+  size_t asm_args = 0;   // every recording's AssembleArgs
+  int max_N = 0;
+  int64_t max_Np = 0;
+  // The plan's device memory, kept from call to call and refilled where its
+  // contents differ; then the scratch words.
+  std::vector<unsigned char> host;  // contents
+  unsigned char* dev_mem = nullptr;
+  unsigned char* pinned = nullptr;
+  size_t cap = 0;
+  int32_t** dcnt = nullptr;  // [n] each context's counters (in the plan)
   int32_t* dsum = nullptr;   // active rows over all recordings
   int32_t* hsum = nullptr;   // pinned
-  std::vector<void*> allocs;
 };
 
 namespace {
-
-template <typename T>
-hipError_t balloc(glmr_batch* b, T*& p, size_t n) {
-  void* q = nullptr;
-  hipError_t e = hipMalloc(&q, (n ? n : 1) * sizeof(T));
-  if (e == hipSuccess) {
-    b->allocs.push_back(q);
-    p = (T*)q;
-  }
-  return e;
-}
-
-void free_queues(glmr_batch* b) {
-  for (void* p : b->allocs) hipFree(p);
-  b->allocs.clear();
-  b->chunks.clear();
-  b->dcnt = nullptr;
-  b->dsum = nullptr;
-}
 
 // Every context works on the batch's stream while the batch runs it.
 struct OnBatchStream {
@@ -1534,84 +1524,118 @@ int shape_class(const glmr_ctx* c) { return c->Np % 256 == 0 ? 0 : 1; }
 // Work queues for the grouped launches (after every context's workspace exists).
 glmr_status build_queues(glmr_batch* b) {
   glmr_ctx* c0 = b->ctxs[0];
-  free_queues(b);
   const int n = (int)b->ctxs.size();
+  std::vector<unsigned char> mem;
+  auto put = [&](const void* p, size_t bytes) {
+    const size_t at = (mem.size() + 255) & ~(size_t)255;
+    mem.resize(at + bytes);
+    std::memcpy(mem.data() + at, p, bytes);
+    return at;
+  };
   std::vector<int32_t*> hc(n);
   for (int r = 0; r < n; ++r) {
     TRY(ensure_workspace(b->ctxs[r], true, false));
     hc[r] = b->ctxs[r]->counters;
   }
-  HIPCHK(c0, balloc(b, b->dcnt, (size_t)n));
-  HIPCHK(c0, balloc(b, b->dsum, 1));
-  HIPCHK(c0, hipMemcpy(b->dcnt, hc.data(), n * sizeof(int32_t*), hipMemcpyHostToDevice));
-  if (!b->grouped) return GLMR_OK;
-  int64_t nch = 0;
-  for (glmr_ctx* c : b->ctxs) nch = std::max<int64_t>(nch, (c->Bp + c->L - 1) / c->L);
-  b->chunks.resize(nch);
-  for (int64_t ci = 0; ci < nch; ++ci) {
-    glmr_batch::Chunk& ch = b->chunks[ci];
-    struct Lists {
-      std::vector<ResUArgs> ua;
-      std::vector<ResGArgs> ga;
-      std::vector<int64_t> pu{0}, pg{0};
-    };
-    std::vector<Lists> lists;
-    for (int r = 0; r < n; ++r) {
-      glmr_ctx* c = b->ctxs[r];
-      const int64_t t0 = ci * c->L;
-      if (t0 >= c->Bp) continue;
-      const int64_t Lc = std::min<int64_t>(c->L, c->Bp - t0);
-      size_t q = 0;
-      while (q < ch.groups.size() && !(ch.groups[q].su == b->rec_u[r] && ch.groups[q].sg == b->rec_g[r])) ++q;
-      if (q == ch.groups.size()) {
-        ch.groups.emplace_back();
-        ch.groups.back().su = b->rec_u[r];
-        ch.groups.back().sg = b->rec_g[r];
-        lists.emplace_back();
-      }
-      glmr_batch::Group& gr = ch.groups[q];
-      Lists& li = lists[q];
-      li.ua.push_back(make_u_args(c, gr.su, t0, Lc));
-      li.ga.push_back(make_g_args(c, gr.sg, t0, Lc));
-      li.pu.push_back(li.pu.back() + (int64_t)li.ua.back().n_itiles * li.ua.back().n_ttiles);
-      li.pg.push_back(li.pg.back() + (int64_t)li.ga.back().n_splits * li.ga.back().n_itiles * li.ga.back().n_jtiles);
-      gr.recs.push_back(r);
-      gr.nsplits.push_back(li.ga.back().n_splits);
+  const size_t at_cnt = put(hc.data(), n * sizeof(int32_t*));
+  b->chunks.clear();
+  if (b->grouped) {
+    std::vector<AssembleArgs> fin;
+    int64_t nch = 0;
+    b->max_N = 0;
+    b->max_Np = 0;
+    for (glmr_ctx* c : b->ctxs) {
+      nch = std::max<int64_t>(nch, (c->Bp + c->L - 1) / c->L);
+      fin.push_back(make_assemble_args(c, true, false, c->Bp / c->bt1));
+      b->max_N = std::max(b->max_N, c->N);
+      b->max_Np = std::max(b->max_Np, c->Np);
     }
-    for (size_t q = 0; q < ch.groups.size(); ++q) {
-      glmr_batch::Group& gr = ch.groups[q];
-      const Lists& li = lists[q];
-      const size_t m = gr.recs.size();
-      HIPCHK(c0, balloc(b, gr.du, m));
-      HIPCHK(c0, balloc(b, gr.dg, m));
-      HIPCHK(c0, balloc(b, gr.pu, m + 1));
-      HIPCHK(c0, balloc(b, gr.pg, m + 1));
-      HIPCHK(c0, hipMemcpy(gr.du, li.ua.data(), m * sizeof(ResUArgs), hipMemcpyHostToDevice));
-      HIPCHK(c0, hipMemcpy(gr.dg, li.ga.data(), m * sizeof(ResGArgs), hipMemcpyHostToDevice));
-      HIPCHK(c0, hipMemcpy(gr.pu, li.pu.data(), (m + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-      HIPCHK(c0, hipMemcpy(gr.pg, li.pg.data(), (m + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-      gr.tu = li.pu.back();
-      gr.tg = li.pg.back();
+    b->asm_args = put(fin.data(), fin.size() * sizeof(AssembleArgs));
+    b->chunks.resize(nch);
+    for (int64_t ci = 0; ci < nch; ++ci) {
+      glmr_batch::Chunk& ch = b->chunks[ci];
+      struct List {
+        std::vector<ResUArgs> ua;
+        std::vector<ResGArgs> ga;
+        std::vector<int64_t> pre{0};
+      };
+      std::vector<List> lu, lg;
+      std::vector<GpReduceArgs> red;
+      // the queue of shape k (one launch), made if it is new
+      auto queue = [](std::vector<glmr_batch::Queue>& qs, std::vector<List>& ls, int k) -> List& {
+        size_t q = 0;
+        while (q < qs.size() && qs[q].shape != k) ++q;
+        if (q == qs.size()) {
+          qs.emplace_back();
+          qs.back().shape = k;
+          ls.emplace_back();
+        }
+        return ls[q];
+      };
+      for (int r = 0; r < n; ++r) {
+        glmr_ctx* c = b->ctxs[r];
+        const int64_t t0 = ci * c->L;
+        if (t0 >= c->Bp) continue;
+        const int64_t Lc = std::min<int64_t>(c->L, c->Bp - t0);
+        const ResUArgs ua = make_u_args(c, b->rec_u[r], t0, Lc);
+        const ResGArgs ga = make_g_args(c, b->rec_g[r], t0, Lc);
+        // (the fragment-major shapes share one kernel U)
+        const int ku = res_shape(b->rec_u[r]).frag ? frag_u_shape() : b->rec_u[r];
+        List& u = queue(ch.u, lu, ku);
+        u.ua.push_back(ua);
+        u.pre.push_back(u.pre.back() + (int64_t)ua.n_itiles * ua.n_ttiles);
+        List& g = queue(ch.g, lg, b->rec_g[r]);
+        g.ga.push_back(ga);
+        g.pre.push_back(g.pre.back() + (int64_t)ga.n_splits * ga.n_itiles * ga.n_jtiles);
+        red.push_back(GpReduceArgs{c->Gp, c->G64, c->Np * c->Np, ga.n_splits, ci == 0 ? 1 : 0});
+        ch.max_n = std::max(ch.max_n, c->Np * c->Np);
+      }
+      ch.red = put(red.data(), red.size() * sizeof(GpReduceArgs));
+      ch.n_red = (int)red.size();
       // each recording's tiles split evenly over the 8 XCDs (see ResUGroup)
-      auto stripes = [&](const std::vector<int64_t>& pre, int64_t*& dst, int64_t* grid) -> glmr_status {
+      auto fill = [&](glmr_batch::Queue& q, const List& li, const void* args, size_t bytes) {
+        const size_t m = li.pre.size() - 1;
+        q.n = (int)m;
+        q.args = put(args, bytes);
+        q.prefix = put(li.pre.data(), (m + 1) * sizeof(int64_t));
+        q.total = li.pre.back();
         std::vector<int64_t> x(8 * (m + 1), 0);
         int64_t most = 0;
         for (int xc = 0; xc < 8; ++xc) {
           for (size_t r = 0; r < m; ++r) {
-            const int64_t t = pre[r + 1] - pre[r];
+            const int64_t t = li.pre[r + 1] - li.pre[r];
             x[xc * (m + 1) + r + 1] = x[xc * (m + 1) + r] + t / 8 + (xc < t % 8 ? 1 : 0);
           }
           most = std::max(most, x[xc * (m + 1) + m]);
         }
-        HIPCHK(c0, balloc(b, dst, x.size()));
-        HIPCHK(c0, hipMemcpy(dst, x.data(), x.size() * sizeof(int64_t), hipMemcpyHostToDevice));
-        *grid = 8 * most;
-        return GLMR_OK;
+        q.xprefix = put(x.data(), x.size() * sizeof(int64_t));
+        q.grid = 8 * most;
       };
-      TRY(stripes(li.pu, gr.xu, &gr.gu));
-      TRY(stripes(li.pg, gr.xg, &gr.gg));
+      for (size_t q = 0; q < ch.u.size(); ++q) fill(ch.u[q], lu[q], lu[q].ua.data(), lu[q].ua.size() * sizeof(ResUArgs));
+      for (size_t q = 0; q < ch.g.size(); ++q) fill(ch.g[q], lg[q], lg[q].ga.data(), lg[q].ga.size() * sizeof(ResGArgs));
     }
   }
+  const size_t at_sum = (mem.size() + 255) & ~(size_t)255;
+  mem.resize(at_sum + 256, 0);
+  if (mem.size() > b->cap) {
+    if (b->dev_mem) (void)hipFree(b->dev_mem);
+    if (b->pinned) (void)hipHostFree(b->pinned);
+    b->dev_mem = b->pinned = nullptr;
+    b->cap = 0;
+    b->host.clear();
+    const size_t cap = std::max<size_t>(2 * mem.size(), 1 << 16);
+    HIPCHK(c0, hipMalloc((void**)&b->dev_mem, cap));
+    HIPCHK(c0, hipHostMalloc((void**)&b->pinned, cap, hipHostMallocDefault));
+    b->cap = cap;
+  }
+  if (mem != b->host) {
+    std::memcpy(b->pinned, mem.data(), mem.size());
+    HIPCHK(c0, hipMemcpyAsync(b->dev_mem, b->pinned, mem.size(), hipMemcpyHostToDevice, b->st));
+    HIPCHK(c0, hipStreamSynchronize(b->st));
+    b->host = std::move(mem);
+  }
+  b->dcnt = (int32_t**)(b->dev_mem + at_cnt);
+  b->dsum = (int32_t*)(b->dev_mem + at_sum);
   return GLMR_OK;
 }
 
@@ -1619,17 +1643,20 @@ glmr_status build_queues(glmr_batch* b) {
 glmr_status launch_chunk_groups(glmr_batch* b, size_t ci, bool want_u, bool want_g) {
   glmr_ctx* c0 = b->ctxs[0];
   const int fp8 = c0->prec == PREC_FP8 ? 1 : 0;
-  for (const glmr_batch::Group& gr : b->chunks[ci].groups) {
-    const int m = (int)gr.recs.size();
-    if (want_u) {
+  const glmr_batch::Chunk& ch = b->chunks[ci];
+  auto i64 = [&](size_t at) { return (const int64_t*)(b->dev_mem + at); };
+  if (want_u)
+    for (const glmr_batch::Queue& q : ch.u) {
       ProfScope ps(c0, K_BU);
-      HIPCHK(c0, launch_res_u_group(gr.su, fp8, ResUGroup{gr.du, gr.pu, m, gr.tu, gr.xu, gr.gu}, b->st));
+      HIPCHK(c0, launch_res_u_group(q.shape, fp8, ResUGroup{(const ResUArgs*)(b->dev_mem + q.args), i64(q.prefix), q.n,
+                                                            q.total, i64(q.xprefix), q.grid}, b->st));
     }
-    if (want_g) {
+  if (want_g)
+    for (const glmr_batch::Queue& q : ch.g) {
       ProfScope ps(c0, K_BG);
-      HIPCHK(c0, launch_res_g_group(gr.sg, fp8, ResGGroup{gr.dg, gr.pg, m, gr.tg, gr.xg, gr.gg}, b->st));
+      HIPCHK(c0, launch_res_g_group(q.shape, fp8, ResGGroup{(const ResGArgs*)(b->dev_mem + q.args), i64(q.prefix), q.n,
+                                                            q.total, i64(q.xprefix), q.grid}, b->st));
     }
-  }
   return GLMR_OK;
 }
 
@@ -1639,15 +1666,16 @@ glmr_status batch_eval_core(glmr_batch* b) {
     for (glmr_ctx* c : b->ctxs) TRY(eval_core(c, true, false));
     return GLMR_OK;
   }
+  glmr_ctx* c0 = b->ctxs[0];
   for (size_t ci = 0; ci < b->chunks.size(); ++ci) {
     TRY(launch_chunk_groups(b, ci, true, true));
-    for (const glmr_batch::Group& gr : b->chunks[ci].groups)
-      for (size_t q = 0; q < gr.recs.size(); ++q) {
-        glmr_ctx* c = b->ctxs[gr.recs[q]];
-        HIPCHK(c, launch_gp_reduce(c->prec, c->Gp, gr.nsplits[q], c->Np, c->G64, ci == 0, b->st));
-      }
+    const glmr_batch::Chunk& ch = b->chunks[ci];
+    ProfScope ps(c0, K_RED);
+    HIPCHK(c0, launch_gp_reduce_group((const GpReduceArgs*)(b->dev_mem + ch.red), GpReduceArgs{}, ch.n_red, ch.max_n, b->st));
   }
-  for (glmr_ctx* c : b->ctxs) TRY(eval_finish(c, true, false, c->Bp / c->bt1));
+  ProfScope ps(c0, K_ASM);
+  HIPCHK(c0, launch_finish((const AssembleArgs*)(b->dev_mem + b->asm_args), AssembleArgs{}, (int)b->ctxs.size(),
+                           b->max_N, b->max_Np, b->st));
   return GLMR_OK;
 }
 
@@ -1860,7 +1888,8 @@ void glmr_batch_destroy(glmr_batch* b) {
   if (!b) return;
   hipSetDevice(b->dev);
   hipStreamSynchronize(b->st);
-  free_queues(b);
+  if (b->dev_mem) hipFree(b->dev_mem);
+  if (b->pinned) hipHostFree(b->pinned);
   if (b->hsum) hipHostFree(b->hsum);
   hipStreamDestroy(b->st);
   delete b;
