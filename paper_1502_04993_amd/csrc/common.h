@@ -435,12 +435,11 @@ hipError_t launch_finish(const AssembleArgs* list, const AssembleArgs& one, int 
 hipError_t launch_prepare_params(int prec, int j2, int N, int64_t Np, const double* J64, const double* mu,
                                  void* Jc, double* Jr, double* rowscale, float* jscale,
                                  hipStream_t st);
+// dense J, mu (any memory that the device reads) into the padded J64 and mu
+hipError_t launch_load_params(int N, int64_t Np, const double* J, const double* mu, double* J64, double* mu64,
+                              hipStream_t st);
 hipError_t launch_copy_out(const double* src, int64_t src_ld, double* dst, int rows, int cols,
                            hipStream_t st);
-hipError_t launch_fp8_xscale(const void* C32, int64_t NS, int64_t Np, int64_t chunk_sub,
-                             int64_t nchunks, const uint64_t* masks, int planes,
-                             const Tables* tab, float* xscale, hipStream_t st);
-hipError_t launch_fp8_wscale(const float* rowmax, int64_t Np, float* wscale, hipStream_t st);
 
 // Ascent (per-row L-BFGS, FP64) --------------------------------------------
 struct AscentArgs {

@@ -142,7 +142,15 @@ struct glmr_ctx {
   double* Jr = nullptr;
   double* rowscale = nullptr;
 
-  // evaluation workspace
+  // parameters and results without padding: a device buffer [N N + 3 N] and,
+  // for networks whose results fit, pinned host memory that kernels read and
+  // write in place
+  double* io = nullptr;
+  double* pin = nullptr;
+
+  // evaluation workspace, in slabs: those of the precision, and the others
+  std::vector<unsigned char*> slabs;
+  size_t w_bytes = 0, w_temps = 0;  // bytes of W; of them taken by temporaries
   void* W = nullptr;
   void* Gp = nullptr;
   int max_splits = 0;
@@ -154,11 +162,11 @@ struct glmr_ctx {
   double* gJ = nullptr;
   double* gmu = nullptr;
   double* tau_rows = nullptr;
-  double* scal = nullptr;  // [4] device scalars
-  double* host_scal = nullptr;
+  double* scal = nullptr;  // [4] pinned host memory that the kernels write: L, dL/dtau
 
   // ascent state
   AscentArgs asc{};
+  unsigned char* asc_mem = nullptr;
   bool have_asc = false;
   bool asc_live = false;  // asc holds an ascent of the current objective that a fit can resume
   bool asc_hist = false;  // asc holds L-BFGS pairs of this recording, kernel and delays (any precision)
@@ -245,9 +253,38 @@ struct Arena {
   size_t cap = 0, used = 0;
 };
 
+// Temporaries of a set-up outside the no-allocation entry point: W's memory
+// where the context has it (nothing is kept in W between evaluations, and the
+// stream orders the set-up after the one that last used it), else hipMalloc.
+// They nest: an inner set-up takes what the outer one has left.
+struct Temps {
+  glmr_ctx* c;
+  const size_t mark;
+  std::vector<void*> own;
+  explicit Temps(glmr_ctx* c_) : c(c_), mark(c_->w_temps) {}
+  Temps(const Temps&) = delete;
+  template <typename T>
+  glmr_status get(T*& p, size_t n) {
+    const size_t at = (c->w_temps + 255) & ~(size_t)255, bytes = std::max<size_t>(n, 1) * sizeof(T);
+    if (c->W && at + bytes <= c->w_bytes) {
+      p = (T*)((unsigned char*)c->W + at);
+      c->w_temps = at + bytes;
+      return GLMR_OK;
+    }
+    p = nullptr;
+    TRY(dalloc(c, p, n));
+    own.push_back(p);
+    return GLMR_OK;
+  }
+  ~Temps() {
+    for (void* q : own) dfree(c, q);
+    c->w_temps = mark;
+  }
+};
+
 template <typename T>
-glmr_status temp_alloc(glmr_ctx* c, Arena* ar, T*& p, size_t n) {
-  if (!ar) return dalloc(c, p, n);
+glmr_status temp_alloc(glmr_ctx* c, Arena* ar, Temps& tmp, T*& p, size_t n) {
+  if (!ar) return tmp.get(p, n);
   const size_t at = (ar->used + 255) & ~(size_t)255;
   const size_t bytes = std::max<size_t>(n, 1) * sizeof(T);
   if (at + bytes > ar->cap)
@@ -255,12 +292,6 @@ glmr_status temp_alloc(glmr_ctx* c, Arena* ar, T*& p, size_t n) {
   p = (T*)(ar->base + at);
   ar->used = at + bytes;
   return GLMR_OK;
-}
-
-template <typename T>
-void temp_free(glmr_ctx* c, Arena* ar, T*& p) {
-  if (ar) p = nullptr;
-  else dfree(c, p);
 }
 
 constexpr int kMaxDevices = 64;
@@ -408,9 +439,9 @@ glmr_status build_ev_tables(glmr_ctx* c, Arena* ar) {
   const int64_t n = c->NS * 64;
   TRY(persist(c, ar, c->evtab, (size_t)(5 * n + c->NS)));
   unsigned long long* ms = nullptr;
-  TRY(temp_alloc(c, ar, ms, 1));
-  if (ar) HIPCHK(c, launch_fill_i32((int32_t*)ms, 2, 0, c->st));  // the static scratch keeps old contents
-  else HIPCHK(c, hipMemsetAsync(ms, 0, sizeof(unsigned long long), c->st));
+  Temps tmp(c);
+  TRY(temp_alloc(c, ar, tmp, ms, 1));
+  HIPCHK(c, launch_fill_i32((int32_t*)ms, 2, 0, c->st));  // neither memory is clear
   EvTableArgs ta{};
   ta.tslot = c->tslot;
   ta.tau = c->tau;
@@ -432,7 +463,6 @@ glmr_status build_ev_tables(glmr_ctx* c, Arena* ar) {
   unsigned long long h = 0;
   HIPCHK(c, hipMemcpyAsync(&h, ms, sizeof h, hipMemcpyDeviceToHost, c->st));
   HIPCHK(c, hipStreamSynchronize(c->st));
-  temp_free(c, ar, ms);
   double span = 0;
   std::memcpy(&span, &h, sizeof span);
   c->max_span = span;
@@ -551,19 +581,14 @@ glmr_status build_lists(glmr_ctx* c, const uint64_t* masks, glmr_ctx::WinList* w
   a.NS = c->NS;
   a.Np = c->Np;
   int64_t* tmp = nullptr;
-  auto cleanup = [&]() {
-    dfree(c, a.wcnt);
-    dfree(c, a.woff);
-    dfree(c, a.scnt);
-    dfree(c, tmp);
-  };
+  Temps t(c);
   glmr_status st = GLMR_OK;
   do {
-    if ((st = dalloc(c, a.wcnt, (size_t)nw)) != GLMR_OK) break;
-    if ((st = dalloc(c, a.woff, (size_t)nw + 1)) != GLMR_OK) break;
-    if ((st = dalloc(c, tmp, (size_t)ingest_scan_tmp_len(std::max(nw, c->NS)))) != GLMR_OK) break;
+    if ((st = t.get(a.wcnt, (size_t)nw)) != GLMR_OK) break;
+    if ((st = t.get(a.woff, (size_t)nw + 1)) != GLMR_OK) break;
+    if ((st = t.get(tmp, (size_t)ingest_scan_tmp_len(std::max(nw, c->NS)))) != GLMR_OK) break;
     if (bins) {
-      if ((st = dalloc(c, a.scnt, (size_t)c->NS)) != GLMR_OK) break;
+      if ((st = t.get(a.scnt, (size_t)c->NS)) != GLMR_OK) break;
       if (!c->off1 && (st = dalloc(c, c->off1, (size_t)c->NS + 1)) != GLMR_OK) break;
       if ((st = dalloc(c, c->ent1, (size_t)c->nspk + 192)) != GLMR_OK) break;
       a.off1 = c->off1;
@@ -594,7 +619,6 @@ glmr_status build_lists(glmr_ctx* c, const uint64_t* masks, glmr_ctx::WinList* w
     wl->ok = true;
     if (bins) c->list1 = true;
   } while (false);
-  cleanup();
   return st;
 }
 
@@ -643,8 +667,9 @@ glmr_status build_kernel_caches(glmr_ctx* c, bool want_y, Arena* ar = nullptr) {
   const int64_t G = 64;
   const int64_t nseg = (c->NS + G - 1) / G;
   double *seg = nullptr, *segin = nullptr;
-  TRY(temp_alloc(c, ar, seg, (size_t)nseg * c->Np * 2));
-  TRY(temp_alloc(c, ar, segin, (size_t)nseg * c->Np * 2));
+  Temps tmp(c);
+  TRY(temp_alloc(c, ar, tmp, seg, (size_t)nseg * c->Np * 2));
+  TRY(temp_alloc(c, ar, tmp, segin, (size_t)nseg * c->Np * 2));
   CarryArgs ca{};
   ca.masks = c->masks;
   ca.planes = c->planes;
@@ -694,7 +719,7 @@ glmr_status build_kernel_caches(glmr_ctx* c, bool want_y, Arena* ar = nullptr) {
   double* part = nullptr;
   // the self-delay correction reuses it for 64 time splits of Np sums
   const size_t part_n = std::max<size_t>((size_t)splits * nij, self_delayed(c) ? 64 * (size_t)c->Np : 0);
-  TRY(temp_alloc(c, ar, part, part_n));
+  TRY(temp_alloc(c, ar, tmp, part, part_n));
   SpikeTermArgs sa{};
   sa.masks = c->masks;
   sa.planes = c->planes;
@@ -731,53 +756,153 @@ glmr_status build_kernel_caches(glmr_ctx* c, bool want_y, Arena* ar = nullptr) {
     HIPCHK(c, launch_self_spike(ss, c->st));
   }
   HIPCHK(c, hipStreamSynchronize(c->st));
-  temp_free(c, ar, part);
-  temp_free(c, ar, seg);
-  temp_free(c, ar, segin);
   c->have_kernel = true;
   c->have_y = want_y;
   return GLMR_OK;
 }
 
-glmr_status ensure_workspace(glmr_ctx* c, bool want_grad, bool want_tau) {
-  const int64_t Np = c->Np;
-  const size_t wb = in_bytes(c->prec);
-  if (!c->W) {
-    void* p = nullptr;
-    TRY(dalloc(c, (unsigned char*&)p, (size_t)Np * c->L * wb));
-    c->W = p;
+// One allocation for a list of buffers (those that exist already are left out).
+struct Slab {
+  std::vector<std::pair<void**, size_t>> items;
+  size_t bytes = 0;
+  template <typename T>
+  void want(T*& p, size_t n) {
+    if (p) return;
+    items.push_back({(void**)&p, bytes});
+    bytes = (bytes + std::max<size_t>(n, 1) * sizeof(T) + 255) & ~(size_t)255;
   }
+  glmr_status get(glmr_ctx* c, unsigned char** mem) {
+    *mem = nullptr;
+    if (items.empty()) return GLMR_OK;
+    TRY(dalloc(c, *mem, bytes));
+    for (auto& it : items) *it.first = *mem + it.second;
+    return GLMR_OK;
+  }
+};
+
+glmr_status ensure_workspace(glmr_ctx* c, bool want_grad, bool want_tau) {
+  const size_t Np = (size_t)c->Np;
   const int64_t seg = rec_seg(c), nseg = (c->B + seg - 1) / seg;
-  const int64_t ntiles_t = std::max(c->Bp / c->bt1, c->prec == PREC_F64 || c->prec == PREC_F32 ? nseg : 0);
+  const bool fp = c->prec == PREC_F64 || c->prec == PREC_F32;
+  const size_t tiles = (size_t)std::max(c->Bp / c->bt1, fp ? nseg : 0);
+  // buffers whose size or element type depend on the precision
+  Slab s;
+  const size_t wb = Np * (size_t)c->L * in_bytes(c->prec);
+  s.want((unsigned char*&)c->W, wb);
+  c->w_bytes = wb;
+  s.want(c->rowpart, tiles * Np);
+  if (want_tau) s.want(c->rowpartV, tiles * Np);
+  if (self_delayed(c)) s.want(c->gpart, tiles * Np);
+  if (want_grad) s.want((unsigned char*&)c->Gp, (size_t)c->max_splits * Np * Np * (fp ? 8 : 4));
+  if (use_rec(c) && want_grad) s.want(c->rec_head, (size_t)c->max_splits * Np);
+  unsigned char* mem = nullptr;
+  glmr_status st = s.get(c, &mem);
+  if (st != GLMR_OK) {
+    if (!c->W) c->w_bytes = 0;
+    return st;
+  }
+  if (mem) c->slabs.push_back(mem);
+  // the others
+  Slab o;
   if (use_rec(c)) {
     const size_t rows = (size_t)(c->NS / std::max<int64_t>(1, seg / 64) + 1);
-    if (!c->rec_Dc) TRY(dalloc(c, c->rec_Dc, rows * Np));
-    if (want_tau && !c->rec_Vc) TRY(dalloc(c, c->rec_Vc, rows * Np));
-    if (want_grad && !c->rec_head) TRY(dalloc(c, c->rec_head, (size_t)c->max_splits * Np));
+    o.want(c->rec_Dc, rows * Np);
+    if (want_tau) o.want(c->rec_Vc, rows * Np);
   }
-  if (!c->rowpart) TRY(dalloc(c, c->rowpart, (size_t)ntiles_t * Np));
-  if (want_tau && !c->rowpartV) TRY(dalloc(c, c->rowpartV, (size_t)ntiles_t * Np));
-  if (self_delayed(c) && !c->gpart) TRY(dalloc(c, c->gpart, (size_t)ntiles_t * Np));
-  if (!c->rp_tmp) TRY(dalloc(c, c->rp_tmp, (size_t)rowpart_tmp_len(Np)));
-  if (!c->ll_rows) TRY(dalloc(c, c->ll_rows, (size_t)Np));
-  if (!c->tau_rows) TRY(dalloc(c, c->tau_rows, (size_t)Np));
-  if (!c->scal) TRY(dalloc(c, c->scal, 4));
-  if (!c->host_scal) {
-    HIPCHK(c, hipHostMalloc((void**)&c->host_scal, 4 * sizeof(double), hipHostMallocDefault));
-  }
+  o.want(c->rp_tmp, (size_t)rowpart_tmp_len(c->Np));
+  o.want(c->ll_rows, Np);
+  o.want(c->tau_rows, Np);
   if (want_grad) {
-    if (!c->gmu) TRY(dalloc(c, c->gmu, (size_t)Np));
-    if (!c->gJ) TRY(dalloc(c, c->gJ, (size_t)Np * Np));
-    if (!c->G64) TRY(dalloc(c, c->G64, (size_t)Np * Np));
-    if (!c->Gp) {
-      const size_t gb = (c->prec == PREC_F64 || c->prec == PREC_F32) ? 8 : 4;
-      void* p = nullptr;
-      TRY(dalloc(c, (unsigned char*&)p, (size_t)c->max_splits * Np * Np * gb));
-      c->Gp = p;
-    }
+    o.want(c->gmu, Np);
+    o.want(c->gJ, Np * Np);
+    o.want(c->G64, Np * Np);
   }
+  TRY(o.get(c, &mem));
+  if (!c->scal) HIPCHK(c, hipHostMalloc((void**)&c->scal, 4 * sizeof(double), hipHostMallocDefault));
   return GLMR_OK;
 }
+
+// Drop the workspace that depends on the precision.
+void drop_workspace(glmr_ctx* c) {
+  for (unsigned char* p : c->slabs) dfree(c, p);
+  c->slabs.clear();
+  c->W = c->Gp = nullptr;
+  c->w_bytes = 0;
+  c->rowpart = c->rowpartV = c->gpart = c->rec_head = nullptr;
+}
+
+// ---------------------------------------------------------------- parameters and results
+constexpr size_t kPinned = 1 << 16;  // doubles that pass through pinned memory in place (N <= 254)
+
+// doubles: J (or its gradient), mu (or its gradient), the rows of L, and one row more
+size_t io_len(const glmr_ctx* c) { return (size_t)c->N * c->N + 3 * (size_t)c->N; }
+
+// Whether a kernel on the context's device can use the n doubles at p: device
+// memory of that device, aligned, and inside one allocation.  Anything else
+// passes through a copy.
+bool on_device(const glmr_ctx* c, const double* p, size_t n) {
+  hipPointerAttribute_t at{};
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if ((uintptr_t)p % alignof(double) || hipPointerGetAttributes(&at, p) != hipSuccess ||
+      at.type != hipMemoryTypeDevice || at.device != c->cfg.device ||
+      hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return (const char*)(p + n) <= (const char*)base + size;
+}
+
+// the buffer that dense arrays pass through: pinned for host arrays that fit
+glmr_status io_buffer(glmr_ctx* c, int32_t where, double** buf) {
+  if (where == GLMR_HOST && io_len(c) <= kPinned) {
+    if (!c->pin) HIPCHK(c, hipHostMalloc((void**)&c->pin, io_len(c) * sizeof(double), hipHostMallocDefault));
+    *buf = c->pin;
+    return GLMR_OK;
+  }
+  if (!c->io) TRY(dalloc(c, c->io, io_len(c)));
+  *buf = c->io;
+  return GLMR_OK;
+}
+
+// Where an evaluation's (or a read-back's) dense results go: the caller's own
+// device memory, or the io buffer and from there to the caller.
+struct Results {
+  glmr_ctx* c;
+  int32_t where;
+  double* buf = nullptr;
+  struct Copy {
+    double* dst;
+    const double* src;
+    size_t n;
+  };
+  std::vector<Copy> copies;
+  // the pointer for the kernels of the caller's array p of n doubles, at `at` of the buffer
+  glmr_status out(double* p, size_t at, size_t n, double** dev) {
+    *dev = nullptr;
+    if (!p) return GLMR_OK;
+    if (where == GLMR_DEVICE && on_device(c, p, n)) {
+      *dev = p;
+      return GLMR_OK;
+    }
+    if (!buf) TRY(io_buffer(c, where, &buf));
+    *dev = buf + at;
+    copies.push_back({p, *dev, n});
+    return GLMR_OK;
+  }
+  bool pinned() const { return buf && buf != c->io; }
+  // after the kernels: copies out of device memory, the stream, copies out of pinned memory
+  glmr_status finish() {
+    if (!pinned())
+      for (const Copy& k : copies)
+        HIPCHK(c, hipMemcpyAsync(k.dst, k.src, k.n * sizeof(double),
+                                 where == GLMR_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, c->st));
+    HIPCHK(c, hipStreamSynchronize(c->st));
+    if (pinned())
+      for (const Copy& k : copies) std::memcpy(k.dst, k.src, k.n * sizeof(double));
+    return GLMR_OK;
+  }
+};
 
 // split length (bins) of kernel G for a chunk of Lc bins: about 2048
 // workgroups over `tiles` output tiles, at most max_splits partials.  (For
@@ -898,12 +1023,15 @@ hipError_t launch_g_chunk(glmr_ctx* c, int k, int64_t t0, int64_t Lc, int* n_spl
   return launch_res_g(k, c->prec == PREC_FP8 ? 1 : 0, ga, c->st);
 }
 
-glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau, int64_t row_tiles);
+struct Outputs {  // dense results that the assembly writes besides the context's own (nullable)
+  double *rows = nullptr, *gJ = nullptr, *gmu = nullptr;
+};
+glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau, int64_t row_tiles, const Outputs& o);
 glmr_status prepare_params(glmr_ctx* c);
 
 // One evaluation by the recurrence: the whole recording at once for the
 // likelihood alone, in chunks of W's length with the gradient.
-glmr_status eval_rec(glmr_ctx* c, bool want_grad, bool want_tau) {
+glmr_status eval_rec(glmr_ctx* c, bool want_grad, bool want_tau, const Outputs& o) {
   const int64_t seg = rec_seg(c), kc = std::max<int64_t>(1, seg / 64);
   const int64_t nseg = (c->B + seg - 1) / seg;
   const EvSlots ev = ev_slots(c);
@@ -967,15 +1095,15 @@ glmr_status eval_rec(glmr_ctx* c, bool want_grad, bool want_tau) {
     ProfScope ps(c, K_G);
     HIPCHK(c, launch_rec_gather(c->prec, g, ci == 0, c->st));
   }
-  return eval_finish(c, want_grad, want_tau, nseg);
+  return eval_finish(c, want_grad, want_tau, nseg, o);
 }
 
-glmr_status eval_core(glmr_ctx* c, bool want_grad, bool want_tau) {
+glmr_status eval_core(glmr_ctx* c, bool want_grad, bool want_tau, const Outputs& o = {}) {
   TRY(ensure_workspace(c, want_grad, want_tau));
   const int64_t Np = c->Np;
   if (c->prec == PREC_F64 || c->prec == PREC_F32) {
     if (use_rec(c) != c->jc_rec) TRY(prepare_params(c));  // the weights were staged for the other path
-    if (c->jc_rec) return eval_rec(c, want_grad, want_tau);
+    if (c->jc_rec) return eval_rec(c, want_grad, want_tau, o);
   }
   for (int64_t t0 = 0, ci = 0; t0 < c->Bp; t0 += c->L, ++ci) {
     const int64_t Lc = std::min<int64_t>(c->L, c->Bp - t0);
@@ -1064,7 +1192,7 @@ glmr_status eval_core(glmr_ctx* c, bool want_grad, bool want_tau) {
       HIPCHK(c, launch_gp_reduce(c->prec, c->Gp, g2.n_splits, Np, c->G64, ci == 0, c->st));
     }
   }
-  return eval_finish(c, want_grad, want_tau, c->Bp / c->bt1);
+  return eval_finish(c, want_grad, want_tau, c->Bp / c->bt1, o);
 }
 
 // Arguments of the last kernels of an evaluation: row sums of the weights over
@@ -1094,9 +1222,13 @@ AssembleArgs make_assemble_args(glmr_ctx* c, bool want_grad, bool want_tau, int6
   return aa;
 }
 
-glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau, int64_t n_tiles) {
+glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau, int64_t n_tiles, const Outputs& o) {
   ProfScope ps(c, K_ASM);
-  HIPCHK(c, launch_finish(nullptr, make_assemble_args(c, want_grad, want_tau, n_tiles), 1, c->N, c->Np, c->st));
+  AssembleArgs aa = make_assemble_args(c, want_grad, want_tau, n_tiles);
+  aa.out_rows = o.rows;
+  aa.out_gJ = o.gJ;
+  aa.out_gmu = o.gmu;
+  HIPCHK(c, launch_finish(nullptr, aa, 1, c->N, c->Np, c->st));
   return GLMR_OK;
 }
 
@@ -1170,6 +1302,18 @@ glmr_status check_ready(glmr_ctx* c) {
   return GLMR_OK;
 }
 
+// Copies a padded matrix and a vector to the caller's arrays (nullable) and waits.
+glmr_status read_back(glmr_ctx* c, const double* M, const double* v, double* to_M, double* to_v, int32_t where) {
+  const size_t N = (size_t)c->N;
+  Results r{c, where};
+  double *dM = nullptr, *dv = nullptr;
+  TRY(r.out(to_M, 0, N * N, &dM));
+  TRY(r.out(to_v, N * N, N, &dv));
+  if (dM) HIPCHK(c, launch_copy_out(M, c->Np, dM, c->N, c->N, c->st));
+  if (dv) HIPCHK(c, launch_copy_out(v, c->Np, dv, 1, c->N, c->st));
+  return r.finish();
+}
+
 hipMemcpyKind kind_to(int where) { return where == GLMR_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice; }
 hipMemcpyKind kind_from(int where) { return where == GLMR_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice; }
 
@@ -1184,26 +1328,21 @@ glmr_status alloc_ascent(glmr_ctx* c, int m) {
   a.P = P;
   a.m = m;
   const size_t np = (size_t)N * P;
-  TRY(dalloc(c, a.theta, np));
-  TRY(dalloc(c, a.theta_try, np));
-  TRY(dalloc(c, a.g, np));
-  TRY(dalloc(c, a.g_try, np));
-  TRY(dalloc(c, a.d, np));
-  TRY(dalloc(c, a.S, np * m));
-  TRY(dalloc(c, a.Y, np * m));
-  TRY(dalloc(c, a.rho, (size_t)m * N));
-  TRY(dalloc(c, a.hist_len, (size_t)N));
-  TRY(dalloc(c, a.hist_head, (size_t)N));
-  TRY(dalloc(c, a.f, (size_t)N));
-  TRY(dalloc(c, a.f_try, (size_t)N));
-  TRY(dalloc(c, a.step, (size_t)N));
-  TRY(dalloc(c, a.gd, (size_t)N));
-  TRY(dalloc(c, a.state, (size_t)N));
-  TRY(dalloc(c, a.accepted, (size_t)N));
-  TRY(dalloc(c, a.eta, (size_t)N));
-  TRY(dalloc(c, a.bt, (size_t)N));
-  TRY(dalloc(c, a.gstep, (size_t)N));
-  TRY(dalloc(c, c->counters, 4));
+  c->have_asc = false;
+  dfree(c, c->asc_mem);
+  for (double** p : {&a.theta, &a.theta_try, &a.g, &a.g_try, &a.d, &a.S, &a.Y, &a.rho, &a.f, &a.f_try, &a.step, &a.gd,
+                     &a.eta, &a.gstep})
+    *p = nullptr;
+  for (int32_t** p : {&a.hist_len, &a.hist_head, &a.state, &a.accepted, &a.bt}) *p = nullptr;
+  Slab s;
+  for (double** p : {&a.theta, &a.theta_try, &a.g, &a.g_try, &a.d}) s.want(*p, np);
+  s.want(a.S, np * m);
+  s.want(a.Y, np * m);
+  s.want(a.rho, (size_t)m * N);
+  for (double** p : {&a.f, &a.f_try, &a.step, &a.gd, &a.eta, &a.gstep}) s.want(*p, (size_t)N);
+  for (int32_t** p : {&a.hist_len, &a.hist_head, &a.state, &a.accepted, &a.bt}) s.want(*p, (size_t)N);
+  TRY(s.get(c, &c->asc_mem));
+  if (!c->counters) TRY(dalloc(c, c->counters, 4));
   if (!c->host_cnt) HIPCHK(c, hipHostMalloc((void**)&c->host_cnt, 4 * sizeof(int32_t), hipHostMallocDefault));
   c->have_asc = true;
   return GLMR_OK;
@@ -1804,8 +1943,9 @@ glmr_status glmr_get_state(glmr_ctx* c, void* buf, size_t* len) {
   std::memcpy(o, &h, sizeof h);
   o += sizeof h;
   const size_t N = (size_t)c->N;
-  HIPCHK(c, hipMemcpy2DAsync(o, N * sizeof(double), c->J64, c->Np * sizeof(double), N * sizeof(double), N,
-                             hipMemcpyDeviceToHost, c->st));
+  if (!c->io) TRY(dalloc(c, c->io, io_len(c)));
+  HIPCHK(c, launch_copy_out(c->J64, c->Np, c->io, c->N, c->N, c->st));
+  HIPCHK(c, hipMemcpyAsync(o, c->io, N * N * sizeof(double), hipMemcpyDeviceToHost, c->st));
   o += N * N * sizeof(double);
   HIPCHK(c, hipMemcpyAsync(o, c->mu, N * sizeof(double), hipMemcpyDeviceToHost, c->st));
   o += N * sizeof(double);
@@ -1935,12 +2075,10 @@ glmr_status glmr_batch_eval(glmr_batch* b, double* ll) {
   OnBatchStream on(b);
   TRY(batch_prepare(b));
   TRY(batch_eval_core(b));
-  for (glmr_ctx* c : b->ctxs)
-    HIPCHK(c, hipMemcpyAsync(c->host_scal, c->scal, sizeof(double), hipMemcpyDeviceToHost, b->st));
   HIPCHK(b->ctxs[0], hipStreamSynchronize(b->st));
   for (size_t r = 0; r < b->ctxs.size(); ++r) {
-    if (ll) ll[r] = b->ctxs[r]->host_scal[0];
-    if (!std::isfinite(b->ctxs[r]->host_scal[0]))
+    if (ll) ll[r] = b->ctxs[r]->scal[0];
+    if (!std::isfinite(b->ctxs[r]->scal[0]))
       return fail(b->ctxs[r], GLMR_ENONFINITE, "log-likelihood is not finite");
   }
   return GLMR_OK;
@@ -1951,12 +2089,8 @@ glmr_status glmr_batch_get_grad(glmr_batch* b, int32_t r, double* grad_J, double
   glmr_ctx* c = b->ctxs[r];
   if (where != GLMR_HOST && where != GLMR_DEVICE) return fail(c, GLMR_EINVAL, "bad where");
   if (!c->gJ) return fail(c, GLMR_ESTATE, "no batch evaluation yet");
-  if (grad_mu) HIPCHK(c, hipMemcpyAsync(grad_mu, c->gmu, c->N * sizeof(double), kind_to(where), c->st));
-  if (grad_J)
-    HIPCHK(c, hipMemcpy2DAsync(grad_J, c->N * sizeof(double), c->gJ, c->Np * sizeof(double),
-                               c->N * sizeof(double), c->N, kind_to(where), c->st));
-  HIPCHK(c, hipStreamSynchronize(c->st));
-  return GLMR_OK;
+  HIPCHK(c, hipSetDevice(c->cfg.device));
+  return read_back(c, c->gJ, c->gmu, grad_J, grad_mu, where);
 }
 
 glmr_status glmr_batch_autotune(glmr_batch* b, const char* cache_path, int32_t* shape_u, int32_t* shape_g) {
@@ -2229,7 +2363,8 @@ void glmr_destroy(glmr_ctx* c) {
   hipSetDevice(c->cfg.device);
   hipStreamSynchronize(c->st);
   for (void* p : c->allocs) hipFree(p);
-  if (c->host_scal) hipHostFree(c->host_scal);
+  if (c->scal) hipHostFree(c->scal);
+  if (c->pin) hipHostFree(c->pin);
   if (c->host_cnt) hipHostFree(c->host_cnt);
   for (auto& r : c->pending) {
     hipEventDestroy(r.a);
@@ -2244,7 +2379,7 @@ namespace {
 
 // Spike ingest from device arrays of (bin, neuron) pairs (spike layout of the
 // regular grid, or the pseudo-bins of the event grid).
-glmr_status ingest_pairs(glmr_ctx* c, const int64_t* bin, const int32_t* neuron, int64_t n) {
+glmr_status ingest_pairs(glmr_ctx* c, Temps& tmp, const int64_t* bin, const int32_t* neuron, int64_t n) {
   ProfScope ps(c, K_INGEST);
   c->asc_live = false;
   c->asc_hist = false;
@@ -2260,11 +2395,11 @@ glmr_status ingest_pairs(glmr_ctx* c, const int64_t* bin, const int32_t* neuron,
   unsigned long long* bad = nullptr;
   int32_t *cnt = nullptr, *cursor = nullptr, *maxmult = nullptr;
   int64_t* scan_tmp = nullptr;
-  TRY(dalloc(c, bad, 2));
-  TRY(dalloc(c, cnt, (size_t)nseg + 1));
-  TRY(dalloc(c, cursor, (size_t)nseg + 1));
-  TRY(dalloc(c, maxmult, 1));
-  TRY(dalloc(c, scan_tmp, (size_t)ingest_scan_tmp_len(nseg)));
+  TRY(tmp.get(bad, 2));
+  TRY(tmp.get(cnt, (size_t)nseg + 1));
+  TRY(tmp.get(cursor, (size_t)nseg + 1));
+  TRY(tmp.get(maxmult, 1));
+  TRY(tmp.get(scan_tmp, (size_t)ingest_scan_tmp_len(nseg)));
   if (!c->seg_off) TRY(dalloc(c, c->seg_off, (size_t)nseg + 1));
   dfree(c, c->seg_ent);
   TRY(dalloc(c, c->seg_ent, (size_t)std::max<int64_t>(n, 1)));
@@ -2313,11 +2448,6 @@ glmr_status ingest_pairs(glmr_ctx* c, const int64_t* bin, const int32_t* neuron,
   HIPCHK(c, hipMemcpyAsync(c->q_host.data(), c->q, c->Np * sizeof(int64_t), hipMemcpyDeviceToHost, c->st));
   HIPCHK(c, hipStreamSynchronize(c->st));
   c->raster_digest = (uint64_t)dig[0] ^ ((uint64_t)dig[1] * 0x9E3779B97F4A7C15ull);
-  dfree(c, bad);
-  dfree(c, cnt);
-  dfree(c, cursor);
-  dfree(c, maxmult);
-  dfree(c, scan_tmp);
   c->nspk = n;
   c->have_spikes = true;
   drop_lists(c);
@@ -2341,20 +2471,19 @@ glmr_status glmr_set_spikes(glmr_ctx* c, const int64_t* bin, const int32_t* neur
   if (n > 0 && (!bin || !neuron)) return fail(c, GLMR_EINVAL, "null spike arrays");
   if (where != GLMR_HOST && where != GLMR_DEVICE) return fail(c, GLMR_EINVAL, "bad where");
   HIPCHK(c, hipSetDevice(c->cfg.device));
+  Temps tmp(c);
   int64_t* dbin = nullptr;
   int32_t* dneu = nullptr;
   if (where == GLMR_HOST && n > 0) {
-    TRY(dalloc(c, dbin, (size_t)n));
-    TRY(dalloc(c, dneu, (size_t)n));
+    TRY(tmp.get(dbin, (size_t)n));
+    TRY(tmp.get(dneu, (size_t)n));
     HIPCHK(c, hipMemcpyAsync(dbin, bin, n * sizeof(int64_t), hipMemcpyHostToDevice, c->st));
     HIPCHK(c, hipMemcpyAsync(dneu, neuron, n * sizeof(int32_t), hipMemcpyHostToDevice, c->st));
     bin = dbin;
     neuron = dneu;
   }
-  const glmr_status st = ingest_pairs(c, bin, neuron, n);
+  const glmr_status st = ingest_pairs(c, tmp, bin, neuron, n);
   HIPCHK(c, hipStreamSynchronize(c->st));
-  dfree(c, dbin);
-  dfree(c, dneu);
   return st;
 }
 
@@ -2373,11 +2502,12 @@ glmr_status glmr_set_spike_times(glmr_ctx* c, const double* times, const int32_t
   HIPCHK(c, hipSetDevice(c->cfg.device));
   c->have_spikes = false;
   c->have_kernel = false;
+  Temps tmp(c);
   double* dt_ = nullptr;
   int32_t* dn_ = nullptr;
   if (where == GLMR_HOST && n > 0) {
-    TRY(dalloc(c, dt_, (size_t)n));
-    TRY(dalloc(c, dn_, (size_t)n));
+    TRY(tmp.get(dt_, (size_t)n));
+    TRY(tmp.get(dn_, (size_t)n));
     HIPCHK(c, hipMemcpyAsync(dt_, times, n * sizeof(double), hipMemcpyHostToDevice, c->st));
     HIPCHK(c, hipMemcpyAsync(dn_, neuron, n * sizeof(int32_t), hipMemcpyHostToDevice, c->st));
     times = dt_;
@@ -2393,23 +2523,13 @@ glmr_status glmr_set_spike_times(glmr_ctx* c, const double* times, const int32_t
   a.max_gap = mg;
   a.NS = c->NS;
   const size_t nn = (size_t)std::max<int64_t>(n, 1);
-  auto cleanup = [&]() {
-    (void)hipStreamSynchronize(c->st);
-    dfree(c, dt_);
-    dfree(c, dn_);
-    dfree(c, a.bad);
-    dfree(c, a.cnt);
-    dfree(c, a.slot);
-    dfree(c, a.scan_tmp);
-    dfree(c, a.bins);
-  };
   glmr_status st = GLMR_OK;
   do {
-    if ((st = dalloc(c, a.bad, 2)) != GLMR_OK) break;
-    if ((st = dalloc(c, a.cnt, nn)) != GLMR_OK) break;
-    if ((st = dalloc(c, a.slot, nn)) != GLMR_OK) break;
-    if ((st = dalloc(c, a.scan_tmp, (size_t)ev_scan_tmp_len(n))) != GLMR_OK) break;
-    if ((st = dalloc(c, a.bins, nn)) != GLMR_OK) break;
+    if ((st = tmp.get(a.bad, 2)) != GLMR_OK) break;
+    if ((st = tmp.get(a.cnt, nn)) != GLMR_OK) break;
+    if ((st = tmp.get(a.slot, nn)) != GLMR_OK) break;
+    if ((st = tmp.get(a.scan_tmp, (size_t)ev_scan_tmp_len(n))) != GLMR_OK) break;
+    if ((st = tmp.get(a.bins, nn)) != GLMR_OK) break;
     unsigned long long hbad[2] = {0, 0};
     if (hipMemsetAsync(a.bad, 0, sizeof(unsigned long long), c->st) != hipSuccess ||
         hipMemsetAsync(a.bad + 1, 0xff, sizeof(unsigned long long), c->st) != hipSuccess ||
@@ -2450,9 +2570,9 @@ glmr_status glmr_set_spike_times(glmr_ctx* c, const double* times, const int32_t
     c->T0 = T0;
     c->T1 = T1;
     c->max_gap = mg;
-    st = ingest_pairs(c, a.bins, neuron, n);
+    st = ingest_pairs(c, tmp, a.bins, neuron, n);
   } while (false);
-  cleanup();
+  (void)hipStreamSynchronize(c->st);
   return st;
 }
 
@@ -2555,9 +2675,21 @@ glmr_status glmr_set_params(glmr_ctx* c, const double* J, const double* mu, int3
     TRY(dalloc(c, c->Jr, (size_t)Np * Np));
     TRY(dalloc(c, c->rowscale, (size_t)Np));
   }
-  HIPCHK(c, hipMemcpy2DAsync(c->J64, Np * sizeof(double), J, c->N * sizeof(double),
-                             c->N * sizeof(double), c->N, kind_from(where), c->st));
-  HIPCHK(c, hipMemcpyAsync(c->mu, mu, c->N * sizeof(double), kind_from(where), c->st));
+  const size_t N = (size_t)c->N;
+  if (where == GLMR_HOST || !on_device(c, J, N * N) || !on_device(c, mu, N)) {
+    double* buf = nullptr;
+    TRY(io_buffer(c, where, &buf));
+    if (buf == c->pin) {  // the calls that use it wait for the stream, so it is free
+      std::memcpy(buf, J, N * N * sizeof(double));
+      std::memcpy(buf + N * N, mu, N * sizeof(double));
+    } else {
+      HIPCHK(c, hipMemcpyAsync(buf, J, N * N * sizeof(double), kind_from(where), c->st));
+      HIPCHK(c, hipMemcpyAsync(buf + N * N, mu, N * sizeof(double), kind_from(where), c->st));
+    }
+    J = buf;
+    mu = buf + N * N;
+  }
+  HIPCHK(c, launch_load_params(c->N, Np, J, mu, c->J64, c->mu, c->st));
   TRY(prepare_params(c));
   if (where == GLMR_HOST) HIPCHK(c, hipStreamSynchronize(c->st));
   c->have_params = true;
@@ -2600,17 +2732,7 @@ glmr_status glmr_set_precision(glmr_ctx* c, int32_t precision) {
   c->j2 = j2;
   c->prec = prec;
   setup_precision(c);
-  // buffers whose size or element type depend on the precision
-  unsigned char* w = (unsigned char*)c->W;
-  dfree(c, w);
-  c->W = nullptr;
-  unsigned char* gp = (unsigned char*)c->Gp;
-  dfree(c, gp);
-  c->Gp = nullptr;
-  dfree(c, c->rowpart);
-  dfree(c, c->rowpartV);
-  dfree(c, c->gpart);
-  dfree(c, c->rec_head);
+  drop_workspace(c);
   if (c->Jc) {
     unsigned char* jc = (unsigned char*)c->Jc;
     dfree(c, jc);
@@ -2631,12 +2753,7 @@ glmr_status glmr_get_params(glmr_ctx* c, double* J, double* mu, double* tau, int
   if (tau) *tau = c->tau;
   if ((J || mu) && !c->have_params) return fail(c, GLMR_ESTATE, "no parameters set");
   HIPCHK(c, hipSetDevice(c->cfg.device));
-  if (J)
-    HIPCHK(c, hipMemcpy2DAsync(J, c->N * sizeof(double), c->J64, c->Np * sizeof(double),
-                               c->N * sizeof(double), c->N, kind_to(where), c->st));
-  if (mu) HIPCHK(c, hipMemcpyAsync(mu, c->mu, c->N * sizeof(double), kind_to(where), c->st));
-  HIPCHK(c, hipStreamSynchronize(c->st));
-  return GLMR_OK;
+  return read_back(c, c->J64, c->mu, J, mu, where);
 }
 
 glmr_status glmr_eval(glmr_ctx* c, double* ll, double* ll_rows, double* grad_J, double* grad_mu,
@@ -2659,18 +2776,17 @@ glmr_status glmr_eval(glmr_ctx* c, double* ll, double* ll_rows, double* grad_J, 
     c->keep_y = true;
     TRY(build_kernel_caches(c, true));
   }
-  TRY(eval_core(c, want_grad, want_tau));
-  if (ll_rows)
-    HIPCHK(c, hipMemcpyAsync(ll_rows, c->ll_rows, c->N * sizeof(double), kind_to(where), c->st));
-  if (grad_mu) HIPCHK(c, hipMemcpyAsync(grad_mu, c->gmu, c->N * sizeof(double), kind_to(where), c->st));
-  if (grad_J)
-    HIPCHK(c, hipMemcpy2DAsync(grad_J, c->N * sizeof(double), c->gJ, c->Np * sizeof(double),
-                               c->N * sizeof(double), c->N, kind_to(where), c->st));
-  HIPCHK(c, hipMemcpyAsync(c->host_scal, c->scal, 2 * sizeof(double), hipMemcpyDeviceToHost, c->st));
-  HIPCHK(c, hipStreamSynchronize(c->st));
-  if (ll) *ll = c->host_scal[0];
-  if (grad_tau) *grad_tau = c->host_scal[1];
-  if (!std::isfinite(c->host_scal[0])) return fail(c, GLMR_ENONFINITE, "log-likelihood is not finite");
+  const size_t N = (size_t)c->N;
+  Results r{c, where};
+  Outputs o;
+  TRY(r.out(grad_J, 0, N * N, &o.gJ));
+  TRY(r.out(grad_mu, N * N, N, &o.gmu));
+  TRY(r.out(ll_rows, N * N + N, N, &o.rows));
+  TRY(eval_core(c, want_grad, want_tau, o));
+  TRY(r.finish());
+  if (ll) *ll = c->scal[0];
+  if (grad_tau) *grad_tau = c->scal[1];
+  if (!std::isfinite(c->scal[0])) return fail(c, GLMR_ENONFINITE, "log-likelihood is not finite");
   return GLMR_OK;
 }
 
