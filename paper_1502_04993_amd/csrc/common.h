@@ -5,9 +5,6 @@
 //   Bp  = B rounded up to 256 bins;  NS = Bp / 64 subtiles of 64 bins
 //   masks[p][s][j]  uint64: bit b set if neuron j has more than p spikes in bin
 //                   64*s + b (p = 0..planes-1; planes = max spikes per bin)
-//   seg_off[s*NIB + ib], seg_ent[]: spikes of subtile s whose neuron lies in the
-//                   64-neuron block ib (NIB = Np/64); entry = i_local | (b << 6),
-//                   sorted, so a segment lists its spikes in bin order
 //   C[s][j]         trace x_j at bin 64*s (the carry into subtile s)
 //   CY[s][j]        d x_j / d tau at bin 64*s
 //   dsig[i][j]      sum_t s_i[t] x_j[t]     (Eq. (12), parameter-free)
@@ -81,15 +78,16 @@ struct IngestBufs {
   const int32_t* neu;
   int32_t N;
   int64_t B, NS, NIB;
-  unsigned long long* bad;    // [2]: count, first bad index (min)
+  unsigned long long* bad;    // [3]: count, first bad index (min), whether a cell holds several spikes
+  // with several spikes in a cell:
   int32_t* cnt;               // [NS*NIB + 1]
   int32_t* off;               // [NS*NIB + 1]
   int32_t* cursor;            // [NS*NIB]
   uint16_t* ent;              // [n]
-  int64_t* q;                 // [Np]
   int32_t* maxmult;           // [1]
   int64_t* scan_tmp;          // [>= nseg/1024 + 2]
 };
+hipError_t launch_ingest_place(const IngestBufs& b, uint64_t* masks, int64_t Np, hipStream_t st);
 hipError_t launch_ingest_count(const IngestBufs& b, hipStream_t st);
 hipError_t launch_ingest_scan(const IngestBufs& b, hipStream_t st);
 hipError_t launch_ingest_scatter(const IngestBufs& b, hipStream_t st);
@@ -98,8 +96,9 @@ hipError_t launch_ingest_masks(const IngestBufs& b, uint64_t* masks, int planes,
                                hipStream_t st);
 // exclusive scan of cnt[0 .. n) into off[0 .. n], off[n] the total; tmp of ingest_scan_tmp_len(n)
 hipError_t launch_scan_i32(const int32_t* cnt, int64_t n, int64_t* tmp, int32_t* off, hipStream_t st);
-hipError_t launch_digest_u64(const uint64_t* p, int64_t n_outer, int64_t inner, int64_t ld, int64_t cols,
-                             unsigned long long* out, hipStream_t st);
+hipError_t launch_digest_u64(const uint64_t* p, int64_t n, unsigned long long* out, hipStream_t st);
+hipError_t launch_digest_count(const uint64_t* masks, int planes, int64_t NS, int64_t Np, int N,
+                               unsigned long long* out, int64_t* q, hipStream_t st);
 
 // Event grid layout (events.hip) ---------------------------------------------
 struct EvLayoutArgs {
@@ -213,9 +212,6 @@ struct SelfDelayArgs {
 hipError_t launch_self_delay(const SelfDelayArgs& a, hipStream_t st);
 struct SelfSpikeArgs {
   DelayTrace x;
-  const int32_t* seg_off;
-  const uint16_t* seg_ent;
-  int64_t NIB;
   int splits;
   int64_t d, ds;
   double* part;              // [splits][Np]

@@ -172,8 +172,9 @@ __global__ __launch_bounds__(256) void k_self_delay_frag(SelfDelayArgs a) {
   }
 }
 
-// dSigma_ii += sum_{spikes of i at t} Delta_i[t]: one wave per (64-neuron
-// block, split of the subtiles), lane = neuron of the block; partials per split
+// dSigma_ii += sum_{spikes of i at t} Delta_i[t] over the recorded spikes: one
+// wave per (64-neuron block, split of the subtiles), lane = neuron of the
+// block; partials per split
 __global__ __launch_bounds__(64) void k_self_spike(SelfSpikeArgs a) {
   const int lane = threadIdx.x;
   const int64_t ib = blockIdx.x, split = blockIdx.y;
@@ -183,13 +184,12 @@ __global__ __launch_bounds__(64) void k_self_spike(SelfSpikeArgs a) {
   const int64_t i = ib * 64 + lane;
   double acc = 0.0;
   for (int64_t s = sb; s < se; ++s) {
-    const int64_t sg = s * a.NIB + ib;
-    const int32_t e0 = a.seg_off[sg], e1 = a.seg_off[sg + 1];
-    for (int32_t e = e0; e < e1; ++e) {
-      const int v = a.seg_ent[e];
-      if ((v & 63) != lane) continue;
-      const int64_t t = s * 64 + (v >> 6);
-      acc += trace_at(a.x, i, t - a.ds) - trace_at(a.x, i, t - a.d);
+    uint64_t w = a.x.masks[s * a.x.Np + i];
+    while (w) {
+      const int64_t t = s * 64 + __builtin_ctzll(w);
+      w &= w - 1;
+      const double delta = trace_at(a.x, i, t - a.ds) - trace_at(a.x, i, t - a.d);
+      for (int n = (int)spikes_at(a.x, i, t); n > 0; --n) acc += delta;
     }
   }
   a.part[split * a.x.Np + i] = acc;
@@ -238,7 +238,7 @@ hipError_t launch_self_delay(const SelfDelayArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_self_spike(const SelfSpikeArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_self_spike, dim3((unsigned)a.NIB, (unsigned)a.splits), dim3(64), 0, st, a);
+  hipLaunchKernelGGL(k_self_spike, dim3((unsigned)(a.x.Np / 64), (unsigned)a.splits), dim3(64), 0, st, a);
   hipLaunchKernelGGL(k_self_spike_sum, dim3((unsigned)((a.x.Np + 255) / 256)), dim3(256), 0, st, a);
   return hipGetLastError();
 }

@@ -73,8 +73,6 @@ struct glmr_ctx {
   bool have_spikes = false;
   int64_t nspk = 0;
   int planes = 1;
-  int32_t* seg_off = nullptr;
-  uint16_t* seg_ent = nullptr;
   uint64_t* masks = nullptr;
   int64_t* q = nullptr;
   std::vector<int64_t> q_host;
@@ -744,9 +742,6 @@ glmr_status build_kernel_caches(glmr_ctx* c, bool want_y, Arena* ar = nullptr) {
   if (self_delayed(c)) {
     SelfSpikeArgs ss{};
     ss.x = delay_trace(c);
-    ss.seg_off = c->seg_off;
-    ss.seg_ent = c->seg_ent;
-    ss.NIB = c->NIB;
     ss.splits = (int)std::max<int64_t>(1, std::min<int64_t>(64, c->NS));
     ss.d = c->dly;
     ss.ds = c->dly_s;
@@ -2377,13 +2372,39 @@ void glmr_destroy(glmr_ctx* c) {
 
 namespace {
 
+// The planes of a raster with several spikes in one cell, from the (valid) pairs.
+glmr_status ingest_planes(glmr_ctx* c, Temps& tmp, IngestBufs& b) {
+  const int64_t nseg = c->NS * c->NIB;
+  TRY(tmp.get(b.cnt, (size_t)nseg + 1));
+  TRY(tmp.get(b.off, (size_t)nseg + 1));
+  TRY(tmp.get(b.cursor, (size_t)nseg + 1));
+  TRY(tmp.get(b.ent, (size_t)b.n));
+  TRY(tmp.get(b.maxmult, 1));
+  TRY(tmp.get(b.scan_tmp, (size_t)ingest_scan_tmp_len(nseg)));
+  HIPCHK(c, hipMemsetAsync(b.cnt, 0, (nseg + 1) * sizeof(int32_t), c->st));
+  HIPCHK(c, hipMemsetAsync(b.cursor, 0, (nseg + 1) * sizeof(int32_t), c->st));
+  HIPCHK(c, hipMemsetAsync(b.maxmult, 0, sizeof(int32_t), c->st));
+  HIPCHK(c, launch_ingest_count(b, c->st));
+  HIPCHK(c, launch_ingest_scan(b, c->st));
+  HIPCHK(c, launch_ingest_scatter(b, c->st));
+  HIPCHK(c, launch_ingest_sort(b, c->st));
+  int32_t hmax = 0;
+  HIPCHK(c, hipMemcpyAsync(&hmax, b.maxmult, sizeof hmax, hipMemcpyDeviceToHost, c->st));
+  HIPCHK(c, hipStreamSynchronize(c->st));
+  c->planes = std::max(1, (int)hmax);
+  const size_t nm = (size_t)c->planes * c->NS * c->Np;
+  TRY(dalloc(c, c->masks, nm));
+  HIPCHK(c, hipMemsetAsync(c->masks, 0, nm * sizeof(uint64_t), c->st));
+  HIPCHK(c, launch_ingest_masks(b, c->masks, c->planes, c->Np, c->st));
+  return GLMR_OK;
+}
+
 // Spike ingest from device arrays of (bin, neuron) pairs (spike layout of the
 // regular grid, or the pseudo-bins of the event grid).
 glmr_status ingest_pairs(glmr_ctx* c, Temps& tmp, const int64_t* bin, const int32_t* neuron, int64_t n) {
   ProfScope ps(c, K_INGEST);
   c->asc_live = false;
   c->asc_hist = false;
-  const int64_t nseg = c->NS * c->NIB;
   IngestBufs b{};
   b.n = n;
   b.N = c->N;
@@ -2392,58 +2413,32 @@ glmr_status ingest_pairs(glmr_ctx* c, Temps& tmp, const int64_t* bin, const int3
   b.NIB = c->NIB;
   b.bin = bin;
   b.neu = neuron;
-  unsigned long long* bad = nullptr;
-  int32_t *cnt = nullptr, *cursor = nullptr, *maxmult = nullptr;
-  int64_t* scan_tmp = nullptr;
-  TRY(tmp.get(bad, 2));
-  TRY(tmp.get(cnt, (size_t)nseg + 1));
-  TRY(tmp.get(cursor, (size_t)nseg + 1));
-  TRY(tmp.get(maxmult, 1));
-  TRY(tmp.get(scan_tmp, (size_t)ingest_scan_tmp_len(nseg)));
-  if (!c->seg_off) TRY(dalloc(c, c->seg_off, (size_t)nseg + 1));
-  dfree(c, c->seg_ent);
-  TRY(dalloc(c, c->seg_ent, (size_t)std::max<int64_t>(n, 1)));
+  TRY(tmp.get(b.bad, 3));
   if (!c->q) TRY(dalloc(c, c->q, (size_t)c->Np));
-  HIPCHK(c, hipMemsetAsync(bad, 0, sizeof(unsigned long long), c->st));
-  HIPCHK(c, hipMemsetAsync(bad + 1, 0xff, sizeof(unsigned long long), c->st));
-  HIPCHK(c, hipMemsetAsync(cnt, 0, (nseg + 1) * sizeof(int32_t), c->st));
-  HIPCHK(c, hipMemsetAsync(cursor, 0, (nseg + 1) * sizeof(int32_t), c->st));
-  HIPCHK(c, hipMemsetAsync(maxmult, 0, sizeof(int32_t), c->st));
-  HIPCHK(c, hipMemsetAsync(c->q, 0, c->Np * sizeof(int64_t), c->st));
-  b.bad = bad;
-  b.cnt = cnt;
-  b.off = c->seg_off;
-  b.cursor = cursor;
-  b.ent = c->seg_ent;
-  b.q = c->q;
-  b.maxmult = maxmult;
-  b.scan_tmp = scan_tmp;
+  const size_t nm = (size_t)c->NS * c->Np;
   c->have_spikes = false;
   c->have_kernel = false;
-  unsigned long long hbad[2] = {0, 0};
-  if (n > 0) HIPCHK(c, launch_ingest_count(b, c->st));
-  HIPCHK(c, hipMemcpyAsync(hbad, bad, sizeof hbad, hipMemcpyDeviceToHost, c->st));
-  HIPCHK(c, hipStreamSynchronize(c->st));
-  if (hbad[0] > 0) return fail(c, GLMR_EINVAL, "%llu spikes out of range; first at index %llu", hbad[0], hbad[1]);
-  HIPCHK(c, launch_ingest_scan(b, c->st));
-  if (n > 0) HIPCHK(c, launch_ingest_scatter(b, c->st));
-  HIPCHK(c, launch_ingest_sort(b, c->st));
-  int32_t hmax = 0;
-  HIPCHK(c, hipMemcpyAsync(&hmax, maxmult, sizeof hmax, hipMemcpyDeviceToHost, c->st));
-  HIPCHK(c, hipStreamSynchronize(c->st));
-  c->planes = std::max(1, (int)hmax);
-  const size_t nm = (size_t)c->planes * c->NS * c->Np;
-  dfree(c, c->masks);
-  dfree(c, c->masks0);
-  TRY(dalloc(c, c->masks, nm));
+  if (c->planes != 1 || c->masks0 || !c->masks) {
+    dfree(c, c->masks);
+    dfree(c, c->masks0);
+    c->planes = 1;
+    TRY(dalloc(c, c->masks, nm));
+  }
+  unsigned long long h[3] = {0, ~0ull, 0};
+  HIPCHK(c, hipMemcpyAsync(b.bad, h, sizeof h, hipMemcpyHostToDevice, c->st));
   HIPCHK(c, hipMemsetAsync(c->masks, 0, nm * sizeof(uint64_t), c->st));
-  HIPCHK(c, launch_ingest_masks(b, c->masks, c->planes, c->Np, c->st));
-  // digest of the recorded raster (before any delay shifts it), for checkpoints
-  HIPCHK(c, hipMemsetAsync(bad, 0, 2 * sizeof(unsigned long long), c->st));
-  HIPCHK(c, launch_digest_u64(c->masks, (int64_t)c->planes * c->NS, c->NS, c->Np, c->N, bad, c->st));
-  if (c->evm) HIPCHK(c, launch_digest_u64((const uint64_t*)c->tslot, 1, 1, 0, c->B + 1, bad + 1, c->st));
+  if (n > 0) HIPCHK(c, launch_ingest_place(b, c->masks, c->Np, c->st));
+  HIPCHK(c, hipMemcpyAsync(h, b.bad, sizeof h, hipMemcpyDeviceToHost, c->st));
+  HIPCHK(c, hipStreamSynchronize(c->st));
+  if (h[0] > 0) return fail(c, GLMR_EINVAL, "%llu spikes out of range; first at index %llu", h[0], h[1]);
+  if (h[2]) TRY(ingest_planes(c, tmp, b));
+  // counts, and a digest of the recorded raster (before any delay shifts it), for checkpoints
+  HIPCHK(c, hipMemsetAsync(b.bad, 0, 2 * sizeof(unsigned long long), c->st));
+  HIPCHK(c, hipMemsetAsync(c->q, 0, c->Np * sizeof(int64_t), c->st));
+  HIPCHK(c, launch_digest_count(c->masks, c->planes, c->NS, c->Np, c->N, b.bad, c->q, c->st));
+  if (c->evm) HIPCHK(c, launch_digest_u64((const uint64_t*)c->tslot, c->B + 1, b.bad + 1, c->st));
   unsigned long long dig[2] = {0, 0};
-  HIPCHK(c, hipMemcpyAsync(dig, bad, sizeof dig, hipMemcpyDeviceToHost, c->st));
+  HIPCHK(c, hipMemcpyAsync(dig, b.bad, sizeof dig, hipMemcpyDeviceToHost, c->st));
   c->q_host.assign(c->Np, 0);
   HIPCHK(c, hipMemcpyAsync(c->q_host.data(), c->q, c->Np * sizeof(int64_t), hipMemcpyDeviceToHost, c->st));
   HIPCHK(c, hipStreamSynchronize(c->st));
