@@ -690,7 +690,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_res_g_group(ResGGroup q) {
 // reads, exchanging half-fragments between the two half-waves
 // (v_permlane32_swap) so that each lane stores 8 consecutive bins.
 constexpr int FB = 128;                    // neurons per tile of the LDS-staged operand
-constexpr int FLDS = 2 * FB * ROWB;        // its double buffer (bytes)
+constexpr int FLDS = 3 * FB * ROWB;        // its three buffers (bytes), rows padded
+constexpr int GLDS = 3 * FB * 128;         // the same as fragments: three workgroups fit where registers allow
 
 // Buffer resource over [base, base + bytes) for raw buffer loads: the wave-
 // uniform base sits in scalar registers, a lane's offset in one 32-bit
@@ -714,57 +715,86 @@ __device__ __forceinline__ f32x16 mma_bf16(const i32x4& a, const i32x4& b, const
 }
 
 // acc[a][b] += sum over the k steps [0, nk) of Afrag(a, step) Bs(b, step)^T:
-// A fragments come from ga(step, regs) into registers a step ahead; B (128 rows
-// by 64 k per step) from gb(step, regs) through LDS.  BFRAG: B's 16 KB of a
-// step are its 4 x 4 fragments in order (row block, k block), else 128 rows of
-// 128 bytes.  Acc element r of lane l of block (a, b) is row 32 a + 8 (r / 4)
-// + 4 (l / 32) + r % 4 of the wave's rows, column 32 b + l % 32 of the 128
-// columns.
+// A fragments come from ga(step, kc, regs) into registers, B (128 rows by 64 k
+// per step) from gb(step, regs) through LDS.  Everything is on its way well
+// before its use, and the schedule is pinned because the compiler's own moves
+// loads down to their first use:
+//   A    a k block's registers take the fragments of DEPTH steps ahead as soon
+//        as its MFMAs are issued (one to two steps of 1024 MFMA cycles to
+//        arrive; no copies; ga reads nothing past the last step);
+//   B    from memory into registers a step before it is written to LDS, into
+//        the third buffer after the one in use, so that the step's only
+//        barrier lies in the middle of the step and the next step's first
+//        fragments are read before this one ends;
+//   B's  fragment b of a k block is replaced by the next block's as soon as
+//        its MFMAs are issued.
+// BFRAG: B's 16 KB of a step are its 4 x 4 fragments in order (row block, k
+// block), else 128 rows of 128 bytes.  Acc element r of lane l of block (a, b)
+// is row 32 a + 8 (r / 4) + 4 (l / 32) + r % 4 of the wave's rows, column 32 b
+// + l % 32 of the 128 columns.
 template <int MB, bool BFRAG, typename GA, typename GB, int NT = 256>
 __device__ __forceinline__ void frag_loop(int nk, GA ga, GB gb, unsigned char* smem, f32x16 (&acc)[MB][4]) {
-  constexpr int PQ = 1024 / NT;  // 16-byte pieces of B per thread and step
+  constexpr int PQ = 1024 / NT;            // 16-byte pieces of B per thread and step
+  constexpr int DEPTH = MB > 2 ? 1 : 2;    // two register sets of A where they fit
   const int tid = threadIdx.x, lane = tid & 63;
   const int l32 = lane & 31, hi = lane >> 5;
-  i32x4 an[MB][4], bn[PQ];
+  i32x4 an[DEPTH][4][MB], bn[PQ], bv[4];
+  unsigned char* const wr = smem + (BFRAG ? tid * 16 : (tid >> 3) * ROWB + (tid & 7) * 16);
+  const unsigned char* const rd = smem + (BFRAG ? lane * 16 : l32 * ROWB + hi * 16);
   auto sb = [&](int buf) {
 #pragma unroll
-    for (int q = 0; q < PQ; ++q) {
-      const int p = tid + NT * q, r = p >> 3, c = p & 7;
-      *(i32x4*)(smem + buf * (FB * ROWB) + (BFRAG ? p * 16 : r * ROWB + c * 16)) = bn[q];
-    }
+    for (int q = 0; q < PQ; ++q) *(i32x4*)(wr + buf + q * (BFRAG ? NT * 16 : NT / 8 * ROWB)) = bn[q];
+  };
+  auto rb = [&](int buf, int b, int kc) {
+    bv[b] = *(const i32x4*)(rd + buf + (BFRAG ? (b * 4 + kc) * 1024 : b * 32 * ROWB + kc * 32));
   };
   if (nk <= 0) return;
-  ga(0, an);
-  gb(0, bn);
-  sb(0);
+  if (DEPTH == 1) nk += nk & 1;  // one step of zeros: no register is free for a second copy of the loop
+  {
+    i32x4 b1[PQ];
+    gb(0, bn);
+    gb(1, b1);  // unused, and maybe of the next row, when nk is 1
+#pragma unroll
+    for (int c = 0; c < DEPTH; ++c)
+#pragma unroll
+      for (int kc = 0; kc < 4; ++kc) ga(c, kc, an[c][kc]);
+    sb(0);
+#pragma unroll
+    for (int q = 0; q < PQ; ++q) bn[q] = b1[q];
+  }
   __syncthreads();
-  for (int ks = 0; ks < nk; ++ks) {
-    const int cur = ks & 1;
-    const bool more = ks + 1 < nk;
-    i32x4 ac[MB][4];
 #pragma unroll
-    for (int a = 0; a < MB; ++a)
-#pragma unroll
-      for (int kc = 0; kc < 4; ++kc) ac[a][kc] = an[a][kc];
-    if (more) {
-      gb(ks + 1, bn);
-      ga(ks + 1, an);
-    }
-    const unsigned char* Bs = smem + cur * (FB * ROWB) + (BFRAG ? lane * 16 : l32 * ROWB + hi * 16);
+  for (int b = 0; b < 4; ++b) rb(0, b, 0);
+  constexpr int FBUF = BFRAG ? FB * 128 : FB * ROWB;
+  int cur = 0, nxt = FBUF;  // LDS buffers of this step and the next
+  auto step = [&](int ks, i32x4 (&as)[4][MB]) {
 #pragma unroll
     for (int kc = 0; kc < 4; ++kc) {
-      i32x4 bv[4];
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
-        bv[b] = *(const i32x4*)(Bs + (BFRAG ? (b * 4 + kc) * 1024 : b * 32 * ROWB + kc * 32));
+      for (int b = 0; b < 4; ++b) {
 #pragma unroll
-      for (int a = 0; a < MB; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = mma_bf16(ac[a][kc], bv[b], acc[a][b]);
+        for (int a = 0; a < MB; ++a) acc[a][b] = mma_bf16(as[kc][a], bv[b], acc[a][b]);
+        rb(kc < 3 ? cur : nxt, b, (kc + 1) & 3);
+        if (b == 3) ga(ks + DEPTH, kc, as[kc]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (kc == 0 && b == 1 && ks + 1 < nk) {
+          sb(nxt);
+          if (ks + 2 < nk) gb(ks + 2, bn);
+        }
+        if (kc == 1 && b == 3) __syncthreads();
+      }
     }
-    if (more) sb(cur ^ 1);
-    __syncthreads();
+    cur = nxt;
+    nxt = nxt == 2 * FBUF ? 0 : nxt + FBUF;
+  };
+  int ks = 0;
+#pragma unroll 1
+  for (; ks + 1 < nk; ks += 2) {
+    step(ks, an[0]);
+    step(ks + 1, an[DEPTH - 1]);
   }
+  if (DEPTH == 2 && ks < nk) step(ks, an[0]);
+  __syncthreads();  // the caller may use the buffers
 }
 
 // Kernel U: tile 256 bins x 128 neurons, 4 waves of 64 bins x 128 neurons.
@@ -788,14 +818,11 @@ __device__ __forceinline__ void res_uf_tile(const ResUArgs& g, int64_t itile, in
   for (int a = 0; a < MB; ++a)
     xr[a] = buf_rsrc((const unsigned char*)g.Xtj + ((tt0 + 64 * wave) / 32 + a) * kbn * 1024, (int)(kbn * 1024));
   const __amdgpu_buffer_rsrc_t jr = buf_rsrc((const unsigned char*)g.Jc + i0 * ldj, (int)(FB * ldj));
-  auto ga = [&](int ks, i32x4 (&an)[MB][4]) {
-    int kb = ks * 4;
-    if (kb >= kbn) kb -= (int)kbn;  // the two-term J's second half meets the same trace
+  const int wrap = g.j2 ? (int)(kbn / 4) : 0x7fffffff;   // the two-term J's second half meets the same trace
+  auto ga = [&](int ks, int kc, i32x4 (&an)[MB]) {
+    const int kb = (ks >= wrap ? ks - wrap : ks) * 4096;
 #pragma unroll
-    for (int a = 0; a < MB; ++a)
-#pragma unroll
-      for (int kc = 0; kc < 4; ++kc)
-        an[a][kc] = __builtin_amdgcn_raw_buffer_load_b128(xr[a], lane * 16 + kc * 1024, kb * 1024, 0);
+    for (int a = 0; a < MB; ++a) an[a] = __builtin_amdgcn_raw_buffer_load_b128(xr[a], lane * 16 + kc * 1024, kb, 0);
   };
   auto gb = [&](int ks, i32x4 (&bn)[4]) {
 #pragma unroll
@@ -901,6 +928,16 @@ __device__ __forceinline__ void res_uf_tile(const ResUArgs& g, int64_t itile, in
       if (hi == 0) red[wave * FB + b * 32 + l32] = v;
     }
   } else {
+    if (tt0 + GLMR_TT > g.B) {  // the last tile: potentials whose exp is 0 past the last bin
+      const int64_t past = g.B - tt0 - 64 * wave - 4 * hi;
+#pragma unroll
+      for (int a = 0; a < MB; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (32 * a + 8 * (r >> 2) + (r & 3) >= past) acc[a][b][r] = -INFINITY;
+    }
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
       float cs = 0.f;
@@ -909,12 +946,10 @@ __device__ __forceinline__ void res_uf_tile(const ResUArgs& g, int64_t itile, in
         uint32_t pk[8];  // bins 8 q + 4 hi + {0, 1} and {2, 3} for q = 0 .. 3
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int64_t t = tt0 + 64 * wave + 32 * a + 8 * q + 4 * hi;
           float lam[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             lam[e] = __expf(acc[a][b][4 * q + e]);
-            if (t + e >= g.B) lam[e] = 0.f;
             cs += lam[e];
           }
           bf16x2 p0 = {(__bf16)lam[0], (__bf16)lam[1]}, p1 = {(__bf16)lam[2], (__bf16)lam[3]};
@@ -1011,11 +1046,9 @@ __device__ __forceinline__ void res_gf_tile(const ResGArgs& g, int64_t logical, 
   // piece p = tid + NT q of a step's 16 KB: row block p / 256 (uniform over a
   // wave), k block p / 64 % 4, lane p % 64
   const int va = lane * 16, vb = (wave & 3) * 1024 + lane * 16;
-  auto ga = [&](int ks, i32x4 (&an)[MB][4]) {
+  auto ga = [&](int ks, int kc, i32x4 (&an)[MB]) {
 #pragma unroll
-    for (int a = 0; a < MB; ++a)
-#pragma unroll
-      for (int kc = 0; kc < 4; ++kc) an[a][kc] = __builtin_amdgcn_raw_buffer_load_b128(wr[a], va + kc * 1024, ks * 4096, 0);
+    for (int a = 0; a < MB; ++a) an[a] = __builtin_amdgcn_raw_buffer_load_b128(wr[a], va + kc * 1024, ks * 4096, 0);
   };
   auto gb = [&](int ks, i32x4 (&bn)[PQ]) {
 #pragma unroll
@@ -1042,14 +1075,14 @@ __device__ __forceinline__ void res_gf_tile(const ResGArgs& g, int64_t logical, 
 template <int MB, int NW = 4>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(MB == 4 || NW == 8 ? 1 : 2))) void k_res_gf(
     ResGArgs g) {
-  __shared__ __align__(16) unsigned char smem[FLDS];
+  __shared__ __align__(16) unsigned char smem[GLDS];
   res_gf_tile<MB, NW>(g, xcd_logical(blockIdx.x, gridDim.x), smem);
 }
 
 template <int MB, int NW = 4>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(MB == 4 || NW == 8 ? 1 : 2))) void
 k_res_gf_group(ResGGroup q) {
-  __shared__ __align__(16) unsigned char smem[FLDS];
+  __shared__ __align__(16) unsigned char smem[GLDS];
   ResGArgs g;
   int64_t local;
   if (!striped_tile(q, g, local)) return;
