@@ -305,9 +305,14 @@ struct RecGArgs {
   double* G64;
   int64_t NS64;            // slots of the tables (event grid)
 };
-hipError_t launch_rec_gather(int prec, const RecGArgs& a, int first, hipStream_t st);
-hipError_t launch_prepare_t(int prec, int N, int64_t Np, const double* J64, const double* mu, void* Jt, double* Jr,
-                            double* rowscale, hipStream_t st);
+hipError_t launch_rec_gather(int prec, const RecGArgs& a, hipStream_t st);
+hipError_t launch_rec_reduce(const RecGArgs& a, int first, hipStream_t st);
+struct AssembleArgs;
+// the last chunk's reduction (grad), row sums, rows and gradient
+hipError_t launch_rec_finish(const RecGArgs& a, const AssembleArgs& s, int first, int grad, hipStream_t st);
+// J (row pitch ld) and mu to the staged weights; to J64 and mu64 too unless null
+hipError_t launch_prepare_t(int prec, int N, int64_t Np, const double* J, int64_t ld, const double* mu, void* Jt,
+                            double* Jr, double* rowscale, double* J64, double* mu64, hipStream_t st);
 
 // Resident trace (BF16): x built once per tau in two layouts -----------------
 struct ResXArgs {
@@ -420,10 +425,10 @@ struct AssembleArgs {
   double* gJ;             // [Np][Np] or null
   double* gmu;            // [Np] or null
   double* tau_rows;       // [Np] or null
-  double* scal;           // [2] L, dL/dtau
+  double* host_rows;      // nullable: [2][N] pinned copies of ll_rows and tau_rows, which the host adds up
   double *out_rows, *out_gJ, *out_gmu;  // nullable: the same, N and N x N without padding
 };
-// row sums, rows and gradient, totals (list as above)
+// row sums, rows and gradient (list as above)
 hipError_t launch_finish(const AssembleArgs* list, const AssembleArgs& one, int n_rec, int max_N, int64_t max_Np,
                          hipStream_t st);
 

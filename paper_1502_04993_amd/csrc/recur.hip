@@ -182,6 +182,89 @@ __global__ __launch_bounds__(256) void k_rec_reduce(RecGArgs a, int first) {
   *g = (first ? 0.0 : *g) + t[threadIdx.x & 7][threadIdx.x >> 3];
 }
 
+// The end of an evaluation in one launch, workgroups of two kinds.  The first
+// Np / 32 take 32 rows each: the sums of kernel U's partials over the
+// segments, L_i, dL/dmu_i and dL/dtau_i.  The others (with the gradient) take
+// a 32 x 32 tile of the last chunk's reduction (k_rec_reduce) and write dL/dJ:
+// it needs no row sum.  All are short and bound by latency (16 loads in flight
+// a thread); reduction, row sums, assembly and totals as four kernels and
+// their gaps took 25 us more of the 0.26 ms of an evaluation at N = 150 on the
+// event grid, 50 of 1250 us of a gradient step at N = 500.
+__global__ __launch_bounds__(1024) void k_rec_finish(RecGArgs a, AssembleArgs s, int first) {
+  __shared__ double t[32][33];
+  const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
+  const int64_t nb = s.Np / 32;
+  if (blockIdx.x >= nb) {
+    const int64_t k = blockIdx.x - nb, i0 = k % nb * 32, j0 = k / nb * 32, i = i0 + tx, j = j0 + ty;
+    const int64_t cstep = a.wps * (GW / 64) * a.Np, gstep = a.Np * a.Np;
+    const double* __restrict__ gp = (const double*)a.Gp + j * a.Np + i;
+    const double* __restrict__ C = a.C64 + (a.t0 >> 6) * a.Np + j;
+    const double* __restrict__ hd = a.head + i;
+    double v = 0.0;
+    if (i < a.N) {
+#pragma unroll 8
+      for (int p = 0; p < a.n_splits; ++p) v += gp[p * gstep] + hd[p * a.Np] * C[p * cstep];
+    }
+    t[ty][tx] = v;
+    __syncthreads();
+    const int64_t r = i0 + ty, c = j0 + tx;
+    if (r >= s.N) return;
+    const double G = (first ? 0.0 : a.G64[r * s.Np + c]) + t[tx][ty];
+    const double g = c < s.N ? s.dsig[r * s.Np + c] - s.dt * s.rowscale[r] * G : 0.0;
+    s.gJ[r * s.Np + c] = g;
+    if (s.out_gJ && c < s.N) s.out_gJ[r * s.N + c] = g;
+    return;
+  }
+  __shared__ double sums[2][32];
+  const int64_t i0 = (int64_t)blockIdx.x * 32;
+  for (int which = 0; which < 2; ++which) {
+    const double* __restrict__ rp = which ? s.rowpartV : s.rowpart;
+    double v = 0.0;
+    if (rp) {
+#pragma unroll 16
+      for (int64_t k = ty; k < s.n_tiles; k += 32) v += rp[k * s.Np + i0 + tx];
+    }
+    t[ty][tx] = v;
+    __syncthreads();
+    if (ty == 0) {
+      double w = 0.0;
+      for (int k = 0; k < 32; ++k) w += t[k][tx];
+      sums[which][tx] = w;
+    }
+    __syncthreads();
+  }
+  const int lane = tid & 63, wave = tid >> 6;
+  for (int k = 0; k < 2; ++k) {
+    const int il = 2 * wave + k;
+    const int64_t i = i0 + il;
+    if (i >= s.N) return;
+    const double *Jr = s.Jr + i * s.Np, *ds = s.dsig + i * s.Np;
+    double v = 0.0, vy = 0.0;
+    for (int64_t j = lane; j < s.N; j += 64) {
+      v += Jr[j] * ds[j];
+      if (s.dsigY) vy += Jr[j] * s.dsigY[i * s.Np + j];
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      v += __shfl_xor(v, o, 64);
+      vy += __shfl_xor(vy, o, 64);
+    }
+    if (lane) continue;
+    const double sc = s.dt * s.rowscale[i], integ = sc * sums[0][il];
+    const double ll = (double)s.q[i] * s.mu[i] + v - integ, gm = (double)s.q[i] - integ;
+    s.ll_rows[i] = ll;
+    if (s.host_rows) s.host_rows[i] = ll;
+    if (s.out_rows) s.out_rows[i] = ll;
+    if (s.gmu) s.gmu[i] = gm;
+    if (s.out_gmu) s.out_gmu[i] = gm;
+    if (s.tau_rows) {
+      const double tr = vy - sc * sums[1][il];
+      s.tau_rows[i] = tr;
+      if (s.host_rows) s.host_rows[s.N + i] = tr;
+    }
+  }
+}
+
 // ------------------------------------------------------------------ forward
 constexpr uint32_t ENT_FIRST = 0x80000000u;
 __device__ __forceinline__ int ent_bin(uint32_t e, uint32_t base) { return (int)(((e >> 16) - base) & 0x7fffu); }
@@ -577,18 +660,24 @@ __global__ __launch_bounds__(256) void k_carry_gemm(const double* __restrict__ C
 
 // J^T in the mode's type, the weights as used, e^mu
 template <typename JT>
-__global__ __launch_bounds__(256) void k_prepare_t(int N, int64_t Np, const double* J64, const double* mu, JT* Jt,
-                                                   double* Jr, double* rowscale) {
+__global__ __launch_bounds__(256) void k_prepare_t(int N, int64_t Np, const double* J, int64_t ld, const double* mu,
+                                                   JT* Jt, double* Jr, double* rowscale, double* J64, double* mu64) {
   __shared__ JT t[32][33];
   const int64_t i0 = (int64_t)blockIdx.x * 32, j0 = (int64_t)blockIdx.y * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int64_t i = i0 + ty + 8 * q, j = j0 + tx;
-    const JT v = (JT)((i < N && j < N) ? J64[i * Np + j] : 0.0);
+    const double x = (i < N && j < N) ? J[i * ld + j] : 0.0;
+    const JT v = (JT)x;
+    if (J64 && i < N && j < N) J64[i * Np + j] = x;
     Jr[i * Np + j] = (double)v;
     t[ty + 8 * q][tx] = v;
-    if (j == 0) rowscale[i] = (i < N) ? exp(mu[i]) : 0.0;
+    if (j == 0) {
+      const double m = i < N ? mu[i] : 0.0;
+      rowscale[i] = (i < N) ? exp(m) : 0.0;
+      if (J64 && i < N) mu64[i] = m;
+    }
   }
   __syncthreads();
 #pragma unroll
@@ -655,21 +744,30 @@ hipError_t launch_rec_forward(int prec, const RecFArgs& a, hipStream_t st) {
   return prec == PREC_F64 ? rec_forward<double>(a, st) : rec_forward<float>(a, st);
 }
 
-hipError_t launch_rec_gather(int prec, const RecGArgs& a, int first, hipStream_t st) {
-  hipError_t e;
-  if (prec == PREC_F64) e = a.ev.edec ? rec_gather<double, true>(a, st) : rec_gather<double, false>(a, st);
-  else e = a.ev.edec ? rec_gather<float, true>(a, st) : rec_gather<float, false>(a, st);
-  if (e != hipSuccess) return e;
+hipError_t launch_rec_gather(int prec, const RecGArgs& a, hipStream_t st) {
+  if (prec == PREC_F64) return a.ev.edec ? rec_gather<double, true>(a, st) : rec_gather<double, false>(a, st);
+  return a.ev.edec ? rec_gather<float, true>(a, st) : rec_gather<float, false>(a, st);
+}
+
+hipError_t launch_rec_reduce(const RecGArgs& a, int first, hipStream_t st) {
   hipLaunchKernelGGL(k_rec_reduce, dim3((unsigned)(a.Np / 32), (unsigned)(a.Np / 8)), dim3(256), 0, st, a, first);
   return hipGetLastError();
 }
 
-hipError_t launch_prepare_t(int prec, int N, int64_t Np, const double* J64, const double* mu, void* Jt, double* Jr,
-                            double* rowscale, hipStream_t st) {
+hipError_t launch_rec_finish(const RecGArgs& a, const AssembleArgs& s, int first, int grad, hipStream_t st) {
+  const int64_t nb = s.Np / 32;
+  hipLaunchKernelGGL(k_rec_finish, dim3((unsigned)(nb + (grad ? nb * nb : 0))), dim3(1024), 0, st, a, s, first);
+  return hipGetLastError();
+}
+
+hipError_t launch_prepare_t(int prec, int N, int64_t Np, const double* J, int64_t ld, const double* mu, void* Jt,
+                            double* Jr, double* rowscale, double* J64, double* mu64, hipStream_t st) {
   const unsigned nb = (unsigned)(Np / 32);
   if (prec == PREC_F64)
-    hipLaunchKernelGGL(k_prepare_t<double>, dim3(nb, nb), dim3(256), 0, st, N, Np, J64, mu, (double*)Jt, Jr, rowscale);
+    hipLaunchKernelGGL(k_prepare_t<double>, dim3(nb, nb), dim3(256), 0, st, N, Np, J, ld, mu, (double*)Jt, Jr, rowscale,
+                       J64, mu64);
   else
-    hipLaunchKernelGGL(k_prepare_t<float>, dim3(nb, nb), dim3(256), 0, st, N, Np, J64, mu, (float*)Jt, Jr, rowscale);
+    hipLaunchKernelGGL(k_prepare_t<float>, dim3(nb, nb), dim3(256), 0, st, N, Np, J, ld, mu, (float*)Jt, Jr, rowscale,
+                       J64, mu64);
   return hipGetLastError();
 }

@@ -139,31 +139,18 @@ __global__ __launch_bounds__(RT) void k_assemble(const AssembleArgs* __restrict_
   if (tid == 0) {
     const double spike = (double)a.q[i] * a.mu[i] + dot, ll = spike - integ, gm = (double)a.q[i] - integ;
     a.ll_rows[i] = ll;
+    if (a.host_rows) a.host_rows[i] = ll;
     if (a.out_rows) a.out_rows[i] = ll;
     if (a.gmu) a.gmu[i] = gm;
     if (a.out_gmu) a.out_gmu[i] = gm;
   }
   if (a.tau_rows && tid < 64) {
     const double tv = a.rowpartV ? sc * row_total(a, 1, i) : 0.0;
-    if (tid == 0) a.tau_rows[i] = doty - tv;
+    if (tid == 0) {
+      a.tau_rows[i] = doty - tv;
+      if (a.host_rows) a.host_rows[a.N + i] = doty - tv;
+    }
   }
-}
-
-// L (and dL/dtau, blockIdx.x = 1) of each recording (blockIdx.y) from its rows
-__global__ __launch_bounds__(RT) void k_sum_rows(const AssembleArgs* __restrict__ list, AssembleArgs one) {
-  __shared__ double sh[RT];
-  const AssembleArgs a = list ? list[blockIdx.y] : one;
-  const double* v = blockIdx.x ? a.tau_rows : a.ll_rows;
-  if (!v) return;
-  // Neumaier-compensated per-thread partials, then a fixed tree
-  double s = 0.0, c = 0.0;
-  for (int k = threadIdx.x; k < a.N; k += RT) {
-    double x = v[k], t = s + x;
-    c += (fabs(s) >= fabs(x)) ? (s - t) + x : (x - t) + s;
-    s = t;
-  }
-  double tot = block_sum(s + c, sh);
-  if (threadIdx.x == 0) a.scal[blockIdx.x] = tot;
 }
 
 template <typename T> __device__ inline T to_prec(double x);
@@ -606,7 +593,6 @@ hipError_t launch_finish(const AssembleArgs* list, const AssembleArgs& one, int 
   hipLaunchKernelGGL(k_rowpart, dim3((unsigned)((max_Np + 255) / 256), RP_SPLITS, (unsigned)(3 * (n_rec - 1) + parts)),
                      dim3(256), 0, st, list, one);
   hipLaunchKernelGGL(k_assemble, dim3((unsigned)max_N, (unsigned)n_rec), dim3(RT), 0, st, list, one);
-  hipLaunchKernelGGL(k_sum_rows, dim3(one.tau_rows && !list ? 2 : 1, (unsigned)n_rec), dim3(RT), 0, st, list, one);
   return hipGetLastError();
 }
 

@@ -160,7 +160,7 @@ struct glmr_ctx {
   double* gJ = nullptr;
   double* gmu = nullptr;
   double* tau_rows = nullptr;
-  double* scal = nullptr;  // [4] pinned host memory that the kernels write: L, dL/dtau
+  double* host_rows = nullptr;  // [2][N] pinned: the rows of L and dL/dtau
 
   // ascent state
   AscentArgs asc{};
@@ -813,7 +813,8 @@ glmr_status ensure_workspace(glmr_ctx* c, bool want_grad, bool want_tau) {
     o.want(c->G64, Np * Np);
   }
   TRY(o.get(c, &mem));
-  if (!c->scal) HIPCHK(c, hipHostMalloc((void**)&c->scal, 4 * sizeof(double), hipHostMallocDefault));
+  if (!c->host_rows)
+    HIPCHK(c, hipHostMalloc((void**)&c->host_rows, 2 * (size_t)c->N * sizeof(double), hipHostMallocDefault));
   return GLMR_OK;
 }
 
@@ -1018,11 +1019,12 @@ hipError_t launch_g_chunk(glmr_ctx* c, int k, int64_t t0, int64_t Lc, int* n_spl
   return launch_res_g(k, c->prec == PREC_FP8 ? 1 : 0, ga, c->st);
 }
 
-struct Outputs {  // dense results that the assembly writes besides the context's own (nullable)
-  double *rows = nullptr, *gJ = nullptr, *gmu = nullptr;
+struct Outputs {  // what the assembly writes besides the context's own (nullable)
+  double *rows = nullptr, *gJ = nullptr, *gmu = nullptr;  // dense
+  double* host_rows = nullptr;
 };
-glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau, int64_t row_tiles, const Outputs& o);
-glmr_status prepare_params(glmr_ctx* c);
+AssembleArgs make_assemble_args(glmr_ctx* c, bool want_grad, bool want_tau, int64_t n_tiles, const Outputs& o);
+glmr_status prepare_params(glmr_ctx* c, const double* J = nullptr, const double* mu = nullptr);
 
 // One evaluation by the recurrence: the whole recording at once for the
 // likelihood alone, in chunks of W's length with the gradient.
@@ -1031,7 +1033,8 @@ glmr_status eval_rec(glmr_ctx* c, bool want_grad, bool want_tau, const Outputs& 
   const int64_t nseg = (c->B + seg - 1) / seg;
   const EvSlots ev = ev_slots(c);
   const int64_t L = want_grad ? c->L : c->Bp;
-  for (int64_t t0 = 0, ci = 0; t0 < c->B; t0 += L, ++ci) {
+  RecGArgs g{};
+  for (int64_t t0 = 0; t0 < c->B; t0 += L) {
     const int64_t Lc = std::min<int64_t>(L, c->Bp - t0);
     RecFArgs f{};
     f.g.N = c->N;
@@ -1066,7 +1069,7 @@ glmr_status eval_rec(glmr_ctx* c, bool want_grad, bool want_tau, const Outputs& 
       HIPCHK(c, launch_rec_forward(c->prec, f, c->st));
     }
     if (!want_grad) continue;
-    RecGArgs g{};
+    g = RecGArgs{};
     g.W = c->W;
     g.N = c->N;
     g.Np = c->Np;
@@ -1088,9 +1091,12 @@ glmr_status eval_rec(glmr_ctx* c, bool want_grad, bool want_tau, const Outputs& 
     g.G64 = c->G64;
     g.NS64 = c->NS * 64;
     ProfScope ps(c, K_G);
-    HIPCHK(c, launch_rec_gather(c->prec, g, ci == 0, c->st));
+    HIPCHK(c, launch_rec_gather(c->prec, g, c->st));
+    if (t0 + L < c->B) HIPCHK(c, launch_rec_reduce(g, t0 == 0, c->st));
   }
-  return eval_finish(c, want_grad, want_tau, nseg, o);
+  ProfScope ps(c, K_ASM);
+  HIPCHK(c, launch_rec_finish(g, make_assemble_args(c, want_grad, want_tau, nseg, o), L >= c->B, want_grad, c->st));
+  return GLMR_OK;
 }
 
 glmr_status eval_core(glmr_ctx* c, bool want_grad, bool want_tau, const Outputs& o = {}) {
@@ -1187,12 +1193,14 @@ glmr_status eval_core(glmr_ctx* c, bool want_grad, bool want_tau, const Outputs&
       HIPCHK(c, launch_gp_reduce(c->prec, c->Gp, g2.n_splits, Np, c->G64, ci == 0, c->st));
     }
   }
-  return eval_finish(c, want_grad, want_tau, c->Bp / c->bt1, o);
+  ProfScope ps(c, K_ASM);
+  HIPCHK(c, launch_finish(nullptr, make_assemble_args(c, want_grad, want_tau, c->Bp / c->bt1, o), 1, c->N, c->Np, c->st));
+  return GLMR_OK;
 }
 
 // Arguments of the last kernels of an evaluation: row sums of the weights over
 // all bins (n_tiles partials a row), then L_i, dL/dmu, dL/dJ (dL/dtau) in FP64.
-AssembleArgs make_assemble_args(glmr_ctx* c, bool want_grad, bool want_tau, int64_t n_tiles) {
+AssembleArgs make_assemble_args(glmr_ctx* c, bool want_grad, bool want_tau, int64_t n_tiles, const Outputs& o) {
   AssembleArgs aa{};
   aa.N = c->N;
   aa.Np = c->Np;
@@ -1213,26 +1221,39 @@ AssembleArgs make_assemble_args(glmr_ctx* c, bool want_grad, bool want_tau, int6
   aa.gJ = want_grad ? c->gJ : nullptr;
   aa.gmu = want_grad ? c->gmu : nullptr;
   aa.tau_rows = want_tau ? c->tau_rows : nullptr;
-  aa.scal = c->scal;
-  return aa;
-}
-
-glmr_status eval_finish(glmr_ctx* c, bool want_grad, bool want_tau, int64_t n_tiles, const Outputs& o) {
-  ProfScope ps(c, K_ASM);
-  AssembleArgs aa = make_assemble_args(c, want_grad, want_tau, n_tiles);
   aa.out_rows = o.rows;
   aa.out_gJ = o.gJ;
   aa.out_gmu = o.gmu;
-  HIPCHK(c, launch_finish(nullptr, aa, 1, c->N, c->Np, c->st));
-  return GLMR_OK;
+  aa.host_rows = o.host_rows;
+  return aa;
 }
 
-glmr_status prepare_params(glmr_ctx* c) {
+// L (which = 0) or dL/dtau (1) from its rows, in their order (Neumaier-compensated)
+double total_of_rows(const glmr_ctx* c, int which) {
+  const double* v = c->host_rows + (size_t)which * c->N;
+  double s = 0.0, e = 0.0;
+  for (int i = 0; i < c->N; ++i) {
+    const double t = s + v[i];
+    e += std::fabs(s) >= std::fabs(v[i]) ? (s - t) + v[i] : (v[i] - t) + s;
+    s = t;
+  }
+  return s + e;
+}
+
+// Stages the parameters for the contractions: the context's own, or dense J and
+// mu, which the context then holds.
+glmr_status prepare_params(glmr_ctx* c, const double* J, const double* mu) {
   ProfScope ps(c, K_PREP);
   if (c->prec == PREC_FP8 && !c->jscale) TRY(dalloc(c, c->jscale, (size_t)c->Np));
   c->jc_rec = use_rec(c);
+  // pinned host memory is read once, by rows (in the staging kernel's tiles: 27 us against 22 at N = 50)
+  if (J && (!c->jc_rec || J == c->pin)) {
+    HIPCHK(c, launch_load_params(c->N, c->Np, J, mu, c->J64, c->mu, c->st));
+    J = nullptr;
+  }
   if (c->jc_rec) {
-    HIPCHK(c, launch_prepare_t(c->prec, c->N, c->Np, c->J64, c->mu, c->Jc, c->Jr, c->rowscale, c->st));
+    HIPCHK(c, launch_prepare_t(c->prec, c->N, c->Np, J ? J : c->J64, J ? c->N : c->Np, J ? mu : c->mu, c->Jc, c->Jr,
+                               c->rowscale, J ? c->J64 : nullptr, J ? c->mu : nullptr, c->st));
     return GLMR_OK;
   }
   HIPCHK(c, launch_prepare_params(c->prec, c->j2 ? 1 : 0, c->N, c->Np, c->J64, c->mu, c->Jc, c->Jr, c->rowscale,
@@ -1680,7 +1701,9 @@ glmr_status build_queues(glmr_batch* b) {
     b->max_Np = 0;
     for (glmr_ctx* c : b->ctxs) {
       nch = std::max<int64_t>(nch, (c->Bp + c->L - 1) / c->L);
-      fin.push_back(make_assemble_args(c, true, false, c->Bp / c->bt1));
+      Outputs o;
+      o.host_rows = c->host_rows;
+      fin.push_back(make_assemble_args(c, true, false, c->Bp / c->bt1, o));
       b->max_N = std::max(b->max_N, c->N);
       b->max_Np = std::max(b->max_Np, c->Np);
     }
@@ -2072,8 +2095,9 @@ glmr_status glmr_batch_eval(glmr_batch* b, double* ll) {
   TRY(batch_eval_core(b));
   HIPCHK(b->ctxs[0], hipStreamSynchronize(b->st));
   for (size_t r = 0; r < b->ctxs.size(); ++r) {
-    if (ll) ll[r] = b->ctxs[r]->scal[0];
-    if (!std::isfinite(b->ctxs[r]->scal[0]))
+    const double L = total_of_rows(b->ctxs[r], 0);
+    if (ll) ll[r] = L;
+    if (!std::isfinite(L))
       return fail(b->ctxs[r], GLMR_ENONFINITE, "log-likelihood is not finite");
   }
   return GLMR_OK;
@@ -2358,7 +2382,7 @@ void glmr_destroy(glmr_ctx* c) {
   hipSetDevice(c->cfg.device);
   hipStreamSynchronize(c->st);
   for (void* p : c->allocs) hipFree(p);
-  if (c->scal) hipHostFree(c->scal);
+  if (c->host_rows) hipHostFree(c->host_rows);
   if (c->pin) hipHostFree(c->pin);
   if (c->host_cnt) hipHostFree(c->host_cnt);
   for (auto& r : c->pending) {
@@ -2684,8 +2708,7 @@ glmr_status glmr_set_params(glmr_ctx* c, const double* J, const double* mu, int3
     J = buf;
     mu = buf + N * N;
   }
-  HIPCHK(c, launch_load_params(c->N, Np, J, mu, c->J64, c->mu, c->st));
-  TRY(prepare_params(c));
+  TRY(prepare_params(c, J, mu));
   if (where == GLMR_HOST) HIPCHK(c, hipStreamSynchronize(c->st));
   c->have_params = true;
   return GLMR_OK;
@@ -2777,11 +2800,14 @@ glmr_status glmr_eval(glmr_ctx* c, double* ll, double* ll_rows, double* grad_J, 
   TRY(r.out(grad_J, 0, N * N, &o.gJ));
   TRY(r.out(grad_mu, N * N, N, &o.gmu));
   TRY(r.out(ll_rows, N * N + N, N, &o.rows));
+  TRY(ensure_workspace(c, want_grad, want_tau));
+  o.host_rows = c->host_rows;
   TRY(eval_core(c, want_grad, want_tau, o));
   TRY(r.finish());
-  if (ll) *ll = c->scal[0];
-  if (grad_tau) *grad_tau = c->scal[1];
-  if (!std::isfinite(c->scal[0])) return fail(c, GLMR_ENONFINITE, "log-likelihood is not finite");
+  const double L = total_of_rows(c, 0);
+  if (ll) *ll = L;
+  if (grad_tau) *grad_tau = want_tau ? total_of_rows(c, 1) : 0.0;
+  if (!std::isfinite(L)) return fail(c, GLMR_ENONFINITE, "log-likelihood is not finite");
   return GLMR_OK;
 }
 
