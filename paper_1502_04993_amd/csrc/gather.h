@@ -10,20 +10,26 @@
 namespace glmr_gather {
 
 constexpr int GW = GLMR_GW;          // bins per window
-constexpr int GI = 16;               // tile columns, lanes of a group
+constexpr int GI = 16;               // tile columns
 constexpr int GNT = 1024;            // threads of the gather workgroups
-constexpr int GG = GNT / GI;         // their groups of 16 lanes
+// Lanes of a group, two columns each, so that a lane reads 16 bytes of a row
+// at a time (16 lanes of one column, 8 bytes: kernel G 3.4 against 3.1 ms and
+// the spike term 2.55 against 2.45 ms at N = 1000, 1.2e6 bins, although the
+// longest of eight lists is longer than that of four).
+constexpr int GL = 8;
+constexpr int GG = GNT / GL;         // groups
 constexpr int TILE = (GW + 1) * GI;  // doubles; the last row is zero
 constexpr int CAP = 3070;            // groups of four entries staged in LDS
-constexpr int SCAN = 2 * 16 * GI;    // doubles of kernel G's scan
+constexpr int SCAN = 34 * GI;        // doubles of kernel G's scan
 constexpr int ENTRIES = TILE + SCAN; // where the staged entries start (in 8 bytes)
 constexpr size_t GATHER_LDS = (size_t)(ENTRIES + CAP + 2) * 8;
 static_assert(GATHER_LDS <= 160 * 1024, "tile, scan and entries fit in a CU's LDS");
 
-// value of v in lane K of the 16-lane group
+// value of v in lane K of the 8-lane group
 template <int K>
 __device__ __forceinline__ int group_bcast(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, 0x150 + K, 0xf, 0xf, false);  // row_newbcast
+  const int u = __builtin_amdgcn_update_dpp(0, v, 0x150 + K, 0xf, 0x3, false);  // row_newbcast, lower half of the rows
+  return __builtin_amdgcn_update_dpp(u, v, 0x150 + 8 + K, 0xf, 0xc, false);     // upper half
 }
 
 // A window's share of the lists for the JB neurons of a group (from idx in
@@ -36,10 +42,13 @@ __device__ __forceinline__ Ends load_ends(const int32_t* __restrict__ end2, int6
   return Ends{end2[idx - 1], end2[idx + (il < JB ? il : 0)]};
 }
 
-// acc[k] += the tile's rows at the entries of the group's neuron k: its 16
+// acc[k] += the tile's rows at the entries of the group's neuron k: its 8
 // lanes hold 16 tile columns and take one neuron after another; the lists of
 // consecutive neurons follow each other, so the next four entries are always
 // being loaded.
+struct Cols {
+  double a, b;  // a lane's two columns
+};
 // LDS byte address 8 u + base of the low or high half u of e, in one instruction
 __device__ __forceinline__ uint32_t addr_lo(uint32_t e, uint32_t base) {
   uint32_t a;
@@ -51,15 +60,16 @@ __device__ __forceinline__ uint32_t addr_hi(uint32_t e, uint32_t base) {
   asm("v_mad_u32_u16 %0, %1, 8, %2 op_sel:[1,0,0,0]" : "=v"(a) : "v"(e), "v"(base));
   return a;
 }
-typedef __attribute__((address_space(3))) const double lds_double;
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) const f64x2 lds_f64x2;
 typedef __attribute__((address_space(3))) const u32x2 lds_u32x2;
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
 
-// col: byte address of the lane's column; p, lim: of entries
+// col: byte address of the lane's columns; p, lim: of entries
 template <int K, int JB>
-__device__ __forceinline__ void walk(double (&acc)[JB], uint32_t col, uint32_t& p, u32x2& nx, uint32_t ends,
+__device__ __forceinline__ void walk(Cols (&acc)[JB], uint32_t col, uint32_t& p, u32x2& nx, uint32_t ends,
                                      uint32_t lim) {
   if constexpr (K < JB) {
     const uint32_t e0 = (uint32_t)group_bcast<K>((int)ends), end = e0 < lim ? e0 : lim;
@@ -67,9 +77,10 @@ __device__ __forceinline__ void walk(double (&acc)[JB], uint32_t col, uint32_t& 
       const u32x2 e = nx;
       p += 8;
       nx = *(lds_u32x2*)p;
-      const double v0 = *(lds_double*)addr_lo(e[0], col), v1 = *(lds_double*)addr_hi(e[0], col);
-      const double v2 = *(lds_double*)addr_lo(e[1], col), v3 = *(lds_double*)addr_hi(e[1], col);
-      acc[K] += (v0 + v1) + (v2 + v3);
+      const f64x2 v0 = *(lds_f64x2*)addr_lo(e[0], col), v1 = *(lds_f64x2*)addr_hi(e[0], col);
+      const f64x2 v2 = *(lds_f64x2*)addr_lo(e[1], col), v3 = *(lds_f64x2*)addr_hi(e[1], col);
+      acc[K].a += (v0[0] + v1[0]) + (v2[0] + v3[0]);
+      acc[K].b += (v0[1] + v1[1]) + (v2[1] + v3[1]);
     }
     walk<K + 1, JB>(acc, col, p, nx, ends, lim);
   }
@@ -85,10 +96,10 @@ __device__ __forceinline__ void stage_entries(uint2* es, const uint2* __restrict
 }
 
 template <int JB>
-__device__ __forceinline__ void gather_lists(double (&acc)[JB], double* lds, const uint2* __restrict__ ent, int base,
+__device__ __forceinline__ void gather_lists(Cols (&acc)[JB], double* lds, const uint2* __restrict__ ent, int base,
                                              int n, Ends e, int il, bool rows) {
   uint2* es = (uint2*)(lds + ENTRIES);
-  const uint32_t l0 = lds_addr(lds), col = l0 + 8 * il, e8 = l0 + 8 * ENTRIES;
+  const uint32_t l0 = lds_addr(lds), col = l0 + 16 * il, e8 = l0 + 8 * ENTRIES;
   int p = e.begin - base;
 #pragma unroll 1
   for (int q0 = 0; q0 < n; q0 += CAP) {
@@ -107,11 +118,11 @@ __device__ __forceinline__ void gather_lists(double (&acc)[JB], double* lds, con
   }
 }
 
-// neurons per group of 16 lanes: the smallest that covers them, at most 16
-// (16 FP64 sums a lane; more neurons take further blocks of 1024)
+// neurons per group: the smallest that covers them, at most 8 (16 FP64 sums a
+// lane; more neurons take further blocks of 1024)
 inline int gather_jb(int64_t Np) {
   int jb = 1;
-  while (jb < 16 && GG * jb < Np) jb *= 2;
+  while (jb < 8 && GG * jb < Np) jb *= 2;
   return jb;
 }
 

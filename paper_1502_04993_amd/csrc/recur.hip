@@ -27,7 +27,7 @@
 // What bounds it (N = 1000, 1.2e6 bins, 7.7e6 spikes, one evaluation with the
 // gradient): k_rec_fwd 2.5 ms (FP32) and 4.9 ms (FP64: twice the bytes of J
 // from the L2), half of it vector and scalar issue (20 of the instructions a
-// bin are the exponential, 7 a spike); k_rec_gather 3.7 ms, LDS reads and the
+// bin are the exponential, 7 a spike); k_rec_gather 3.1 ms, LDS reads and the
 // phases that form a tile.  The dense kernels took 56 and 58 ms.  On the event
 // grid (FP64): k_rec_fwd_ev 0.145 ms at N = 150, 6.6e4 slots and 2.1 ms at
 // N = 1000, 4.4e5 slots, the FP64 arithmetic of the integrals and, with four
@@ -43,6 +43,24 @@ namespace {
 
 using namespace glmr_gather;
 
+// The rows of 16 lanes of a wave: in every lane, its pair's even and odd row.
+struct Pair16 {
+  double even, odd;
+};
+__device__ __forceinline__ Pair16 swap_rows(double x) {
+  const u32x2 u = __builtin_bit_cast(u32x2, x);
+  const auto lo = __builtin_amdgcn_permlane16_swap(u[0], u[0], false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(u[1], u[1], false, false);
+  return Pair16{__builtin_bit_cast(double, u32x2{lo[0], hi[0]}), __builtin_bit_cast(double, u32x2{lo[1], hi[1]})};
+}
+// the value 32 lanes on, in every lane that of the upper half
+__device__ __forceinline__ double upper_half(double x) {
+  const u32x2 u = __builtin_bit_cast(u32x2, x);
+  const auto lo = __builtin_amdgcn_permlane32_swap(u[0], u[0], false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(u[1], u[1], false, false);
+  return __builtin_bit_cast(double, u32x2{lo[1], hi[1]});
+}
+
 // Kernel G: rows i0 .. i0 + 15, windows of a split from the last to the
 // first.  A thread holds 16 bins of one row: their W are loaded while the
 // window before is gathered, a first backward pass gives the 16 bins' share
@@ -53,6 +71,7 @@ __global__ __launch_bounds__(GNT) void k_rec_gather(RecGArgs a) {
   extern __shared__ __align__(16) double tile[];
   double* wh = tile + TILE;       // [16 waves][GI] a wave's 64 bins: share of R before them
   double* wp = wh + 16 * GI;      // and their decay
+  double* ce = wp + 16 * GI;      // [2][GI] R at a window's last bin, by the parity of the window
   uint2* es = (uint2*)(tile + ENTRIES);
   const uint2* __restrict__ ent = (const uint2*)a.ent2;
   const int tid = threadIdx.x, il = tid & (GI - 1), tb = tid / GI, wave = tid >> 6, tl = tb & 3;
@@ -62,11 +81,12 @@ __global__ __launch_bounds__(GNT) void k_rec_gather(RecGArgs a) {
   const int64_t split = blockIdx.y;
   const int64_t nw = (a.Lc + GW - 1) / GW;
   const int64_t w0 = split * a.wps, w1 = w0 + a.wps < nw ? w0 + a.wps : nw;
-  const int64_t j0 = jb0 + (int64_t)tb * JB;
+  const int gl = tid & (GL - 1);  // the lane's columns of the sums: 2 gl and the next
+  const int64_t j0 = jb0 + (int64_t)(tid / GL) * JB;
   const bool rows = j0 < a.Np;
-  double acc[JB];
+  Cols acc[JB];
 #pragma unroll
-  for (int k = 0; k < JB; ++k) acc[k] = 0.0;
+  for (int k = 0; k < JB; ++k) acc[k] = Cols{0.0, 0.0};
   if (tid < GI) tile[GW * GI + tid] = 0.0;
   const double ag = a.a;
   // W of the window by raw buffer loads: the row offsets sit in scalar
@@ -89,56 +109,92 @@ __global__ __launch_bounds__(GNT) void k_rec_gather(RecGArgs a) {
   const int64_t jend = jb0 + GG * JB < a.Np ? jb0 + GG * JB : a.Np;
   const int64_t wg = a.t0 / GW;  // the chunk's first window
   Ends en{0, 0};
-  double cend = 0.0;  // R at the last bin of the window
+  double cend = 0.0;  // R at the last bin of the window (uniform grid: in wave 0)
+  if (!EV && tid < GI) ce[((w1 - 1) & 1) * GI + tid] = 0.0;
+  double P = 1.0, P64 = 1.0;  // decay over 16 and (bins) 64 steps
+  if (!EV) {
+    P = ag * ag;
+    P *= P;
+    P *= P;
+    P *= P;
+    P64 = P * P;
+    P64 *= P64;
+  }
   if (w1 > w0) {
     fetch(w1 - 1);
-    if (rows) en = load_ends<JB>(a.end2, (wg + w1 - 1) * a.Np + j0, il);
+    if (rows) en = load_ends<JB>(a.end2, (wg + w1 - 1) * a.Np + j0, gl);
   }
   for (int64_t w = w1 - 1; w >= w0; --w) {
-    double h = 0.0, P = 1.0;
+    double h = 0.0;
     double dn[EV ? 16 : 1];
     if (EV) {
       const double* __restrict__ ed = a.ev.edec + a.t0 + w * GW + tb * 16;
       const bool in = a.t0 + w * GW + tb * 16 < a.NS64;
 #pragma unroll
       for (int m = 0; m < 16; ++m) dn[m] = in ? ed[m] : 1.0;
-    }
-    if (!EV) {
-      P = ag * ag;
-      P *= P;
-      P *= P;
-      P *= P;
+      P = 1.0;
     }
 #pragma unroll
     for (int m = 15; m >= 0; --m) {
       h = (double)wn[m] + (EV ? dn[m] : ag) * h;
       if (EV) P *= dn[m];
     }
-    // inclusive suffix over the wave's four 16-bin blocks
-    double hs = h, Ps = P;
-    {
+    // hx, Px: what the later blocks of the wave (its rows of 16 lanes) add to
+    // R at this block's end, and their decay; in row 0, ht and Pt with this block
+    double hx, Px, ht, Pt;
+    if constexpr (EV) {
+      double hs = h, Ps = P;
       const double h1 = __shfl_down(hs, 16, 64), P1 = __shfl_down(Ps, 16, 64);
       if (tl < 3) { hs += Ps * h1; Ps *= P1; }
       const double h2 = __shfl_down(hs, 32, 64), P2 = __shfl_down(Ps, 32, 64);
       if (tl < 2) { hs += Ps * h2; Ps *= P2; }
+      ht = hs;
+      Pt = Ps;
+      hx = __shfl_down(hs, 16, 64);
+      Px = __shfl_down(Ps, 16, 64);
+      if (tl == 3) { hx = 0.0; Px = 1.0; }
+    } else {  // pairs of rows, then the pair two rows on; the decays are known
+      // (by permutes through LDS, and with every wave going over all sixteen
+      // shares and decays below, the kernel took 5 % longer)
+      const bool odd = tl & 1;
+      const Pair16 p = swap_rows(h);
+      const double late = odd ? h : p.odd, pair = (odd ? p.even : h) + P * late, next = upper_half(pair);
+      ht = pair + P * P * next;
+      Pt = P64;
+      hx = tl == 0 ? late + P * next : tl == 1 ? next : tl == 2 ? late : 0.0;
+      Px = tl == 0 ? P * P * P : tl == 1 ? P * P : tl == 2 ? P : 1.0;
     }
     if (tl == 0) {
-      wh[wave * GI + il] = hs;
-      wp[wave * GI + il] = Ps;
+      wh[wave * GI + il] = ht;
+      if (EV) wp[wave * GI + il] = Pt;
     }
     const Ends ec = en;
     const int base = a.end2[(wg + w) * a.Np + jb0 - 1], n = a.end2[(wg + w) * a.Np + jend - 1] - base;
     __syncthreads();  // (also: the previous window's tile has been read)
     stage_entries(es, ent, base, n);
-    double c = cend, cw = cend;
+    // into this wave from the later ones; on the uniform grid only wave 0
+    // goes on to the window's start and passes it on through LDS (half the
+    // reads, but the registers of the slots' decays leave no room for it)
+    double c;
+    if constexpr (EV) {
+      double all = cend;
+      c = cend;
 #pragma unroll 4
-    for (int v = 15; v >= 0; --v) {
-      if (v == wave) cw = c;
-      c = wh[v * GI + il] + wp[v * GI + il] * c;
+      for (int v = 15; v >= 0; --v) {
+        if (v == wave) c = all;
+        all = wh[v * GI + il] + wp[v * GI + il] * all;
+      }
+      cend = all;
+    } else {
+      c = ce[(w & 1) * GI + il];
+#pragma unroll 4
+      for (int v = 15; v > wave; --v) c = wh[v * GI + il] + P64 * c;
+      if (wave == 0) {
+        cend = wh[il] + P64 * c;
+        if (tl == 0) ce[((w - 1) & 1) * GI + il] = cend;
+      }
     }
-    cend = c;
-    const double hx = __shfl_down(hs, 16, 64), Px = __shfl_down(Ps, 16, 64);
-    double r = tl < 3 ? hx + Px * cw : cw;
+    double r = hx + Px * c;
     double* dst = tile + tb * 16 * GI + il;
 #pragma unroll
     for (int m = 15; m >= 0; --m) {
@@ -148,15 +204,15 @@ __global__ __launch_bounds__(GNT) void k_rec_gather(RecGArgs a) {
     __syncthreads();
     if (w > w0) {
       fetch(w - 1);
-      if (rows) en = load_ends<JB>(a.end2, (wg + w - 1) * a.Np + j0, il);
+      if (rows) en = load_ends<JB>(a.end2, (wg + w - 1) * a.Np + j0, gl);
     }
-    gather_lists<JB>(acc, tile, ent, base, n, ec, il, rows);
+    gather_lists<JB>(acc, tile, ent, base, n, ec, gl, rows);
   }
   if (blockIdx.x / nib == 0 && tb == 0) a.head[split * a.Np + i] = cend;
   if (!rows) return;
   double* out = (double*)a.Gp + split * a.Np * a.Np;
 #pragma unroll
-  for (int k = 0; k < JB; ++k) out[(j0 + k) * a.Np + i] = acc[k];
+  for (int k = 0; k < JB; ++k) *(Cols*)(out + (j0 + k) * a.Np + (i - il + 2 * gl)) = acc[k];
 }
 
 // G[i][j] (+)= sum over the splits of Gp[p][j][i] + head[p][i] C[start of p][j]:
@@ -692,8 +748,7 @@ hipError_t rec_gather(const RecGArgs& a, hipStream_t st) {
     case 1: return run_gather(k_rec_gather<WT, EV, 1>, a, blocks, a.n_splits, st);
     case 2: return run_gather(k_rec_gather<WT, EV, 2>, a, blocks, a.n_splits, st);
     case 4: return run_gather(k_rec_gather<WT, EV, 4>, a, blocks, a.n_splits, st);
-    case 8: return run_gather(k_rec_gather<WT, EV, 8>, a, blocks, a.n_splits, st);
-    default: return run_gather(k_rec_gather<WT, EV, 16>, a, blocks, a.n_splits, st);
+    default: return run_gather(k_rec_gather<WT, EV, 8>, a, blocks, a.n_splits, st);
   }
 }
 

@@ -15,9 +15,9 @@
 // the event grid the trace at a spike of i is the left limit v_j(t^-) of
 // Eq. (12), x decayed over the whole slot before it.  Partials per time split
 // are reduced in a fixed order.  Bound by the LDS reads (8 bytes a spike and
-// column, in fours: 1.6 times the spikes at N = 1000, where the longest of a
-// wave's four lists sets its pace) and their latency.  N = 1000, 1.2e6 bins,
-// 7.7e6 spikes: 3.15 ms; a wave walking its 16 rows' spikes with the sums in
+// column, in fours: 1.8 times the spikes at N = 1000, where the longest of a
+// wave's eight lists sets its pace) and their latency.  N = 1000, 1.2e6 bins,
+// 7.7e6 spikes: 2.45 ms; a wave walking its 16 rows' spikes with the sums in
 // LDS and the trace selected per spike took 8.95 ms.
 #include <algorithm>
 
@@ -176,14 +176,15 @@ __global__ __launch_bounds__(GNT) void k_spk_gather(SpikeTermArgs a) {
   const int64_t ncb = a.Np / GI;
   const int64_t j = (int64_t)(blockIdx.x % ncb) * GI + il;
   const int64_t ib0 = (int64_t)(blockIdx.x / ncb) * (GG * JB);
+  const int gl = tid & (GL - 1);  // the lane's columns of the sums: 2 gl and the next
   const int64_t split = blockIdx.y;
   const int64_t nw = (a.NS * 64 + GW - 1) / GW, per = (nw + a.splits - 1) / a.splits;
   const int64_t w0 = split * per, w1 = w0 + per < nw ? w0 + per : nw;
-  const int64_t i0 = ib0 + (int64_t)tb * JB;  // this group's rows
+  const int64_t i0 = ib0 + (int64_t)(tid / GL) * JB;  // its group's rows
   const bool rows = i0 < a.Np;
-  double acc[JB];
+  Cols acc[JB];
 #pragma unroll
-  for (int k = 0; k < JB; ++k) acc[k] = 0.0;
+  for (int k = 0; k < JB; ++k) acc[k] = Cols{0.0, 0.0};
   if (tid < GI) tile[GW * GI + tid] = 0.0;
   uint2* es = (uint2*)(tile + ENTRIES);
   const uint2* __restrict__ ent = (const uint2*)a.ent2;
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(GNT) void k_spk_gather(SpikeTermArgs a) {
     Cn = in ? a.C64[s * a.Np + j] : 0.0;
     if (Y) CYn = in ? a.CY64[s * a.Np + j] : 0.0;
     mn = in ? a.masks[s * a.Np + j] : 0ull;
-    if (rows) en = load_ends<JB>(a.end2, w * a.Np + i0, il);
+    if (rows) en = load_ends<JB>(a.end2, w * a.Np + i0, gl);
   };
   if (w0 < w1) fetch(w0);
   for (int64_t w = w0; w < w1; ++w) {
@@ -246,12 +247,12 @@ __global__ __launch_bounds__(GNT) void k_spk_gather(SpikeTermArgs a) {
     }
     __syncthreads();
     if (w + 1 < w1) fetch(w + 1);
-    gather_lists<JB>(acc, tile, ent, base, n, ec, il, rows);
+    gather_lists<JB>(acc, tile, ent, base, n, ec, gl, rows);
   }
   if (!rows) return;
   double* out = a.part + split * a.Np * a.Np;
 #pragma unroll
-  for (int k = 0; k < JB; ++k) out[(i0 + k) * a.Np + j] = acc[k];
+  for (int k = 0; k < JB; ++k) *(Cols*)(out + (i0 + k) * a.Np + (j - il + 2 * gl)) = acc[k];
 }
 
 __global__ void k_split_reduce(const double* part, int splits, int64_t n, double* out) {
@@ -271,8 +272,7 @@ hipError_t spk_gather(const SpikeTermArgs& a, hipStream_t st) {
     case 1: return run_gather(k_spk_gather<Y, EV, 1>, a, blocks, a.splits, st);
     case 2: return run_gather(k_spk_gather<Y, EV, 2>, a, blocks, a.splits, st);
     case 4: return run_gather(k_spk_gather<Y, EV, 4>, a, blocks, a.splits, st);
-    case 8: return run_gather(k_spk_gather<Y, EV, 8>, a, blocks, a.splits, st);
-    default: return run_gather(k_spk_gather<Y, EV, 16>, a, blocks, a.splits, st);
+    default: return run_gather(k_spk_gather<Y, EV, 8>, a, blocks, a.splits, st);
   }
 }
 
