@@ -61,7 +61,10 @@ __device__ inline int64_t xcd_logical(int64_t bid, int64_t nblk) {
 // 16g .. 16g+15 of column j in FP64, from the carry C[s][j] and the spikes of
 // the subtile, and rounds them to BF16.  Xjt rows are written straight from
 // registers (32 contiguous bytes per thread); Xtj rows go through LDS so that
-// each row of 64 columns is written as 128 contiguous bytes.
+// each row of 64 columns is written as 128 contiguous bytes.  Bound by the
+// writes; the fragments pass by the caches, which hold too little of them for
+// the evaluation that reads them next (4.9 GB at N = 1000, 1.2e6 bins: 1.15
+// ms, 1.25 ms with ordinary stores).
 __global__ __launch_bounds__(256) void k_build_x(ResXArgs g) {
   __shared__ __align__(16) unsigned char tile[64 * ROWB];
   const int64_t njb = g.Np / 64;
@@ -116,8 +119,8 @@ __global__ __launch_bounds__(256) void k_build_x(ResXArgs g) {
     // lanes j % 32 (first 8 bins) and j % 32 + 32 of the fragment (j / 32,
     // (64 s + m0) / 16); a wave's 64 columns fill two fragments
     i32x4* xr = (i32x4*)g.Xjt + ((j >> 5) * (g.Bp / 16) + (s * 64 + m0) / 16) * 64 + (j & 31);
-    xr[0] = i32x4{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-    xr[32] = i32x4{(int)w[4], (int)w[5], (int)w[6], (int)w[7]};
+    __builtin_nontemporal_store(i32x4{(int)w[0], (int)w[1], (int)w[2], (int)w[3]}, xr);
+    __builtin_nontemporal_store(i32x4{(int)w[4], (int)w[5], (int)w[6], (int)w[7]}, xr + 32);
   } else {
     // Xjt[j][64 s + m0 .. + 16]
     i32x4* xr = (i32x4*)((__bf16*)g.Xjt + j * g.Bp + s * 64 + m0);
@@ -137,7 +140,7 @@ __global__ __launch_bounds__(256) void k_build_x(ResXArgs g) {
       const int tbl = f >> 2, kbl = f & 3;  // 32-bin and 16-column block within the block
       const i32x4 v = *(const i32x4*)(tile + (tbl * 32 + (ln & 31)) * ROWB + (kbl * 16 + 8 * (ln >> 5)) * 2);
       const int64_t frag = (s * 2 + tbl) * (g.Np / 16) + jb * 4 + kbl;
-      *(i32x4*)((unsigned char*)g.Xtj + (frag * 64 + ln) * 16) = v;
+      __builtin_nontemporal_store(v, (i32x4*)((unsigned char*)g.Xtj + (frag * 64 + ln) * 16));
     }
     return;
   }
