@@ -215,23 +215,28 @@ __global__ __launch_bounds__(GNT) void k_rec_gather(RecGArgs a) {
   for (int k = 0; k < JB; ++k) *(Cols*)(out + (j0 + k) * a.Np + (i - il + 2 * gl)) = acc[k];
 }
 
-// G[i][j] (+)= sum over the splits of Gp[p][j][i] + head[p][i] C[start of p][j]:
-// 32 rows x 8 columns a workgroup, eight splits' loads in flight (with 32 x 32
+// sum over the splits p0, p0 + step, ... of Gp[p][j][i] + head[p][i] C[start of p][j],
+// eight loads in flight
+__device__ __forceinline__ double sum_splits(const RecGArgs& a, int64_t i, int64_t j, int p0, int step) {
+  const int64_t cstep = a.wps * (GW / 64) * a.Np, gstep = a.Np * a.Np;
+  const double* __restrict__ gp = (const double*)a.Gp + j * a.Np + i;
+  const double* __restrict__ C = a.C64 + (a.t0 >> 6) * a.Np + j;
+  const double* __restrict__ hd = a.head + i;
+  double v = 0.0;
+#pragma unroll 8
+  for (int p = p0; p < a.n_splits; p += step) v += gp[p * gstep] + hd[p * a.Np] * C[p * cstep];
+  return v;
+}
+
+// G[i][j] (+)= that sum: 32 rows x 8 columns a workgroup (with 32 x 32
 // a workgroup and a split at a time the few workgroups of a small network
 // waited on memory: 87 us at 256 rows and 65 splits)
 __global__ __launch_bounds__(256) void k_rec_reduce(RecGArgs a, int first) {
   __shared__ double t[8][33];
   const int64_t i0 = (int64_t)blockIdx.x * 32, j0 = (int64_t)blockIdx.y * 8;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const int64_t i = i0 + tx, j = j0 + ty, cstep = a.wps * (GW / 64) * a.Np, gstep = a.Np * a.Np;
-  const double* __restrict__ gp = (const double*)a.Gp + j * a.Np + i;
-  const double* __restrict__ C = a.C64 + (a.t0 >> 6) * a.Np + j;
-  const double* __restrict__ hd = a.head + i;
-  double v = 0.0;
-  if (i < a.N) {
-#pragma unroll 8
-    for (int p = 0; p < a.n_splits; ++p) v += gp[p * gstep] + hd[p * a.Np] * C[p * cstep];
-  }
+  const int64_t i = i0 + tx, j = j0 + ty;
+  const double v = i < a.N ? sum_splits(a, i, j, 0, 1) : 0.0;
   t[ty][tx] = v;
   __syncthreads();
   double* g = a.G64 + (i0 + (threadIdx.x >> 3)) * a.Np + j0 + (threadIdx.x & 7);
@@ -239,85 +244,95 @@ __global__ __launch_bounds__(256) void k_rec_reduce(RecGArgs a, int first) {
 }
 
 // The end of an evaluation in one launch, workgroups of two kinds.  The first
-// Np / 32 take 32 rows each: the sums of kernel U's partials over the
+// Np / RROWS take RROWS rows each: the sums of kernel U's partials over the
 // segments, L_i, dL/dmu_i and dL/dtau_i.  The others (with the gradient) take
-// a 32 x 32 tile of the last chunk's reduction (k_rec_reduce) and write dL/dJ:
-// it needs no row sum.  All are short and bound by latency (16 loads in flight
-// a thread); reduction, row sums, assembly and totals as four kernels and
-// their gaps took 25 us more of the 0.26 ms of an evaluation at N = 150 on the
-// event grid, 50 of 1250 us of a gradient step at N = 500.
+// a 32 x 8 tile of the last chunk's reduction (k_rec_reduce), a quarter of the
+// splits a thread, and write dL/dJ: it needs no row sum.  All are short and
+// bound by latency, hence many small workgroups with 8 or 16 loads in flight a
+// thread: 14 us at N = 150, 65 splits and 2064 segments on the event grid (32
+// x 32 tiles without a split of the splits: 25 us; reduction, row sums,
+// assembly and totals as four kernels: 24 us and three gaps), 9 us for the
+// rows alone at N = 500 (32 rows a workgroup: 19 us).
+constexpr int RROWS = 8;
 __global__ __launch_bounds__(1024) void k_rec_finish(RecGArgs a, AssembleArgs s, int first) {
-  __shared__ double t[32][33];
-  const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
-  const int64_t nb = s.Np / 32;
-  if (blockIdx.x >= nb) {
-    const int64_t k = blockIdx.x - nb, i0 = k % nb * 32, j0 = k / nb * 32, i = i0 + tx, j = j0 + ty;
-    const int64_t cstep = a.wps * (GW / 64) * a.Np, gstep = a.Np * a.Np;
-    const double* __restrict__ gp = (const double*)a.Gp + j * a.Np + i;
-    const double* __restrict__ C = a.C64 + (a.t0 >> 6) * a.Np + j;
-    const double* __restrict__ hd = a.head + i;
-    double v = 0.0;
-    if (i < a.N) {
-#pragma unroll 8
-      for (int p = 0; p < a.n_splits; ++p) v += gp[p * gstep] + hd[p * a.Np] * C[p * cstep];
-    }
-    t[ty][tx] = v;
+  const int tid = threadIdx.x;
+  const int64_t nb = s.Np / 32, rb = s.Np / RROWS;
+  if (blockIdx.x >= rb) {
+    __shared__ double t[4][8][33];
+    const int64_t k = blockIdx.x - rb, i0 = k % nb * 32, j0 = k / nb * 8;
+    const int tx = tid & 31, ty = (tid >> 5) & 7, q = tid >> 8;
+    t[q][ty][tx] = i0 + tx < a.N ? sum_splits(a, i0 + tx, j0 + ty, q, 4) : 0.0;
     __syncthreads();
-    const int64_t r = i0 + ty, c = j0 + tx;
-    if (r >= s.N) return;
-    const double G = (first ? 0.0 : a.G64[r * s.Np + c]) + t[tx][ty];
+    const int u = tid >> 3, w = tid & 7;
+    const int64_t r = i0 + u, c = j0 + w;
+    if (tid >= 256 || r >= s.N) return;
+    const double G = (first ? 0.0 : a.G64[r * s.Np + c]) + ((t[0][w][u] + t[1][w][u]) + (t[2][w][u] + t[3][w][u]));
     const double g = c < s.N ? s.dsig[r * s.Np + c] - s.dt * s.rowscale[r] * G : 0.0;
     s.gJ[r * s.Np + c] = g;
     if (s.out_gJ && c < s.N) s.out_gJ[r * s.N + c] = g;
     return;
   }
-  __shared__ double sums[2][32];
-  const int64_t i0 = (int64_t)blockIdx.x * 32;
+  __shared__ double sums[2][16][RROWS], dot[2][RROWS];
+  const int64_t i0 = (int64_t)blockIdx.x * RROWS;
+  const int lane = tid & 63, wave = tid >> 6;
+  // sixteen segments' loads in flight, then over the wave's lanes of a row
   for (int which = 0; which < 2; ++which) {
     const double* __restrict__ rp = which ? s.rowpartV : s.rowpart;
     double v = 0.0;
-    if (rp) {
-#pragma unroll 16
-      for (int64_t k = ty; k < s.n_tiles; k += 32) v += rp[k * s.Np + i0 + tx];
+    for (int64_t k0 = tid / RROWS; rp && k0 < s.n_tiles; k0 += 1024 / RROWS * 16) {
+      double w[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int64_t k = k0 + 1024 / RROWS * e;
+        w[e] = k < s.n_tiles ? rp[k * s.Np + i0 + tid % RROWS] : 0.0;
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v += w[e];
     }
-    t[ty][tx] = v;
-    __syncthreads();
-    if (ty == 0) {
-      double w = 0.0;
-      for (int k = 0; k < 32; ++k) w += t[k][tx];
-      sums[which][tx] = w;
-    }
-    __syncthreads();
+#pragma unroll
+    for (int o = 32; o >= RROWS; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (lane < RROWS) sums[which][wave][lane] = v;
   }
-  const int lane = tid & 63, wave = tid >> 6;
-  for (int k = 0; k < 2; ++k) {
-    const int il = 2 * wave + k;
-    const int64_t i = i0 + il;
-    if (i >= s.N) return;
-    const double *Jr = s.Jr + i * s.Np, *ds = s.dsig + i * s.Np;
+  // sum_j J_ij dSigma_ij (and of dSigmaY), a wave a row
+  if (wave < RROWS) {
+    const int64_t at = (i0 + wave) * s.Np;
     double v = 0.0, vy = 0.0;
+#pragma unroll 4
     for (int64_t j = lane; j < s.N; j += 64) {
-      v += Jr[j] * ds[j];
-      if (s.dsigY) vy += Jr[j] * s.dsigY[i * s.Np + j];
+      v += s.Jr[at + j] * s.dsig[at + j];
+      if (s.dsigY) vy += s.Jr[at + j] * s.dsigY[at + j];
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
       v += __shfl_xor(v, o, 64);
       vy += __shfl_xor(vy, o, 64);
     }
-    if (lane) continue;
-    const double sc = s.dt * s.rowscale[i], integ = sc * sums[0][il];
-    const double ll = (double)s.q[i] * s.mu[i] + v - integ, gm = (double)s.q[i] - integ;
-    s.ll_rows[i] = ll;
-    if (s.host_rows) s.host_rows[i] = ll;
-    if (s.out_rows) s.out_rows[i] = ll;
-    if (s.gmu) s.gmu[i] = gm;
-    if (s.out_gmu) s.out_gmu[i] = gm;
-    if (s.tau_rows) {
-      const double tr = vy - sc * sums[1][il];
-      s.tau_rows[i] = tr;
-      if (s.host_rows) s.host_rows[s.N + i] = tr;
+    if (lane == 0) {
+      dot[0][wave] = v;
+      dot[1][wave] = vy;
     }
+  }
+  __syncthreads();
+  // the workgroup's rows in one piece (some arrays are host memory)
+  const int64_t i = i0 + tid;
+  if (tid >= RROWS || i >= s.N) return;
+  double total[2] = {0.0, 0.0};
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    total[0] += sums[0][w][tid];
+    total[1] += sums[1][w][tid];
+  }
+  const double sc = s.dt * s.rowscale[i], integ = sc * total[0];
+  const double ll = (double)s.q[i] * s.mu[i] + dot[0][tid] - integ, gm = (double)s.q[i] - integ;
+  s.ll_rows[i] = ll;
+  if (s.host_rows) s.host_rows[i] = ll;
+  if (s.out_rows) s.out_rows[i] = ll;
+  if (s.gmu) s.gmu[i] = gm;
+  if (s.out_gmu) s.out_gmu[i] = gm;
+  if (s.tau_rows) {
+    const double tr = dot[1][tid] - sc * total[1];
+    s.tau_rows[i] = tr;
+    if (s.host_rows) s.host_rows[s.N + i] = tr;
   }
 }
 
@@ -664,53 +679,60 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   rowpart[(g.seg0 + sg) * g.Np + i] = sum;
 }
 
-// Dc[r][i] = sum_j C[(row0 + r) kc][j] J[i][j]: 64 x 64 tiles on the FP64 MFMA,
-// 16 columns j a step through LDS.
+// Dc[r][i] = sum_j C[(row0 + r) kc][j] J[i][j]: 32 x 64 tiles on the FP64 MFMA,
+// KS columns j a step through LDS.  The tiles are few (592 at N = 1000 and
+// 1.2e6 bins, 592 at N = 500 and 3e5) and the busiest CU sets the time: with 64
+// x 64 tiles, two to some CUs and one to the others, and 16 columns a step, the
+// load of a step took longer than its MFMAs and the kernel 98 and 60 us
+// instead of 62 and 44.
+constexpr int KS = 32;
 template <typename JT>
 __global__ __launch_bounds__(256) void k_carry_gemm(const double* __restrict__ C, const JT* __restrict__ Jt,
                                                     double* __restrict__ out, int64_t rows, int64_t row0, int64_t kc,
                                                     int64_t NS, int64_t Np) {
-  __shared__ double As[64][18], Bs[16][66];
+  __shared__ double As[32][KS + 2], Bs[KS][66];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t nt = Np / 64;
-  const int64_t i0 = (int64_t)(blockIdx.x % nt) * 64, r0 = (int64_t)(blockIdx.x / nt) * 64;
-  f64x4 acc[4];
+  const int64_t i0 = (int64_t)(blockIdx.x % nt) * 64, r0 = (int64_t)(blockIdx.x / nt) * 32;
+  const int wr = wave & 1, wc = wave >> 1;  // a wave's 16 rows and 32 columns
+  f64x4 acc[2];
 #pragma unroll
-  for (int b = 0; b < 4; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
-  double an[4], bn[4];
+  for (int b = 0; b < 2; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
+  double an[KS / 8], bn[KS / 4];
   auto fetch = [&](int64_t k0) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = (tid >> 4) + 16 * q, c = tid & 15;
+    for (int q = 0; q < KS / 8; ++q) {
+      const int r = tid / KS + 256 / KS * q, c = tid % KS;
       const int64_t s = (row0 + r0 + r) * kc;
       an[q] = (r0 + r < rows && s < NS) ? C[s * Np + k0 + c] : 0.0;
-      bn[q] = (double)Jt[(k0 + (tid >> 6) + 4 * q) * Np + i0 + lane];
     }
+#pragma unroll
+    for (int q = 0; q < KS / 4; ++q) bn[q] = (double)Jt[(k0 + (tid >> 6) + 4 * q) * Np + i0 + lane];
   };
   fetch(0);
-  for (int64_t k0 = 0; k0 < Np; k0 += 16) {
+  for (int64_t k0 = 0; k0 < Np; k0 += KS) {
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      As[(tid >> 4) + 16 * q][tid & 15] = an[q];
-      Bs[(tid >> 6) + 4 * q][lane] = bn[q];
-    }
+    for (int q = 0; q < KS / 8; ++q) As[tid / KS + 256 / KS * q][tid % KS] = an[q];
+#pragma unroll
+    for (int q = 0; q < KS / 4; ++q) Bs[(tid >> 6) + 4 * q][lane] = bn[q];
     __syncthreads();
-    if (k0 + 16 < Np) fetch(k0 + 16);
+    if (k0 + KS < Np) fetch(k0 + KS);
 #pragma unroll
-    for (int k = 0; k < 16; k += 4) {
-      const double a = As[wave * 16 + (lane & 15)][k + (lane >> 4)];
+    for (int k = 0; k < KS; k += 4) {
+      const double a = As[wr * 16 + (lane & 15)][k + (lane >> 4)];
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
-        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Bs[k + (lane >> 4)][b * 16 + (lane & 15)], acc[b], 0, 0, 0);
+      for (int b = 0; b < 2; ++b)
+        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Bs[k + (lane >> 4)][wc * 32 + b * 16 + (lane & 15)], acc[b], 0,
+                                                      0, 0);
     }
   }
 #pragma unroll
-  for (int b = 0; b < 4; ++b)
+  for (int b = 0; b < 2; ++b)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t row = r0 + wave * 16 + (lane >> 4) + 4 * r;
-      if (row < rows) out[row * Np + i0 + b * 16 + (lane & 15)] = acc[b][r];
+      const int64_t row = r0 + wr * 16 + (lane >> 4) + 4 * r;
+      if (row < rows) out[row * Np + i0 + wc * 32 + b * 16 + (lane & 15)] = acc[b][r];
     }
 }
 
@@ -775,7 +797,7 @@ hipError_t rec_fwd(const RecFArgs& a, hipStream_t st) {
 
 template <typename T>
 hipError_t carry_gemm(const RecFArgs& a, const double* C, double* out, hipStream_t st) {
-  const int64_t blocks = (a.g.Np / 64) * ((a.rows + 63) / 64);
+  const int64_t blocks = (a.g.Np / 64) * ((a.rows + 31) / 32);
   hipLaunchKernelGGL(k_carry_gemm<T>, dim3((unsigned)blocks), dim3(256), 0, st, C, (const T*)a.Jt, out, a.rows,
                      a.g.row0, a.g.kc, a.g.NS, a.g.Np);
   return hipGetLastError();
@@ -811,7 +833,7 @@ hipError_t launch_rec_reduce(const RecGArgs& a, int first, hipStream_t st) {
 
 hipError_t launch_rec_finish(const RecGArgs& a, const AssembleArgs& s, int first, int grad, hipStream_t st) {
   const int64_t nb = s.Np / 32;
-  hipLaunchKernelGGL(k_rec_finish, dim3((unsigned)(nb + (grad ? nb * nb : 0))), dim3(1024), 0, st, a, s, first);
+  hipLaunchKernelGGL(k_rec_finish, dim3((unsigned)(s.Np / RROWS + (grad ? nb * (s.Np / 8) : 0))), dim3(1024), 0, st, a, s, first);
   return hipGetLastError();
 }
 
