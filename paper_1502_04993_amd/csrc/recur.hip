@@ -25,7 +25,7 @@
 // sum_t W_i[t] (decay since its start) times C_j at its start (k_rec_reduce).
 //
 // What bounds it (N = 1000, 1.2e6 bins, 7.7e6 spikes, one evaluation with the
-// gradient): k_rec_fwd 2.5 ms (FP32) and 4.9 ms (FP64: twice the bytes of J
+// gradient): k_rec_fwd 2.5 ms (FP32) and 2.9 ms (FP64: twice the bytes of J
 // from the L2), half of it vector and scalar issue (20 of the instructions a
 // bin are the exponential, 7 a spike); k_rec_gather 3.1 ms, LDS reads and the
 // phases that form a tile.  The dense kernels took 56 and 58 ms.  On the event
@@ -353,15 +353,38 @@ __device__ __forceinline__ void buf_store(T v, __amdgpu_buffer_rsrc_t r, int vof
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, 0);
 }
 
-// One wave per 64 rows (lane = row) and segment of g.seg bins (PART: less than
-// a subtile).  A batch is 8 entries (uniform loads, a batch ahead); each
+// R neighbouring values of T by one buffer access
+template <typename T, int R>
+struct Vals {
+  T v[R];
+};
+template <typename T, int R>
+__device__ __forceinline__ Vals<T, R> buf_load_r(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  if constexpr (R == 1) return Vals<T, R>{{buf_load<T>(r, voff, soff)}};
+  else if constexpr (sizeof(T) == 8)
+    return __builtin_bit_cast(Vals<T, R>, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+  else
+    return __builtin_bit_cast(Vals<T, R>, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+}
+template <typename T, int R>
+__device__ __forceinline__ void buf_store_r(const Vals<T, R>& x, __amdgpu_buffer_rsrc_t r, int voff, int soff) {
+  if constexpr (R == 1) buf_store<T>(x.v[0], r, voff, soff);
+  else if constexpr (sizeof(T) == 8)
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, x), r, voff, soff, 0);
+  else
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, voff, soff, 0);
+}
+
+// One wave per 64 R rows (a lane holds R neighbours) and segment of g.seg bins
+// (PART: less than a subtile).  With two rows a lane the scalar unit and the
+// entries' loads serve twice the sums.  A batch is 8 entries (uniform loads, a batch ahead); each
 // entry's row of J^T is loaded as the entry 8 before it is used.  Row offsets
 // are 32-bit scalars of one buffer: with 64-bit addresses and a bin comparison
 // per entry the scalar unit, which a CU's four SIMDs share, set the time (174
 // scalar instructions a bin and wave at N = 1000).
 constexpr int FB8 = 8;
 
-template <typename T, bool TAU, bool STORE, bool FUSED, bool PART>
+template <typename T, int R, bool TAU, bool STORE, bool FUSED, bool PART>
 __global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ ent, const int32_t* __restrict__ off,
                                                  const T* __restrict__ Jt, const double* __restrict__ Dc,
                                                  const double* __restrict__ Vc, const double* __restrict__ C64,
@@ -369,8 +392,8 @@ __global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ en
                                                  double* __restrict__ rowpart, double* __restrict__ rowpartV,
                                                  RecFDims g) {
   const int lane = threadIdx.x & 63;
-  const uint32_t nib = (uint32_t)((g.N + 63) / 64);
-  const int i = (int)(blockIdx.x % nib) * 64 + lane;
+  const uint32_t nib = (uint32_t)((g.N + 64 * R - 1) / (64 * R));
+  const int i = ((int)(blockIdx.x % nib) * 64 + lane) * R;
   const int64_t sg = (int64_t)(blockIdx.x / nib) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (sg >= g.n_seg) return;
   const int64_t t0 = g.t0 + sg * g.seg;              // the segment's first bin
@@ -384,36 +407,51 @@ __global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ en
   const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(STORE ? W + (t0 - g.tw) * g.Np : nullptr), (short)0, STORE ? (int)(g.seg * pitch) : 0, 0x00020000);
   const double ag = g.a;
-  double D = 0.0, V = 0.0;
+  double D[R], V[R], sum[R], sumv[R], acc[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) D[k] = V[k] = sum[k] = sumv[k] = acc[k] = 0.0;
   if (FUSED) {
     const double* __restrict__ C = C64 + s0 * g.Np;
     const double* __restrict__ CY = CY64 + s0 * g.Np;
 #pragma unroll 8
     for (int j = 0; j < (int)g.N; ++j) {
-      const double w = (double)buf_load<T>(jr, voff, j * pitch);
-      D += w * C[j];
-      if (TAU) V += w * CY[j];
+      const Vals<T, R> w = buf_load_r<T, R>(jr, voff, j * pitch);
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        D[k] += (double)w.v[k] * C[j];
+        if (TAU) V[k] += (double)w.v[k] * CY[j];
+      }
     }
   } else {
-    D = Dc[(s0 / g.kc - g.row0) * g.Np + i];
-    if (TAU) V = Vc[(s0 / g.kc - g.row0) * g.Np + i];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      D[k] = Dc[(s0 / g.kc - g.row0) * g.Np + i + k];
+      if (TAU) V[k] = Vc[(s0 / g.kc - g.row0) * g.Np + i + k];
+    }
   }
-  double sum = 0.0, sumv = 0.0, acc = 0.0;
   int t = 0, wo = 0;  // bin, and offset of its row in W
   auto emit = [&]() {
     if (PART && t < skip) return;
-    const double lam = exp_f64(D);
-    sum += lam;
-    if (TAU) sumv += lam * V;
+    Vals<T, R> w;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const double lam = exp_f64(D[k]);
+      sum[k] += lam;
+      if (TAU) sumv[k] += lam * V[k];
+      w.v[k] = (T)lam;
+    }
     if (STORE) {
-      buf_store<T>((T)lam, wr, voff, wo);
+      buf_store_r<T, R>(w, wr, voff, wo);
       wo += pitch;
     }
   };
   auto step = [&]() {
-    if (TAU) V = ag * (V + g.ctau * D);
-    D = ag * D + acc;
-    acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      if (TAU) V[k] = ag * (V[k] + g.ctau * D[k]);
+      D[k] = ag * D[k] + acc[k];
+      acc[k] = 0.0;
+    }
     ++t;
     emit();
   };
@@ -423,10 +461,10 @@ __global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ en
     const int64_t s1 = (t0 + g.seg + 63) >> 6;
     const int e1 = off[s1 < g.NS ? s1 : g.NS];
     const uint32_t base = (uint32_t)(s0 * 64) & 0x7fffu;
-    auto row = [&](uint32_t q) { return buf_load<T>(jr, voff, (int)(q & 0xffffu) * pitch); };
+    auto row = [&](uint32_t q) { return buf_load_r<T, R>(jr, voff, (int)(q & 0xffffu) * pitch); };
     const uint32_t last = ENT_FIRST | ((((uint32_t)(tend - 1) + base) & 0x7fffu) << 16);
     uint32_t ec[FB8], en[FB8];
-    T rn[FB8];
+    Vals<T, R> rn[FB8];
     if (e0 < e1) {
 #pragma unroll
       for (int q = 0; q < FB8; ++q) ec[q] = ent[e0 + q];
@@ -448,7 +486,8 @@ __global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ en
           const int b = ent_bin(ec[q], base), to = b < tend - 1 ? b : tend - 1;
           while (t < to) step();
         }
-        acc += (double)rn[q];
+#pragma unroll
+        for (int k = 0; k < R; ++k) acc[k] += (double)rn[q].v[k];
         rn[q] = row(en[q]);
       }
 #pragma unroll
@@ -458,8 +497,11 @@ __global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ en
     }
     while (t < tend - 1) step();
   }
-  rowpart[(g.seg0 + sg) * g.Np + i] = sum;
-  if (TAU) rowpartV[(g.seg0 + sg) * g.Np + i] = sumv;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    rowpart[(g.seg0 + sg) * g.Np + i + k] = sum[k];
+    if (TAU) rowpartV[(g.seg0 + sg) * g.Np + i + k] = sumv[k];
+  }
 }
 
 // ------------------------------------------------------------------ forward, event grid
@@ -777,12 +819,25 @@ hipError_t rec_gather(const RecGArgs& a, hipStream_t st) {
 template <typename T, bool TAU, bool STORE, bool FUSED, bool PART>
 hipError_t rec_fwd_run(const RecFArgs& a, hipStream_t st) {
   const RecFDims& g = a.g;
-  const unsigned blocks = (unsigned)((g.N + 63) / 64 * ((g.n_seg + 3) / 4));
+  const int64_t nib = (g.N + 63) / 64, segs = (g.n_seg + 3) / 4;
+  const unsigned blocks = (unsigned)(nib * segs);
+  // Two rows a lane where J is in FP64, whose loads bound the kernel (from the
+  // L2, 8 bytes a lane; likelihood alone at N = 1000, 4e5 bins: 1431 us with
+  // one row, 990 with two; in FP32 873 and 867, the conversions bound it), and
+  // where at most one block of 64 rows in eight is padding.  Segments shorter
+  // than a subtile are those of recordings with too few waves.
+  if constexpr (sizeof(T) == 8 && !FUSED && !PART)
+    if (!a.edec && (nib % 2 == 0 || nib >= 7)) {
+      hipLaunchKernelGGL((k_rec_fwd<T, 2, TAU, STORE, false, false>), dim3((unsigned)((nib + 1) / 2 * segs)), dim3(256),
+                         0, st, a.ent1, a.off1, (const T*)a.Jt, a.Dc, a.Vc, a.C64, a.CY64, (T*)a.W, a.rowpart,
+                         a.rowpartV, g);
+      return hipGetLastError();
+    }
   if (a.edec)
     hipLaunchKernelGGL((k_rec_fwd_ev<T, STORE, FUSED, PART>), dim3(blocks), dim3(256), 0, st, a.ent1, a.off1,
                        (const T*)a.Jt, a.Dc, a.C64, a.edec, a.delta, (T*)a.W, a.rowpart, g);
   else
-    hipLaunchKernelGGL((k_rec_fwd<T, TAU, STORE, FUSED, PART>), dim3(blocks), dim3(256), 0, st, a.ent1, a.off1,
+    hipLaunchKernelGGL((k_rec_fwd<T, 1, TAU, STORE, FUSED, PART>), dim3(blocks), dim3(256), 0, st, a.ent1, a.off1,
                        (const T*)a.Jt, a.Dc, a.Vc, a.C64, a.CY64, (T*)a.W, a.rowpart, a.rowpartV, g);
   return hipGetLastError();
 }

@@ -81,6 +81,13 @@ def test_against_the_dense_contractions(N, B, density, kw, monkeypatch):
         assert np.max(np.abs(a - b)) <= 1e-11 * max(1.0, np.max(np.abs(b))), k
 
 
+@pytest.mark.parametrize("N,B,kw", [
+    (445, 38_000, {}), (1030, 16_500, dict(chunk_bins=8192)), (130, 100_001, {}), (257, 55_000, dict(chunk_bins=20480))])
+def test_two_rows_a_lane_against_the_dense_contractions(N, B, kw, monkeypatch):
+    """Segments of 64 bins and more: blocks of 128 rows at 7, 17, 3 and 5 blocks of 64 (the last two one row a lane)."""
+    test_against_the_dense_contractions(N, B, 0.007, kw, monkeypatch)
+
+
 @pytest.mark.parametrize("N,T,precision,kw", [
     (1, 1.0, "fp64", {}), (5, 3.0, "fp64", {}), (90, 6.0, "fp64", dict(chunk_bins=4096)), (150, 4.0, "fp32", {}),
     (70, 2.0, "fp64", dict(max_gap=0.0001)), (12, 5.0, "fp64", dict(tau=0.002))])
