@@ -731,6 +731,13 @@ __device__ __forceinline__ f32x16 mma_bf16(const i32x4& a, const i32x4& b, const
 //        fragments are read before this one ends;
 //   B's  fragment b of a k block is replaced by the next block's as soon as
 //        its MFMAs are issued.
+// With loads one step ahead, fragments copied at the end of a step and the
+// barrier there, kernel G took 3.50 instead of 3.16 ms a launch at N = 1000
+// (1.8e6 bins), kernel U of the two-term J 4.85 instead of 4.25 ms (1.2e6
+// bins) and the event grid's 2.46 instead of 2.23 ms (8.5e5 slots).  Kernel U
+// itself, 3.7 ms, is bound by its epilogue's stores of W (3.8 GB) and the
+// trace's reads (7.3 GB): without the stores it takes 2.8 ms, with the trace
+// from the L2 3.2 ms, without the exponentials still 3.7 ms.
 // BFRAG: B's 16 KB of a step are its 4 x 4 fragments in order (row block, k
 // block), else 128 rows of 128 bytes.  Acc element r of lane l of block (a, b)
 // is row 32 a + 8 (r / 4) + 4 (l / 32) + r % 4 of the wave's rows, column 32 b
