@@ -29,10 +29,10 @@
 // from the L2), half of it vector and scalar issue (20 of the instructions a
 // bin are the exponential, 7 a spike); k_rec_gather 3.1 ms, LDS reads and the
 // phases that form a tile.  The dense kernels took 56 and 58 ms.  On the event
-// grid (FP64): k_rec_fwd_ev 0.145 ms at N = 150, 6.6e4 slots and 2.1 ms at
-// N = 1000, 4.4e5 slots, the FP64 arithmetic of the integrals and, with four
-// waves a SIMD, its latency (written out per lane, with the closed forms as a
-// call: 0.47 and 5.2 ms).
+// grid (FP64): k_rec_fwd_ev 0.128 ms at N = 150, 6.6e4 slots and 4.2 us per
+// thousand slots at N = 1000, the FP64 arithmetic of the integrals and, with four
+// waves a SIMD, its latency (at N = 150 0.145 ms with one term more, 0.47 ms
+// written out per lane, with the closed forms as a call).
 #include <algorithm>
 
 #include "evfun.h"
@@ -508,9 +508,11 @@ __global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ en
 // The interval integrals F, H (evfun.h) of a slot of length delta, over p equal
 // pieces of length d = delta / p <= 1/16: the midpoint expansion holds where
 // d max(1, |u|) <= 0.25, so up to |u| = 4 for the longest pieces (p = 1 between
-// the events of a large network).  Its sums over k are polynomials of degree
-// 12 in u whose coefficients depend on the slot only: with S the Stirling
-// numbers of the second kind and c_k = d^2k / (4^k (2k+1)!),
+// the events of a large network).  Its sums over k, to k = 5 (at d = 1/16 and u
+// = 4, where the bound lets the terms be largest, the next one is 1.4e-17 of
+// the sum), are polynomials of degree 10 in u whose coefficients depend on the
+// slot only: with S the Stirling numbers of the second kind and c_k = d^2k /
+// (4^k (2k+1)!),
 //   F = d e^u sum_j u^j sum_k c_k S(2k, j),
 //   H = d e^{-d/2} e^u sum_j u^j sum_k c_k S(2k+1, j+1).
 // A wave forms those of 32 slots at a time, a slot a lane, in LDS; a step then
@@ -520,11 +522,14 @@ __global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ en
 // wave takes at nearly every slot of a small network, a thousand
 // instructions and, as a call, 247 registers.
 constexpr int EVS = 32;  // slots in LDS
-constexpr int EVC = 34;  // doubles a slot: F's 13 coefficients, H's, e^{-d/2}, e^{-d}, 0.25 / d, p, delta, decay, (pad)
+constexpr int EVK = 6;            // terms, k = 0 .. 5
+constexpr int EVJ = 2 * EVK - 1;  // coefficients of each polynomial
+constexpr int EVE = 2 * EVJ;      // then e^{-d/2}, e^{-d}, 0.25 / d, p, delta, decay
+constexpr int EVC = EVE + 8;      // doubles a slot (two of them padding)
 constexpr double kEvPiece = 1.0 / 16.0;
 
 struct EvStirling {
-  double f[7][13], h[7][13];  // S(2k, j), S(2k+1, j+1)
+  double f[EVK][EVJ], h[EVK][EVJ];  // S(2k, j), S(2k+1, j+1)
 };
 constexpr EvStirling ev_stirling() {
   double S[14][14] = {};
@@ -532,8 +537,8 @@ constexpr EvStirling ev_stirling() {
   for (int n = 1; n < 14; ++n)
     for (int k = 1; k <= n; ++k) S[n][k] = k * S[n - 1][k] + S[n - 1][k - 1];
   EvStirling e{};
-  for (int k = 0; k < 7; ++k)
-    for (int j = 0; j < 13; ++j) {
+  for (int k = 0; k < EVK; ++k)
+    for (int j = 0; j < EVJ; ++j) {
       e.f[k][j] = S[2 * k][j];
       e.h[k][j] = S[2 * k + 1][j + 1];
     }
@@ -545,26 +550,26 @@ __device__ __forceinline__ void ev_coefficients(double delta, double edec, doubl
   // past 16 pieces ev_rare is cheaper: one piece, out of its bound
   const double p = delta > kEvPiece && delta <= 1.0 ? __builtin_ceil(delta * (1.0 / kEvPiece)) : 1.0;
   const double d = delta / p, eh = exp_f64(-0.5 * d);
-  double c[7] = {1.0};
+  double c[EVK] = {1.0};
 #pragma unroll
-  for (int k = 1; k < 7; ++k) c[k] = c[k - 1] * (d * d) * (1.0 / (4.0 * (2 * k) * (2 * k + 1)));
+  for (int k = 1; k < EVK; ++k) c[k] = c[k - 1] * (d * d) * (1.0 / (4.0 * (2 * k) * (2 * k + 1)));
 #pragma unroll
-  for (int j = 0; j < 13; ++j) {
+  for (int j = 0; j < EVJ; ++j) {
     double f = 0.0, h = 0.0;
 #pragma unroll
-    for (int k = 6; k >= 0; --k) {
+    for (int k = EVK - 1; k >= 0; --k) {
       if (S.f[k][j] != 0.0) f = fma(c[k], S.f[k][j], f);
       if (S.h[k][j] != 0.0) h = fma(c[k], S.h[k][j], h);
     }
     o[j] = d * f;
-    o[13 + j] = d * eh * h;
+    o[EVJ + j] = d * eh * h;
   }
-  o[26] = eh;
-  o[27] = eh * eh;
-  o[28] = d > 0.0 ? 0.25 / d : 0.0;  // an empty slot's coefficients are zero: any u will do
-  o[29] = p;
-  o[30] = delta;
-  o[31] = edec;
+  o[EVE] = eh;
+  o[EVE + 1] = eh * eh;
+  o[EVE + 2] = d > 0.0 ? 0.25 / d : 0.0;  // an empty slot's coefficients are zero: any u will do
+  o[EVE + 3] = p;
+  o[EVE + 4] = delta;
+  o[EVE + 5] = edec;
 }
 
 // Past the bound of the staged pieces: the expansion over pieces of 0.25 / |D|
@@ -666,33 +671,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         if (lane < EVS) ev_coefficients(delta[s0 * 64 + t + lane], edec[s0 * 64 + t + lane], mine + lane * EVC);
         __builtin_amdgcn_wave_barrier();
       }
-      const double dec = mine[(t & (EVS - 1)) * EVC + 31];
+      const double dec = mine[(t & (EVS - 1)) * EVC + EVE + 5];
       if (!PART || t >= skip) {
         const double2* src = (const double2*)(mine + (t & (EVS - 1)) * EVC);
-        double c[32];
+        double c[EVE + 6];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
+        for (int v = 0; v < (EVE + 6) / 2; ++v) {
           const double2 x = src[v];
           c[2 * v] = x.x;
           c[2 * v + 1] = x.y;
         }
         double F = 0.0, H = 0.0, Dk = D, w = 1.0;
-        const int p = __builtin_amdgcn_readfirstlane((int)c[29]);
-        const bool out = c[28] > 0.0 && !(fmax(1.0, fabs(D * c[26])) <= c[28]);
+        const int p = __builtin_amdgcn_readfirstlane((int)c[EVE + 3]);
+        const bool out = c[EVE + 2] > 0.0 && !(fmax(1.0, fabs(D * c[EVE])) <= c[EVE + 2]);
         for (int k = 0; k < p; ++k) {
-          const double u = Dk * c[26], E = exp_f64(u);
-          double f = c[12], h = c[25];
+          const double u = Dk * c[EVE], E = exp_f64(u);
+          double f = c[EVJ - 1], h = c[2 * EVJ - 1];
 #pragma unroll
-          for (int v = 11; v >= 0; --v) {
+          for (int v = EVJ - 2; v >= 0; --v) {
             f = fma(f, u, c[v]);
-            h = fma(h, u, c[13 + v]);
+            h = fma(h, u, c[EVJ + v]);
           }
           F = fma(E, f, F);
           H = fma(w * E, h, H);
-          Dk *= c[27];
-          w *= c[27];
+          Dk *= c[EVE + 1];
+          w *= c[EVE + 1];
         }
-        if (out) ev_rare(D, c[30], &F, &H);
+        if (out) ev_rare(D, c[EVE + 4], &F, &H);
         sum += F;
         if (STORE) {
           buf_store<T>((T)H, wr, voff, wo);
