@@ -195,6 +195,12 @@ __global__ __launch_bounds__(GNT) void k_rec_gather(RecGArgs a) {
       }
     }
     double r = hx + Px * c;
+    // converted again and not kept as FP64 across the barrier: on the event grid
+    // that spilled 34 registers (kernel G 101 instead of 53 ms at N = 1000, one hour)
+    if constexpr (sizeof(WT) == 4) {
+#pragma unroll
+      for (int m = 0; m < 16; ++m) asm volatile("" : "+v"(wn[m]));
+    }
     double* dst = tile + tb * 16 * GI + il;
 #pragma unroll
     for (int m = 15; m >= 0; --m) {
