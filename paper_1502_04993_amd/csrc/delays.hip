@@ -7,7 +7,7 @@
 //  * The shared trace of all rows is that of the raster shifted by d: the
 //    spike-mask words are shifted by d bits across subtiles (k_shift_masks) and
 //    the carries, the resident trace and both contractions use the shifted
-//    masks unchanged.  The spike segments (and q) keep the recorded bins, so
+//    masks unchanged.  The recorded masks, their lists and q stay as they are, so
 //    the spike term walks the recorded spikes of i against the shifted trace.
 //  * With d_s != d the self term differs: U_i[t] needs J_ii x_i[t - d_s]
 //    instead of J_ii x_i[t - d].  After kernel U, k_self_delay multiplies
