@@ -1820,7 +1820,11 @@ glmr_status launch_chunk_groups(glmr_batch* b, size_t ci, bool want_u, bool want
 // L and the gradient of every recording at its current parameters.
 glmr_status batch_eval_core(glmr_batch* b) {
   if (!b->grouped) {
-    for (glmr_ctx* c : b->ctxs) TRY(eval_core(c, true, false));
+    for (glmr_ctx* c : b->ctxs) {
+      Outputs o;
+      o.host_rows = c->host_rows;  // the batch's totals are added up from them
+      TRY(eval_core(c, true, false, o));
+    }
     return GLMR_OK;
   }
   glmr_ctx* c0 = b->ctxs[0];
