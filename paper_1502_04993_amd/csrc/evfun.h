@@ -40,6 +40,8 @@
 
 #include <math.h>
 
+#include "fexp.h"
+
 #if defined(__HIPCC__)
 #define GLMR_HD __host__ __device__
 #else
@@ -223,6 +225,189 @@ inline void interval_long(double D, const Slot& q, double* F, double* H) {
 
 GLMR_HD inline void interval(double D, double delta, double* F, double* H) {
   interval(D, slot_consts(delta), F, H);
+}
+
+// The recurrence's evaluation in FP64 (recur.hip), from coefficients staged
+// per slot.  A slot of length delta is p equal pieces of length d = delta / p
+// <= 1/16: the midpoint expansion holds where d max(1, |u|) <= 0.25, so up to
+// |u| = 4 for the longest pieces (p = 1 between the events of a large network).
+// Its sums over k, to k = 5 (at d = 1/16 and u = 4, where the bound lets the
+// terms be largest, the next one is 1.4e-17 of the sum), are polynomials of
+// degree 10 in u whose coefficients depend on the slot only: with S the
+// Stirling numbers of the second kind and c_k = d^2k / (4^k (2k+1)!),
+//   F = d e^u sum_j u^j sum_k c_k S(2k, j),
+//   H = d e^{-d/2} e^u sum_j u^j sum_k c_k S(2k+1, j+1).
+constexpr int EVK = 6;            // terms, k = 0 .. 5
+constexpr int EVJ = 2 * EVK - 1;  // coefficients of each polynomial
+constexpr int EVE = 2 * EVJ;      // then e^{-d/2}, e^{-d}, 0.25 / d, p, delta, decay
+constexpr int EVC = EVE + 8;      // doubles a slot (two of them padding)
+constexpr double kEvPiece = 1.0 / 16.0;
+
+struct EvStirling {
+  double f[EVK][EVJ], h[EVK][EVJ];  // S(2k, j), S(2k+1, j+1)
+};
+constexpr EvStirling ev_stirling() {
+  double S[14][14] = {};
+  S[0][0] = 1.0;
+  for (int n = 1; n < 14; ++n)
+    for (int k = 1; k <= n; ++k) S[n][k] = k * S[n - 1][k] + S[n - 1][k - 1];
+  EvStirling e{};
+  for (int k = 0; k < EVK; ++k)
+    for (int j = 0; j < EVJ; ++j) {
+      e.f[k][j] = S[2 * k][j];
+      e.h[k][j] = S[2 * k + 1][j + 1];
+    }
+  return e;
+}
+
+// The slot's EVC doubles (edec: its decay e^{-delta}).
+GLMR_HD inline void stage_pieces(double delta, double edec, double* o) {
+  constexpr EvStirling S = ev_stirling();
+  // past 16 pieces interval_any is cheaper: one piece, out of its bound
+  const double p = delta > kEvPiece && delta <= 1.0 ? __builtin_ceil(delta * (1.0 / kEvPiece)) : 1.0;
+  const double d = delta / p, eh = exp_f64(-0.5 * d);
+  double c[EVK] = {1.0};
+#pragma unroll
+  for (int k = 1; k < EVK; ++k) c[k] = c[k - 1] * (d * d) * (1.0 / (4.0 * (2 * k) * (2 * k + 1)));
+#pragma unroll
+  for (int j = 0; j < EVJ; ++j) {
+    double f = 0.0, h = 0.0;
+#pragma unroll
+    for (int k = EVK - 1; k >= 0; --k) {
+      if (S.f[k][j] != 0.0) f = fma(c[k], S.f[k][j], f);
+      if (S.h[k][j] != 0.0) h = fma(c[k], S.h[k][j], h);
+    }
+    o[j] = d * f;
+    o[EVJ + j] = d * eh * h;
+  }
+  o[EVE] = eh;
+  o[EVE + 1] = eh * eh;
+  o[EVE + 2] = d > 0.0 ? 0.25 / d : 0.0;  // an empty slot's coefficients are zero: any u will do
+  o[EVE + 3] = p;
+  o[EVE + 4] = delta;
+  o[EVE + 5] = edec;
+}
+
+// F and H from a slot's coefficients and its number of pieces; returns whether
+// the expansion holds (else F and H are to be taken from interval_any).
+GLMR_HD inline bool interval_pieces(const double* c, int p, double D, double* F, double* H) {
+  const bool in = !(c[EVE + 2] > 0.0 && !(fmax(1.0, fabs(D * c[EVE])) <= c[EVE + 2]));
+  double sf = 0.0, sh = 0.0, w = 1.0;
+  for (int k = 0; k < p; ++k) {
+    const double u = D * c[EVE], E = exp_f64(u);
+    double f = c[EVJ - 1], h = c[2 * EVJ - 1];
+#pragma unroll
+    for (int v = EVJ - 2; v >= 0; --v) {
+      f = fma(f, u, c[v]);
+      h = fma(h, u, c[EVJ + v]);
+    }
+    sf = fma(E, f, sf);
+    sh = fma(w * E, h, sh);
+    D *= c[EVE + 1];
+    w *= c[EVE + 1];
+  }
+  *F = sf;
+  *H = sh;
+  return in;
+}
+
+// 1 - e^{-r}, without the cancellation for short r: r - r^2 / 2! + ...
+GLMR_HD inline double one_minus_exp(double r) {
+  if (!(r < 0.25)) return 1.0 - exp_f64(-r);
+  double q = 1.0;
+#pragma unroll 1
+  for (double n = 14.0; n >= 2.0; n -= 1.0) q = 1.0 - r / n * q;
+  return r * q;
+}
+
+// F and H of any interval and any potential, in a bounded number of steps and
+// without calls, so that a kernel keeps its registers.  Where |D| > 2 and
+// |D| delta <= 1, the most frequent, the short-interval branch over four pieces
+// of 0.25 / |D| at most (and one of what rounding leaves).  Else, with |u|
+// running from lo = |D| xi to hi = |D| over the interval:
+//  * where |u| <= 2 the series (of the last log(hi / 2) less of the interval)
+//      F = delta + e1 sum_{n>=1} D^n S_n / (n n!),  S_n = 1 + xi + ... + xi^{n-1};
+//  * where |u| >= 2 the integral of e^u / |u| by 16-point Gauss-Legendre over
+//    pieces no longer than 8 and than 1.5 times their nearer end to the pole
+//    (error below 1e-19), and only over the 40 units nearest to the integrand's
+//    largest value (the rest is below e^-40 of it): six pieces at most.
+// H is e^M (1 - e^{-|D| e1}) / |D| with M the larger of D and D xi, or where
+// |D| e1 <= 2 the series
+//   H = e^{D xi} e1 sum_{n>=0} (D e1)^n / (n+1)!.
+// Past D = 710 (e^D overflows) F is infinite, at D = -infinity both are zero.
+GLMR_HD inline void interval_any(double D, double delta, double* F, double* H) {
+  *F = *H = 0.0;
+  if (!(delta > 0.0) || D == -INFINITY) return;
+  if (!(D < INFINITY)) {
+    *F = *H = D;
+    return;
+  }
+  const double hi = fabs(D);
+  if (hi > 2.0 && hi * delta <= 1.0) {
+    double sf = 0.0, sh = 0.0, w = 1.0;
+#pragma unroll 1
+    for (int k = 0; k < 8 && delta > 0.0; ++k) {
+      const double d = fmin(delta, 0.25 / hi), eh = exp_f64(-0.5 * d);
+      double f, h;
+      (void)interval_short(D, slot_short(d, eh), &f, &h);
+      sf += f;
+      sh = fma(w, h, sh);
+      D *= eh * eh;
+      w *= eh * eh;
+      delta -= d;
+    }
+    *F = sf;
+    *H = sh;
+    return;
+  }
+  const double e1 = one_minus_exp(delta), xi = exp_f64(-delta);
+  const double lo = hi * xi, y = D * e1;
+  if (fabs(y) <= 2.0) {
+    double q = 1.0;
+#pragma unroll 1
+    for (double n = 26.0; n >= 2.0; n -= 1.0) q = fma(y / n, q, 1.0);
+    *H = exp_f64(D * xi) * e1 * q;
+  } else {
+    const double E = exp_f64(0.5 * fmax(D, D * xi));
+    *H = E * (E / hi * (1.0 - exp_f64(-fabs(y))));
+  }
+  if (D > 710.0) {
+    *F = INFINITY;
+    return;
+  }
+  double sf = 0.0;
+  if (lo < 2.0) {
+    const double r = hi > 2.0 ? fmax(delta - log(0.5 * hi), 0.0) : delta;
+    const double d = one_minus_exp(r), x = 1.0 - d, Dr = fmax(-2.0, fmin(D, 2.0));
+    double p = 1.0, S = 1.0, acc = 0.0;
+#pragma unroll 1
+    for (double n = 1.0; n <= 26.0; n += 1.0) {
+      const double g = 1.0 / n;
+      p *= Dr * g;                // D^n / n!
+      acc = fma(p * g, S, acc);   // D^n S_n / (n n!)
+      S = fma(x, S, 1.0);         // S_{n+1}
+    }
+    sf = fma(d, acc, r);
+  }
+  double a = fmax(lo, 2.0), len = lo < 2.0 ? hi - 2.0 : fabs(y);  // [a, a + len]
+  if (len > 40.0) {
+    if (D > 0.0) a = hi - 40.0;
+    len = 40.0;
+  }
+#pragma unroll 1
+  for (int k = 0; k < 8 && len > 0.0; ++k) {
+    const double w = fmin(len, fmin(8.0, 1.5 * a)), half = 0.5 * w, mid = a + half;
+    double s = 0.0;
+#pragma unroll 1
+    for (int n = 0; n < 8; ++n) {
+      const double x = gl16_node(n) * half, u1 = mid - x, u2 = mid + x;
+      s = fma(gl16_weight(n), exp_f64(copysign(u1, D)) / u1 + exp_f64(copysign(u2, D)) / u2, s);
+    }
+    sf = fma(half, s, sf);
+    a += w;
+    len -= w;
+  }
+  *F = sf;
 }
 
 // FP32 evaluation for the BF16 mode (whose potential D is an FP32 sum of

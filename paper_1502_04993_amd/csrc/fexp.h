@@ -1,4 +1,4 @@
-// exp in FP64 for the device's epilogues (gfx950): x = k ln 2 + r with
+// exp in FP64 for the device's epilogues (and, for tests, the host): x = k ln 2 + r with
 // |r| <= ln2 / 2 and e^r = 1 + r + r^2 q(r), q of degree 9 interpolating
 // (e^r - 1 - r) / r^2 at Chebyshev points (relative error 1.6e-17 before
 // rounding; about 1 ulp in all).  Overflow gives infinity, underflow 0
@@ -7,9 +7,15 @@
 // multiply-add, and selects for the special cases).
 #pragma once
 
+#if defined(__HIPCC__)
 #include <hip/hip_runtime.h>
+#define GLMR_EXP_FN __host__ __device__ __forceinline__
+#else
+#include <math.h>
+#define GLMR_EXP_FN inline
+#endif
 
-__device__ __forceinline__ double exp_f64(double x) {
+GLMR_EXP_FN double exp_f64(double x) {
   const double c = fmin(fmax(x, -1100.0), 1100.0);
   const double k = __builtin_rint(c * 1.44269504088896338700e+00);
   double r = fma(k, -6.93147180559945286227e-01, c);

@@ -36,7 +36,6 @@
 #include <algorithm>
 
 #include "evfun.h"
-#include "fexp.h"
 #include "gather.h"
 
 namespace {
@@ -511,118 +510,16 @@ __global__ __launch_bounds__(256) void k_rec_fwd(const uint32_t* __restrict__ en
 }
 
 // ------------------------------------------------------------------ forward, event grid
-// The interval integrals F, H (evfun.h) of a slot of length delta, over p equal
-// pieces of length d = delta / p <= 1/16: the midpoint expansion holds where
-// d max(1, |u|) <= 0.25, so up to |u| = 4 for the longest pieces (p = 1 between
-// the events of a large network).  Its sums over k, to k = 5 (at d = 1/16 and u
-// = 4, where the bound lets the terms be largest, the next one is 1.4e-17 of
-// the sum), are polynomials of degree 10 in u whose coefficients depend on the
-// slot only: with S the Stirling numbers of the second kind and c_k = d^2k /
-// (4^k (2k+1)!),
-//   F = d e^u sum_j u^j sum_k c_k S(2k, j),
-//   H = d e^{-d/2} e^u sum_j u^j sum_k c_k S(2k+1, j+1).
-// A wave forms those of 32 slots at a time, a slot a lane, in LDS; a step then
-// reads them at one address and takes an exponential and two Horner sums a
-// piece.  The expansion as written out per slot and lane took three times the
-// multiplications, and the closed forms past its bound, which some lane of a
-// wave takes at nearly every slot of a small network, a thousand
-// instructions and, as a call, 247 registers.
+// The interval integrals F, H of a slot by the staged expansion (evfun.h).  A
+// wave forms the coefficients of 32 slots at a time, a slot a lane, in LDS; a
+// step then reads them at one address and takes an exponential and two Horner
+// sums a piece.  The expansion as written out per slot and lane took three
+// times the multiplications, and the closed forms past its bound, which some
+// lane of a wave takes at nearly every slot of a small network, as a call 247
+// registers.
+using glmr_ev::EVC;
+using glmr_ev::EVE;
 constexpr int EVS = 32;  // slots in LDS
-constexpr int EVK = 6;            // terms, k = 0 .. 5
-constexpr int EVJ = 2 * EVK - 1;  // coefficients of each polynomial
-constexpr int EVE = 2 * EVJ;      // then e^{-d/2}, e^{-d}, 0.25 / d, p, delta, decay
-constexpr int EVC = EVE + 8;      // doubles a slot (two of them padding)
-constexpr double kEvPiece = 1.0 / 16.0;
-
-struct EvStirling {
-  double f[EVK][EVJ], h[EVK][EVJ];  // S(2k, j), S(2k+1, j+1)
-};
-constexpr EvStirling ev_stirling() {
-  double S[14][14] = {};
-  S[0][0] = 1.0;
-  for (int n = 1; n < 14; ++n)
-    for (int k = 1; k <= n; ++k) S[n][k] = k * S[n - 1][k] + S[n - 1][k - 1];
-  EvStirling e{};
-  for (int k = 0; k < EVK; ++k)
-    for (int j = 0; j < EVJ; ++j) {
-      e.f[k][j] = S[2 * k][j];
-      e.h[k][j] = S[2 * k + 1][j + 1];
-    }
-  return e;
-}
-
-__device__ __forceinline__ void ev_coefficients(double delta, double edec, double* o) {
-  constexpr EvStirling S = ev_stirling();
-  // past 16 pieces ev_rare is cheaper: one piece, out of its bound
-  const double p = delta > kEvPiece && delta <= 1.0 ? __builtin_ceil(delta * (1.0 / kEvPiece)) : 1.0;
-  const double d = delta / p, eh = exp_f64(-0.5 * d);
-  double c[EVK] = {1.0};
-#pragma unroll
-  for (int k = 1; k < EVK; ++k) c[k] = c[k - 1] * (d * d) * (1.0 / (4.0 * (2 * k) * (2 * k + 1)));
-#pragma unroll
-  for (int j = 0; j < EVJ; ++j) {
-    double f = 0.0, h = 0.0;
-#pragma unroll
-    for (int k = EVK - 1; k >= 0; --k) {
-      if (S.f[k][j] != 0.0) f = fma(c[k], S.f[k][j], f);
-      if (S.h[k][j] != 0.0) h = fma(c[k], S.h[k][j], h);
-    }
-    o[j] = d * f;
-    o[EVJ + j] = d * eh * h;
-  }
-  o[EVE] = eh;
-  o[EVE + 1] = eh * eh;
-  o[EVE + 2] = d > 0.0 ? 0.25 / d : 0.0;  // an empty slot's coefficients are zero: any u will do
-  o[EVE + 3] = p;
-  o[EVE + 4] = delta;
-  o[EVE + 5] = edec;
-}
-
-// Past the bound of the staged pieces: the expansion over pieces of 0.25 / |D|
-// until the potential has decayed to |D| <= 2 (4 (|D| - 2) of them), then the
-// series of the rest, of length delta and 1 - xi = e1:
-//   F = delta + e1 sum_{n>=1} D^n S_n / (n n!),  S_n = 1 + xi + ... + xi^{n-1},
-//   H = e^{D xi} e1 sum_{n>=0} (D e1)^n / (n+1)!.
-// No call, so that the kernel keeps its registers.
-__device__ __forceinline__ void ev_rare(double D, double delta, double* F, double* H) {
-  double sf = 0.0, sh = 0.0, w = 1.0;
-#pragma unroll 1
-  while (fabs(D) > 2.0 && delta > 0.0) {
-    const double d = fmin(delta, 0.25 / fabs(D)), eh = exp_f64(-0.5 * d);
-    double f, h;
-    (void)glmr_ev::interval_short(D, glmr_ev::slot_short(d, eh), &f, &h);
-    sf += f;
-    sh = fma(w, h, sh);
-    D *= eh * eh;
-    w *= eh * eh;
-    delta -= d;
-  }
-  if (delta > 0.0) {
-    double e1 = 1.0 - exp_f64(-delta);
-    if (delta < 0.25) {  // without the cancellation: delta - delta^2 / 2! + ...
-      double q = 1.0;
-#pragma unroll 1
-      for (double n = 14.0; n >= 2.0; n -= 1.0) q = 1.0 - delta / n * q;
-      e1 = delta * q;
-    }
-    const double xi = 1.0 - e1, y = D * e1;
-    double p = 1.0, S = 1.0, acc = 0.0;
-#pragma unroll 1
-    for (double n = 1.0; n <= 26.0; n += 1.0) {
-      const double r = 1.0 / n;
-      p *= D * r;                 // D^n / n!
-      acc = fma(p * r, S, acc);   // D^n S_n / (n n!)
-      S = fma(xi, S, 1.0);        // S_{n+1}
-    }
-    double q = 1.0;
-#pragma unroll 1
-    for (double n = 26.0; n >= 2.0; n -= 1.0) q = fma(y / n, q, 1.0);
-    sf += fma(e1, acc, delta);
-    sh = fma(w * exp_f64(D * xi), e1 * q, sh);
-  }
-  *F = sf;
-  *H = sh;
-}
 
 template <typename T, bool STORE, bool FUSED, bool PART>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_rec_fwd_ev(
@@ -674,7 +571,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     for (int t = 0;;) {
       if ((t & (EVS - 1)) == 0) {  // a wave's LDS operations are in order: no barrier
         __builtin_amdgcn_wave_barrier();
-        if (lane < EVS) ev_coefficients(delta[s0 * 64 + t + lane], edec[s0 * 64 + t + lane], mine + lane * EVC);
+        if (lane < EVS) glmr_ev::stage_pieces(delta[s0 * 64 + t + lane], edec[s0 * 64 + t + lane], mine + lane * EVC);
         __builtin_amdgcn_wave_barrier();
       }
       const double dec = mine[(t & (EVS - 1)) * EVC + EVE + 5];
@@ -687,23 +584,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
           c[2 * v] = x.x;
           c[2 * v + 1] = x.y;
         }
-        double F = 0.0, H = 0.0, Dk = D, w = 1.0;
+        double F, H;
         const int p = __builtin_amdgcn_readfirstlane((int)c[EVE + 3]);
-        const bool out = c[EVE + 2] > 0.0 && !(fmax(1.0, fabs(D * c[EVE])) <= c[EVE + 2]);
-        for (int k = 0; k < p; ++k) {
-          const double u = Dk * c[EVE], E = exp_f64(u);
-          double f = c[EVJ - 1], h = c[2 * EVJ - 1];
-#pragma unroll
-          for (int v = EVJ - 2; v >= 0; --v) {
-            f = fma(f, u, c[v]);
-            h = fma(h, u, c[EVJ + v]);
-          }
-          F = fma(E, f, F);
-          H = fma(w * E, h, H);
-          Dk *= c[EVE + 1];
-          w *= c[EVE + 1];
-        }
-        if (out) ev_rare(D, c[EVE + 4], &F, &H);
+        const bool out = !glmr_ev::interval_pieces(c, p, D, &F, &H);
+        if (out) glmr_ev::interval_any(D, c[EVE + 4], &F, &H);
         sum += F;
         if (STORE) {
           buf_store<T>((T)H, wr, voff, wo);
