@@ -282,7 +282,7 @@ GLMR_HD inline void stage_pieces(double delta, double edec, double* o) {
   }
   o[EVE] = eh;
   o[EVE + 1] = eh * eh;
-  o[EVE + 2] = d > 0.0 ? 0.25 / d : 0.0;  // an empty slot's coefficients are zero: any u will do
+  o[EVE + 2] = d > 0.0 ? 0.25 / d : 700.0;  // an empty slot's coefficients are zero, so e^u has to be finite
   o[EVE + 3] = p;
   o[EVE + 4] = delta;
   o[EVE + 5] = edec;
@@ -291,7 +291,7 @@ GLMR_HD inline void stage_pieces(double delta, double edec, double* o) {
 // F and H from a slot's coefficients and its number of pieces; returns whether
 // the expansion holds (else F and H are to be taken from interval_any).
 GLMR_HD inline bool interval_pieces(const double* c, int p, double D, double* F, double* H) {
-  const bool in = !(c[EVE + 2] > 0.0 && !(fmax(1.0, fabs(D * c[EVE])) <= c[EVE + 2]));
+  const bool in = fmax(1.0, fabs(D * c[EVE])) <= c[EVE + 2];
   double sf = 0.0, sh = 0.0, w = 1.0;
   for (int k = 0; k < p; ++k) {
     const double u = D * c[EVE], E = exp_f64(u);

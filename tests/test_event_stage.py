@@ -65,7 +65,7 @@ import test_event_stage as T
 big = np.concatenate([10.0 ** np.arange(-300, 301, 10), [2.0, 7.0, 30.0, 700.0, 709.9, 711.0, 745.0, 760.0, 1e3, 1e5, 1e6, 1e15, 1e16,
                       1e18, 1.7e308, np.inf]])
 D, delta = (v.ravel() for v in np.meshgrid(np.concatenate([big, -big, [0.0, np.nan]]),
-                                           [1e-18, 1e-9, 1e-3, 0.1, 0.25, 1.0, 3.0, 40.0, 600.0, 800.0]))
+                                           [0.0, 1e-18, 1e-9, 1e-3, 0.1, 0.25, 1.0, 3.0, 40.0, 600.0, 800.0]))
 np.savez(%r, D=D, delta=delta, any=T.call(%r, "ev_any", D, delta)[:2], slot=T.call(%r, "ev_slot", D, delta)[:2])
 """
 
@@ -79,7 +79,9 @@ def test_huge_infinite_and_undefined_potentials(lib, tmp_path):
     for F, H in (r["any"], r["slot"]):
         for k in range(D.size):
             at = (D[k], delta[k], F[k], H[k])
-            if np.isnan(D[k]):
+            if delta[k] == 0.0:
+                assert np.isnan(D[k]) or np.isinf(D[k]) or F[k] == H[k] == 0.0, at
+            elif np.isnan(D[k]):
                 assert np.isnan(F[k]) and np.isnan(H[k]), at
             elif D[k] > 720.0 + 20.0 * delta[k]:  # e^D over the interval's first 20th overflows
                 assert F[k] == H[k] == np.inf, at

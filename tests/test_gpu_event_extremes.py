@@ -68,3 +68,29 @@ def test_not_finite(precision, monkeypatch):
     again = c.eval(grad=True)
     assert again["ll"] == ok["ll"] and np.array_equal(again["gJ"], ok["gJ"])
     c.close()
+
+
+def test_empty_slot_between_tied_events(monkeypatch):
+    """Between two events at one time the potential may be past e^709, over no time at all."""
+    N, T = 6, 1.0
+    times, neu = events(N, T, 6)
+    J, mu = params(N, 6)
+    at = np.searchsorted(times, 0.5)
+    times = np.insert(times, at, [0.5, 0.5])
+    neu = np.insert(neu, at, [1, 2]).astype(np.int32)
+    J[0, 1], J[0, 2] = 1024.0, -1024.0
+    mask = (neu != 1) & (neu != 2)
+    mask[at:at + 2] = True
+    extra = np.array([0.9, 0.9])  # 1 and 2 spike in pairs only
+    times, neu = np.append(times[mask], extra), np.append(neu[mask], [1, 2]).astype(np.int32)
+    order = np.lexsort((neu, times))
+    times, neu = times[order], neu[order]
+    out = []
+    for mode in "01":
+        c = context(N, T, times, neu, "fp64", mode, monkeypatch)
+        c.set_params(J, mu)
+        out.append(c.eval(grad=True))
+        c.close()
+    for k in ("ll", "gJ", "gmu"):
+        a, b = np.asarray(out[1][k]), np.asarray(out[0][k])
+        assert np.all(np.isfinite(b)) and np.max(np.abs(a - b)) <= 1e-11 * max(1.0, np.max(np.abs(b))), k
