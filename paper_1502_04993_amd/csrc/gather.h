@@ -87,12 +87,19 @@ __device__ __forceinline__ void walk(Cols (&acc)[JB], uint32_t col, uint32_t& p,
 }
 
 // The window's entries of a workgroup's neurons, groups base .. base + n - 1,
-// pass through LDS in pieces of CAP (one piece up to 3 spikes a neuron and
-// second in 1 ms bins at 1024 neurons).  The first piece is copied with the
+// pass through LDS in pieces of CAP (one piece for three groups a neuron and
+// window at 1024 neurons, about 10 spikes a second in 1 ms bins).  The first piece is copied with the
 // tile, before its barrier; every thread of the workgroup calls both.
 __device__ __forceinline__ void stage_entries(uint2* es, const uint2* __restrict__ ent, int base, int n) {
   n = n < CAP ? n : CAP;
   for (int q = threadIdx.x; q <= n; q += GNT) es[q] = ent[base + q];  // one past the end is loaded ahead
+}
+
+// Address of the end of a neuron's list in the piece staged at e8; end: in
+// groups from the piece's first.  A list that ended in an earlier piece ends
+// here at the piece's start (its end, below zero, must not wrap around).
+__host__ __device__ __forceinline__ uint32_t piece_end(uint32_t e8, int end) {
+  return e8 + 8 * (uint32_t)(end < 0 ? 0 : end < CAP ? end : CAP);
 }
 
 template <int JB>
@@ -109,10 +116,9 @@ __device__ __forceinline__ void gather_lists(Cols (&acc)[JB], double* lds, const
       __syncthreads();
     }
     if (rows && p >= q0 && p < q0 + CAP) {  // a group that is done stays where its lists ended
-      const int e1 = e.end - base - q0;
       uint32_t pl = e8 + 8 * (p - q0);
       u32x2 nx = *(lds_u32x2*)pl;
-      walk<0, JB>(acc, col, pl, nx, e8 + 8 * (e1 < CAP ? e1 : CAP), e8 + 8 * CAP);
+      walk<0, JB>(acc, col, pl, nx, piece_end(e8, e.end - base - q0), e8 + 8 * CAP);
       p = q0 + (int)(pl - e8) / 8;
     }
   }
