@@ -26,7 +26,7 @@
 //
 // What bounds it (N = 1000, 1.2e6 bins, 7.7e6 spikes, one evaluation with the
 // gradient): k_rec_fwd 2.5 ms (FP32) and 2.9 ms (FP64: twice the bytes of J
-// from the L2), half of it vector and scalar issue (20 of the instructions a
+// from the L2), half of it vector and scalar issue (21 of the instructions a
 // bin are the exponential, 7 a spike); k_rec_gather 3.1 ms, LDS reads and the
 // phases that form a tile.  The dense kernels took 56 and 58 ms.  On the event
 // grid (FP64): k_rec_fwd_ev 0.128 ms at N = 150, 6.6e4 slots and 4.2 us per

@@ -98,3 +98,11 @@ def test_exponential(lib):
     y = np.empty_like(x)
     ctypes.CDLL(lib).ev_exp(x.size, x.ctypes.data_as(ctypes.c_void_p), y.ctypes.data_as(ctypes.c_void_p))
     assert np.max(np.abs(y - np.exp(x)) / np.spacing(np.exp(x))) <= 2.0  # about 1 ulp each
+
+
+def test_exponential_of_infinities(lib):
+    x = np.array([-np.inf, -1.7e308, -1e5, -746.0, 0.0, 710.0, 1e5, 1.7e308, np.inf, np.nan, -np.nan])
+    y = np.empty_like(x)
+    ctypes.CDLL(lib).ev_exp(x.size, x.ctypes.data_as(ctypes.c_void_p), y.ctypes.data_as(ctypes.c_void_p))
+    with np.errstate(over="ignore"):
+        assert np.array_equal(y, np.exp(x), equal_nan=True)
