@@ -78,12 +78,13 @@ typedef enum {
 typedef enum {
   GLMR_FP64 = 0, /* trace, J, U, lambda in FP64: the potentials by the trace's
                     recurrence over the spikes of each bin, or on the FP64 MFMA
-                    (rasters of more than 0.12 N + 40 spikes a bin, a self-delay
-                    other than d, more than 8192 neurons) */
-  GLMR_FP32 = 1, /* J and the weights lambda in FP32; by the recurrence the rest
-                    in FP64, on the MFMA (as for FP64) with the trace in FP32
-                    too (rounded stochastically), both contractions on the FP64
-                    MFMA; exp and lambda sums in FP64 */
+                    (rasters of more than 0.12 N + 40 spikes a bin, or without
+                    a gradient 0.03 N + 220, a self-delay other than d, more
+                    than 8192 neurons) */
+  GLMR_FP32 = 1, /* J and the weights lambda in FP32; by the recurrence (to 0.12 N
+                    + 40 spikes a bin) the rest in FP64, on the MFMA with the
+                    trace in FP32 too (rounded stochastically), both contractions
+                    on the FP64 MFMA; exp and lambda sums in FP64 */
   GLMR_BF16 = 2, /* trace, J and lambda in BF16 (trace rounded stochastically),
                     MFMA with FP32 accumulation */
   GLMR_FP8 = 3,  /* trace, J and lambda in OCP e4m3 with power-of-two scales,

@@ -485,18 +485,30 @@ bool want_resident(glmr_ctx* c) {
 }
 
 // Whether the FP64 and FP32 modes evaluate by the recurrence on the spike
-// lists (recur.hip) instead of the dense contractions.  Its time grows with
-// the spikes of a bin, theirs hardly: at N = 1000, 1e5 bins (FP32 / FP64, ms)
-// 0.75 / 0.96 against 9.7 / 9.5 with 7 spikes a bin, 9.0 / 11 against
-// 18 / 17 with 100, 26 / 30 against 25 / 24 with 200; at N = 200, 4e5 bins
-// 4.9 / 6.4 against 9.3 / 9.0 even with 80; at N = 30 it is ahead for every
-// raster.  The event grid has at most one spike a slot.
-constexpr double kRecDensity = 0.12, kRecSpikes = 40.0;
-bool use_rec(const glmr_ctx* c) {
+// lists (recur.hip) instead of the dense contractions; grad: with a gradient
+// (of any kind).  The recurrence's time grows faster with the spikes of a bin
+// than theirs.  Gradient (likelihood alone), ms, dense against recurrence, at
+// the limit of 0.12 N + 40 spikes a bin:
+//   N       spikes/bin  bins    FP32                         FP64
+//     64      48        2e5     2.3 / 0.73 (0.72 / 0.39)     2.2 / 1.0 (0.72 / 0.64)
+//    200      64        2e5     5.1 / 2.0 (1.9 / 0.84)       5.0 / 2.1 (1.9 / 0.89)
+//   1000     160        5e4     13.2 / 7.7 (5.5 / 2.1)       13.0 / 8.0 (5.7 / 2.4)
+//   2000     280        2e4     18.7 / 9.6 (7.5 / 2.8)       18.1 / 10.0 (7.5 / 3.1)
+//   4000     520        8192    28.7 / 19.3 (11.6 / 9.3)     28.0 / 24.4 (11.7 / 14.4)
+//   8000    1000        4096    56.4 / 36.7 (22.7 / 18.1)    54.9 / 53.9 (22.8 / 35.6)
+// (past it at N = 1000, 200 spikes a bin, 1e5 bins: 28.6 / 21.0 and 27.8 / 22.0).
+// Beyond N = 2000 the rows of J^T in FP64 no longer come from the L2, and the
+// likelihood alone is even at N = 2500 and 300 spikes a bin (8.8 / 8.9), at N =
+// 4000 and 364 (10.3 / 10.2) and at N = 8000 and 500 (18.5 / 18.2): hence its
+// own limit of 0.03 N + 220 there.  The event grid has at most one spike a slot.
+bool use_rec(const glmr_ctx* c, bool grad) {
   if ((c->prec != PREC_F64 && c->prec != PREC_F32) || !c->have_spikes || self_delayed(c) || c->rec_mode == 0 ||
       c->Np > 8192)  // row offsets into J are 32-bit
     return false;
-  return c->rec_mode == 1 || (double)c->nspk <= (kRecDensity * (double)c->N + kRecSpikes) * (double)c->B;
+  const double N = (double)c->N;
+  double most = 0.12 * N + 40.0;
+  if (c->prec == PREC_F64 && !grad) most = std::min(most, 0.03 * N + 220.0);
+  return c->rec_mode == 1 || (double)c->nspk <= most * (double)c->B;
 }
 
 // Bins of a segment of the recurrence: the longest that leaves 16 waves a
@@ -789,7 +801,7 @@ glmr_status ensure_workspace(glmr_ctx* c, bool want_grad, bool want_tau) {
   if (want_tau) s.want(c->rowpartV, tiles * Np);
   if (self_delayed(c)) s.want(c->gpart, tiles * Np);
   if (want_grad) s.want((unsigned char*&)c->Gp, (size_t)c->max_splits * Np * Np * (fp ? 8 : 4));
-  if (use_rec(c) && want_grad) s.want(c->rec_head, (size_t)c->max_splits * Np);
+  if (use_rec(c, true) && want_grad) s.want(c->rec_head, (size_t)c->max_splits * Np);
   unsigned char* mem = nullptr;
   glmr_status st = s.get(c, &mem);
   if (st != GLMR_OK) {
@@ -799,7 +811,7 @@ glmr_status ensure_workspace(glmr_ctx* c, bool want_grad, bool want_tau) {
   if (mem) c->slabs.push_back(mem);
   // the others
   Slab o;
-  if (use_rec(c)) {
+  if (use_rec(c, true)) {
     const size_t rows = (size_t)(c->NS / std::max<int64_t>(1, seg / 64) + 1);
     o.want(c->rec_Dc, rows * Np);
     if (want_tau) o.want(c->rec_Vc, rows * Np);
@@ -1024,7 +1036,7 @@ struct Outputs {  // what the assembly writes besides the context's own (nullabl
   double* host_rows = nullptr;
 };
 AssembleArgs make_assemble_args(glmr_ctx* c, bool want_grad, bool want_tau, int64_t n_tiles, const Outputs& o);
-glmr_status prepare_params(glmr_ctx* c, const double* J = nullptr, const double* mu = nullptr);
+glmr_status prepare_params(glmr_ctx* c, const double* J = nullptr, const double* mu = nullptr, bool grad = true);
 
 // One evaluation by the recurrence: the whole recording at once for the
 // likelihood alone, in chunks of W's length with the gradient.
@@ -1103,7 +1115,8 @@ glmr_status eval_core(glmr_ctx* c, bool want_grad, bool want_tau, const Outputs&
   TRY(ensure_workspace(c, want_grad, want_tau));
   const int64_t Np = c->Np;
   if (c->prec == PREC_F64 || c->prec == PREC_F32) {
-    if (use_rec(c) != c->jc_rec) TRY(prepare_params(c));  // the weights were staged for the other path
+    const bool grad = want_grad || want_tau;
+    if (use_rec(c, grad) != c->jc_rec) TRY(prepare_params(c, nullptr, nullptr, grad));  // staged for the other path
     if (c->jc_rec) return eval_rec(c, want_grad, want_tau, o);
   }
   for (int64_t t0 = 0, ci = 0; t0 < c->Bp; t0 += c->L, ++ci) {
@@ -1241,11 +1254,11 @@ double total_of_rows(const glmr_ctx* c, int which) {
 }
 
 // Stages the parameters for the contractions: the context's own, or dense J and
-// mu, which the context then holds.
-glmr_status prepare_params(glmr_ctx* c, const double* J, const double* mu) {
+// mu, which the context then holds; for evaluations with a gradient, or without.
+glmr_status prepare_params(glmr_ctx* c, const double* J, const double* mu, bool grad) {
   ProfScope ps(c, K_PREP);
   if (c->prec == PREC_FP8 && !c->jscale) TRY(dalloc(c, c->jscale, (size_t)c->Np));
-  c->jc_rec = use_rec(c);
+  c->jc_rec = use_rec(c, grad);
   // pinned host memory is read once, by rows (in the staging kernel's tiles: 27 us against 22 at N = 50)
   if (J && (!c->jc_rec || J == c->pin)) {
     HIPCHK(c, launch_load_params(c->N, c->Np, J, mu, c->J64, c->mu, c->st));
