@@ -2776,6 +2776,7 @@ glmr_status glmr_set_precision(glmr_ctx* c, int32_t precision) {
     c->Jc = p;
   }
   if (c->have_kernel) TRY(build_kernel_caches(c, c->have_y));
+  else if (c->have_spikes && c->C64) TRY(ensure_lists(c, nullptr));  // a set-up without allocation may come next
   if (c->have_params) TRY(prepare_params(c));
   HIPCHK(c, hipStreamSynchronize(c->st));
   return GLMR_OK;
