@@ -402,8 +402,10 @@ struct GpReduceArgs {     // FP32 partials of one recording
   int64_t n;
   int n_splits, first;    // first: G64 is set, else added to
 };
-// list: device array of n_rec (the largest n is max_n), or null: `one`
-hipError_t launch_gp_reduce_group(const GpReduceArgs* list, const GpReduceArgs& one, int n_rec, int64_t max_n,
+// workgroups of a recording's reduction
+int64_t gp_reduce_blocks(int64_t n, int n_splits);
+// list: device array of n_rec (the most workgroups of one is blocks), or null: `one`
+hipError_t launch_gp_reduce_group(const GpReduceArgs* list, const GpReduceArgs& one, int n_rec, int64_t blocks,
                                   hipStream_t st);
 struct AssembleArgs {
   int N;

@@ -34,19 +34,24 @@ __device__ double block_sum(double v, double* sh) {
   return r;
 }
 
-// The FP32 partials of kernel G: 64 x 4 consecutive entries a workgroup, each
-// by four threads that take a quarter of the splits (in order; the quarters are
-// then added in order) with eight 16-byte loads in flight.  HBM- or
-// MALL-bound: 268 MB (N = 500, 256 splits) in a third of the time that one
-// thread an entry, walking all splits, took (117 us).  One launch serves the
-// recordings of a batch (blockIdx.y).
+// The FP32 partials of kernel G, 16-byte loads (four entries).  Many splits:
+// 64 fours a workgroup, each by four threads that take a quarter of the splits
+// (in order; the quarters are then added in order) with eight loads in flight.
+// HBM- or MALL-bound: 268 MB (N = 500, 256 splits) in a third of the time that
+// one thread a four, walking all splits, took (117 us).  Up to GP_FEW splits
+// (short recordings) one thread a four: N = 6000 and one split 129 against 254
+// us, N = 4000 85 against 110 with four splits, 175 against 178 with eight.
+// One launch serves the recordings of a batch (blockIdx.y).
+constexpr int GP_FEW = 8;
+__host__ __device__ inline int64_t gp_per_block(int n_splits) { return n_splits <= GP_FEW ? 256 : 64; }
 __global__ __launch_bounds__(256) void k_gp_reduce_f(const GpReduceArgs* __restrict__ list, GpReduceArgs one) {
   __shared__ double4 part[3][64];
   const GpReduceArgs a = list ? list[blockIdx.y] : one;
-  const int tx = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int64_t k = (int64_t)blockIdx.x * 64 + tx, n4 = a.n / 4;
+  const bool few = a.n_splits <= GP_FEW;
+  const int tx = few ? threadIdx.x : threadIdx.x & 63, q = few ? 0 : threadIdx.x >> 6;
+  const int64_t k = (int64_t)blockIdx.x * gp_per_block(a.n_splits) + tx, n4 = a.n / 4;
   const bool in = k < n4;
-  const int per = (a.n_splits + 3) / 4, s0 = q * per, s1 = s0 + per < a.n_splits ? s0 + per : a.n_splits;
+  const int per = few ? a.n_splits : (a.n_splits + 3) / 4, s0 = q * per, s1 = s0 + per < a.n_splits ? s0 + per : a.n_splits;
   double4 v{0.0, 0.0, 0.0, 0.0};
   if (in) {
     const float4* __restrict__ src = (const float4*)a.Gp + k;
@@ -59,18 +64,22 @@ __global__ __launch_bounds__(256) void k_gp_reduce_f(const GpReduceArgs* __restr
       v.w += (double)p.w;
     }
   }
-  if (q) part[q - 1][tx] = v;
-  __syncthreads();
+  if (!few) {
+    if (q) part[q - 1][tx] = v;
+    __syncthreads();
+  }
   if (q || !in) return;
   double4 g{0.0, 0.0, 0.0, 0.0};
   if (!a.first) g = ((const double4*)a.G64)[k];
+  if (!few) {
 #pragma unroll
-  for (int r = 0; r < 3; ++r) {
-    const double4 o = part[r][tx];
-    v.x += o.x;
-    v.y += o.y;
-    v.z += o.z;
-    v.w += o.w;
+    for (int r = 0; r < 3; ++r) {
+      const double4 o = part[r][tx];
+      v.x += o.x;
+      v.y += o.y;
+      v.z += o.z;
+      v.w += o.w;
+    }
   }
   ((double4*)a.G64)[k] = double4{g.x + v.x, g.y + v.y, g.z + v.z, g.w + v.w};
 }
@@ -567,6 +576,11 @@ int grid_for(int64_t n, int threads) {
 
 }  // namespace
 
+int64_t gp_reduce_blocks(int64_t n, int n_splits) {
+  const int64_t per = gp_per_block(n_splits);
+  return (n / 4 + per - 1) / per;
+}
+
 hipError_t launch_gp_reduce(int prec, const void* Gp, int n_splits, int64_t Np, double* G64,
                             int first, hipStream_t st) {
   const int64_t n = Np * Np;
@@ -575,13 +589,12 @@ hipError_t launch_gp_reduce(int prec, const void* Gp, int n_splits, int64_t Np, 
                        n_splits, n, G64, first);
     return hipGetLastError();
   }
-  return launch_gp_reduce_group(nullptr, GpReduceArgs{Gp, G64, n, n_splits, first}, 1, n, st);
+  return launch_gp_reduce_group(nullptr, GpReduceArgs{Gp, G64, n, n_splits, first}, 1, gp_reduce_blocks(n, n_splits), st);
 }
 
-hipError_t launch_gp_reduce_group(const GpReduceArgs* list, const GpReduceArgs& one, int n_rec, int64_t max_n,
+hipError_t launch_gp_reduce_group(const GpReduceArgs* list, const GpReduceArgs& one, int n_rec, int64_t blocks,
                                   hipStream_t st) {
-  hipLaunchKernelGGL(k_gp_reduce_f, dim3((unsigned)((max_n / 4 + 63) / 64), (unsigned)n_rec), dim3(256), 0, st, list,
-                     one);
+  hipLaunchKernelGGL(k_gp_reduce_f, dim3((unsigned)blocks, (unsigned)n_rec), dim3(256), 0, st, list, one);
   return hipGetLastError();
 }
 

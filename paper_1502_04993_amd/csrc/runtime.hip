@@ -1650,7 +1650,7 @@ struct glmr_batch {
     std::vector<Queue> u, g;
     size_t red = 0;      // their GpReduceArgs
     int n_red = 0;
-    int64_t max_n = 0;
+    int64_t red_blocks = 0;
   };
   std::vector<Chunk> chunks;
   size_t asm_args = 0;   // every recording's AssembleArgs
@@ -1758,7 +1758,7 @@ glmr_status build_queues(glmr_batch* b) {
         g.ga.push_back(ga);
         g.pre.push_back(g.pre.back() + (int64_t)ga.n_splits * ga.n_itiles * ga.n_jtiles);
         red.push_back(GpReduceArgs{c->Gp, c->G64, c->Np * c->Np, ga.n_splits, ci == 0 ? 1 : 0});
-        ch.max_n = std::max(ch.max_n, c->Np * c->Np);
+        ch.red_blocks = std::max(ch.red_blocks, gp_reduce_blocks(c->Np * c->Np, ga.n_splits));
       }
       ch.red = put(red.data(), red.size() * sizeof(GpReduceArgs));
       ch.n_red = (int)red.size();
@@ -1845,7 +1845,7 @@ glmr_status batch_eval_core(glmr_batch* b) {
     TRY(launch_chunk_groups(b, ci, true, true));
     const glmr_batch::Chunk& ch = b->chunks[ci];
     ProfScope ps(c0, K_RED);
-    HIPCHK(c0, launch_gp_reduce_group((const GpReduceArgs*)(b->dev_mem + ch.red), GpReduceArgs{}, ch.n_red, ch.max_n, b->st));
+    HIPCHK(c0, launch_gp_reduce_group((const GpReduceArgs*)(b->dev_mem + ch.red), GpReduceArgs{}, ch.n_red, ch.red_blocks, b->st));
   }
   ProfScope ps(c0, K_ASM);
   HIPCHK(c0, launch_finish((const AssembleArgs*)(b->dev_mem + b->asm_args), AssembleArgs{}, (int)b->ctxs.size(),
