@@ -149,6 +149,7 @@ struct glmr_ctx {
   // evaluation workspace, in slabs: those of the precision, and the others
   std::vector<unsigned char*> slabs;
   size_t w_bytes = 0, w_temps = 0;  // bytes of W; of them taken by temporaries
+  size_t gp_bytes = 0, gp_temps = 0;  // the same of Gp
   void* W = nullptr;
   void* Gp = nullptr;
   int max_splits = 0;
@@ -251,32 +252,38 @@ struct Arena {
   size_t cap = 0, used = 0;
 };
 
-// Temporaries of a set-up outside the no-allocation entry point: W's memory
-// where the context has it (nothing is kept in W between evaluations, and the
-// stream orders the set-up after the one that last used it), else hipMalloc.
-// They nest: an inner set-up takes what the outer one has left.
+// Temporaries of a set-up outside the no-allocation entry point: W's or Gp's
+// memory where the context has it (nothing is kept in them between evaluations,
+// and the stream orders the set-up after the one that last used them), else
+// hipMalloc.  They nest: an inner set-up takes what the outer one has left.
+// (W of a short recording is smaller than the spike term's partials, and an
+// allocation and its release cost 30 us of a set-up's 90.)
 struct Temps {
   glmr_ctx* c;
-  const size_t mark;
+  const size_t mark_w, mark_gp;
   std::vector<void*> own;
-  explicit Temps(glmr_ctx* c_) : c(c_), mark(c_->w_temps) {}
+  explicit Temps(glmr_ctx* c_) : c(c_), mark_w(c_->w_temps), mark_gp(c_->gp_temps) {}
   Temps(const Temps&) = delete;
+  static void* carve(void* base, size_t cap, size_t* used, size_t bytes) {
+    const size_t at = (*used + 255) & ~(size_t)255;
+    if (!base || at + bytes > cap) return nullptr;
+    *used = at + bytes;
+    return (unsigned char*)base + at;
+  }
   template <typename T>
   glmr_status get(T*& p, size_t n) {
-    const size_t at = (c->w_temps + 255) & ~(size_t)255, bytes = std::max<size_t>(n, 1) * sizeof(T);
-    if (c->W && at + bytes <= c->w_bytes) {
-      p = (T*)((unsigned char*)c->W + at);
-      c->w_temps = at + bytes;
-      return GLMR_OK;
-    }
-    p = nullptr;
+    const size_t bytes = std::max<size_t>(n, 1) * sizeof(T);
+    p = (T*)carve(c->W, c->w_bytes, &c->w_temps, bytes);
+    if (!p) p = (T*)carve(c->Gp, c->gp_bytes, &c->gp_temps, bytes);
+    if (p) return GLMR_OK;
     TRY(dalloc(c, p, n));
     own.push_back(p);
     return GLMR_OK;
   }
   ~Temps() {
     for (void* q : own) dfree(c, q);
-    c->w_temps = mark;
+    c->w_temps = mark_w;
+    c->gp_temps = mark_gp;
   }
 };
 
@@ -796,18 +803,17 @@ glmr_status ensure_workspace(glmr_ctx* c, bool want_grad, bool want_tau) {
   Slab s;
   const size_t wb = Np * (size_t)c->L * in_bytes(c->prec);
   s.want((unsigned char*&)c->W, wb);
-  c->w_bytes = wb;
   s.want(c->rowpart, tiles * Np);
   if (want_tau) s.want(c->rowpartV, tiles * Np);
   if (self_delayed(c)) s.want(c->gpart, tiles * Np);
-  if (want_grad) s.want((unsigned char*&)c->Gp, (size_t)c->max_splits * Np * Np * (fp ? 8 : 4));
+  const size_t gb = (size_t)c->max_splits * Np * Np * (fp ? 8 : 4);
+  if (want_grad) s.want((unsigned char*&)c->Gp, gb);
   if (use_rec(c, true) && want_grad) s.want(c->rec_head, (size_t)c->max_splits * Np);
   unsigned char* mem = nullptr;
   glmr_status st = s.get(c, &mem);
-  if (st != GLMR_OK) {
-    if (!c->W) c->w_bytes = 0;
-    return st;
-  }
+  c->w_bytes = c->W ? wb : 0;
+  c->gp_bytes = c->Gp ? gb : 0;
+  if (st != GLMR_OK) return st;
   if (mem) c->slabs.push_back(mem);
   // the others
   Slab o;
@@ -835,7 +841,7 @@ void drop_workspace(glmr_ctx* c) {
   for (unsigned char* p : c->slabs) dfree(c, p);
   c->slabs.clear();
   c->W = c->Gp = nullptr;
-  c->w_bytes = 0;
+  c->w_bytes = c->gp_bytes = 0;
   c->rowpart = c->rowpartV = c->gpart = c->rec_head = nullptr;
 }
 
