@@ -150,7 +150,7 @@ struct CarryArgs {
 };
 hipError_t launch_carries(const CarryArgs& c, hipStream_t st);
 
-// Spike lists of a raster, from its masks (recur.hip).
+// Spike lists of a raster, from its masks (spikes.hip).
 struct ListArgs {
   const uint64_t* masks;   // [planes][NS][Np]
   int planes;

@@ -29,7 +29,7 @@
 // from the L2), half of it vector and scalar issue (21 of the instructions a
 // bin are the exponential, 7 a spike); k_rec_gather 3.1 ms, LDS reads and the
 // phases that form a tile.  The dense kernels took 56 and 58 ms.  On the event
-// grid (FP64): k_rec_fwd_ev 0.128 ms at N = 150, 6.6e4 slots and 4.2 us per
+// grid (FP64): k_rec_fwd_ev 0.130 ms at N = 150, 6.6e4 slots and 4.1 us per
 // thousand slots at N = 1000, the FP64 arithmetic of the integrals and, with four
 // waves a SIMD, its latency (at N = 150 0.145 ms with one term more, 0.47 ms
 // written out per lane, with the closed forms as a call).
